@@ -1117,7 +1117,7 @@ def run_sort(args):
     # of a run (8 digit passes, HIP events), is reported beside it against HBM.
     k_avg = st["kernel_ms"] / max(1, runs)
     rows = st["chunk_rows"]
-    ach_hbm = 8 * 24.0 * rows / (k_avg * 1e6)       # per pass: histogram read 8 B, scatter 8 B in + 8 B out
+    ach_hbm = (8 + 8 * 16.0) * rows / (k_avg * 1e6)   # counts read 8 B, each pass 8 B in + 8 B out
     b_peak = cal["h2d_gbs"]
     duplex = cal["duplex_zcw_gbs"]
     link_bytes = 2 * 2 * 8.0 * n                    # each pass: every key in and back out
@@ -1132,9 +1132,9 @@ def run_sort(args):
                     "algorithmic_bytes": "per step: 16 B per key in each of the two passes (8 B in, 8 B out)",
                     "hbm_radix_run": {"achieved": ach_hbm, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                       "frac": ach_hbm / HBM_PEAK_GBS, "avg_launch_ms": k_avg, "rows_per_launch": rows,
-                                      "kernels": "8 digit passes of k_digit_hist, the three-launch scan, k_digit_scatter",
+                                      "kernels": "k_sweep_count, k_sweep_base and 8 digit passes of k_digit_sweep",
                                       "traffic_profile": PROFILE["sort_run"],
-                                      "algorithmic_bytes": "24 B per key per digit pass (8 B histogram read, 8 B read + 8 B written by the scatter), 8 passes"}},
+                                      "algorithmic_bytes": "8 B per key read by the digit counts, then 8 B read + 8 B written in each of 8 digit passes"}},
                    {"cpu_baseline": cpu,
                     "host_link": {"h2d_peak_measured_gbs": b_peak, "duplex_measured_gbs": cal["duplex_zcw_gbs"],
                                   "link_bytes_per_step": link_bytes, "model_ms": t_model * 1e3,

@@ -97,6 +97,22 @@ __device__ __forceinline__ uint32_t wave_granules(bool active, uint64_t a0, uint
   return mask_granules(__ballot(active), a0, es, shift);
 }
 
+// The lanes of `lanes` (a wave's ballot) whose low `bits` bits of id equal this lane's; every lane of
+// the wave calls it.  Each bit costs four vector instructions: the bit as 0 or -1, the ballot's
+// compare, and one three-input boolean per half of the mask (keep & ~(ballot ^ bit), truth table
+// 0x90).  Left to itself the compiler takes eleven.
+__device__ __forceinline__ unsigned long long same_id(uint32_t id, uint32_t bits, unsigned long long lanes) {
+  uint32_t lo = (uint32_t)lanes, hi = (uint32_t)(lanes >> 32);
+#pragma unroll
+  for (uint32_t b = 0; b < bits; ++b) {
+    const int bit = (int)(id << (31 - b)) >> 31;
+    const unsigned long long v = __ballot(bit < 0);
+    lo = (uint32_t)__builtin_amdgcn_bitop3_b32((int)lo, (int)(uint32_t)v, bit, 0x90);
+    hi = (uint32_t)__builtin_amdgcn_bitop3_b32((int)hi, (int)(uint32_t)(v >> 32), bit, 0x90);
+  }
+  return ((unsigned long long)hi << 32) | lo;
+}
+
 template <int NACC>
 __device__ __forceinline__ void block_flush(unsigned long long (&acc)[NACC], int nacc,
                                             unsigned long long* out) {

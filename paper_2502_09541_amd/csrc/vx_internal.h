@@ -109,6 +109,7 @@ struct vx_ctx {
   // readbacks (error flags) that are read beside it
   uint64_t* host_acc = nullptr;
   uint64_t* host_small = nullptr;
+  uint64_t* host_small_dev = nullptr;  // host_small as the device sees it: kernels store there directly
   // device-to-host copies of intermediate results (partition pass write-back)
   hipStream_t d2h = nullptr;
   // pinned host memory for intermediates that live in CPU memory (grow-only, kept until destroy)

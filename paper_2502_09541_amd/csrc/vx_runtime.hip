@@ -259,7 +259,7 @@ vx_status vx_ctx_create(int device, void* arena, uint64_t arena_bytes, void* str
   }
   if (hipStreamCreateWithFlags(&c->copy, hipStreamNonBlocking) != hipSuccess ||
       hipStreamCreateWithFlags(&c->d2h, hipStreamNonBlocking) != hipSuccess ||
-      hipHostMalloc((void**)&c->host_acc, (c->dev_acc_words + kHostSmallWords) * 8, hipHostMallocDefault) !=
+      hipHostMalloc((void**)&c->host_acc, (c->dev_acc_words + kHostSmallWords) * 8, hipHostMallocMapped) !=
           hipSuccess) {
     if (c->own_compute) (void)hipStreamDestroy(c->compute);
     if (c->copy) (void)hipStreamDestroy(c->copy);
@@ -269,6 +269,14 @@ vx_status vx_ctx_create(int device, void* arena, uint64_t arena_bytes, void* str
     return VX_EHIP;
   }
   c->host_small = c->host_acc + c->dev_acc_words;
+  void* mapped = nullptr;
+  if (hipHostGetDevicePointer(&mapped, c->host_acc, 0) != hipSuccess || !mapped) {
+    (void)hipGetLastError();
+    vx_ctx_destroy(c);
+    set_error("vx_ctx_create: pinned scratch has no device mapping");
+    return VX_EHIP;
+  }
+  c->host_small_dev = (uint64_t*)mapped + c->dev_acc_words;
   *out = c;
   return VX_OK;
 }

@@ -15,8 +15,10 @@
 #include <algorithm>
 #include <cstring>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
+#include "vx_device.h"
 #include "vx_part.h"
 #include "vx_pipeline.h"
 
@@ -109,72 +111,64 @@ __global__ void __launch_bounds__(256) k_store4(const uint32_t* src, uint32_t* d
     dst[i] = src[i];
 }
 
-// ---------------------------------------------------------------- LSD radix digit pass
+// ---------------------------------------------------------------- LSD radix digit passes
 //
-// One workgroup per tile of 8192 consecutive keys; wave w holds keys [w*1024, (w+1)*1024) of the
-// tile, 16 per lane in steps of 64.  The histogram launch counts each tile's keys per digit into
-// hist[t * 256 + d] (tile-major: a workgroup's 256 counts are one contiguous store).  A column
-// scan turns them into offs[t * 256 + d], where tile t's first key of digit d goes: the keys of
-// every lower digit plus those of digit d in earlier tiles.  It walks the tiles in blocks, one
-// thread per digit, so its loads and stores are contiguous across the threads.  The scatter
-// launch ranks the tile's keys by digit in input order
-// (ballots give a lane its rank among the step's lanes of the same digit, a per-wave LDS counter
-// carries the count across steps), sorts the tile into LDS by that rank, and writes it out in
-// LDS order: each digit's keys of the tile form one run of consecutive output addresses, about 32
-// keys long, so the stores fill whole lines.  A stable pass, as LSD radix sorting needs.
-constexpr uint32_t kDigitThreads = 512;
+// Each 8-bit digit pass reads every key once and writes it once: bytes in all, 16 per int64 key and
+// pass plus 8 for the digit counts of the whole sort.  A pass is one launch (k_digit_sweep) whose
+// workgroups take tiles of consecutive keys in order, by a ticket.  A tile ranks its keys by digit
+// in input order, publishes its count of every digit, and finds where each digit's keys go by
+// adding up the counts of the tiles before it, back to one whose running total is known
+// (decoupled look-back: Merrill and Garland, "Single-pass parallel prefix scan with decoupled
+// look-back", 2016; for radix sorting: Adinets and Merrill, "Onesweep", 2022).  The counts of every
+// digit of the whole run, which give each digit's first position, come from one pass before
+// (k_sweep_count, k_sweep_base).  A tile is sorted by digit in LDS and written in LDS order, so
+// each digit's keys of a tile are one run of consecutive addresses (64 keys on average at 16384).
+//
+// 16.0 M int64 keys in one run: 567 us of kernels (k_sweep_count 42 us, 3.0 TB/s; a sweep about
+// 65 us, 3.9 TB/s read and written, against 4.8 TB/s of a large copy), where a histogram launch per
+// pass, a three-launch column scan and a scatter took 1185 us (44 + 36 + 68 us a pass).  What bounds
+// a sweep is the ranking: with 11 vector instructions per digit bit instead of 4 (same_id) it took
+// 94 us.  The look-back is hidden behind other tiles' work: windows of 4, 8, 16 and 32 tiles gave
+// 752, 751, 779 and 846 us.
+constexpr uint32_t kDigitThreads = 1024;
 constexpr uint32_t kDigitWaves = kDigitThreads / 64;
-constexpr uint32_t kDigitItems = 16;                            // keys per lane
-constexpr uint32_t kDigitTile = kDigitThreads * kDigitItems;    // keys per workgroup tile
-constexpr uint32_t kWaveKeys = 64 * kDigitItems;                // keys per wave, contiguous
+constexpr uint32_t kLocalSortMax = 8192;                        // runs sorted by one workgroup in LDS
+constexpr uint32_t kCountThreads = 1024;
+constexpr uint32_t kCountGroups = 256;                          // workgroups of k_sweep_count, at most
 
-uint64_t digit_tiles(uint64_t rows) { return std::max<uint64_t>(1, (rows + kDigitTile - 1) / kDigitTile); }
-
-// 8 bits at `shift` of the key's order-preserving unsigned image (sign bit flipped)
-__device__ __forceinline__ uint32_t digit_of(int32_t k, uint32_t shift) {
-  return (((uint32_t)k ^ 0x80000000u) >> shift) & 255u;
+// byte `pass` of the key's order-preserving unsigned image (sign bit flipped)
+__device__ __forceinline__ uint32_t digit_of(int32_t k, uint32_t pass) {
+  return (((uint32_t)k ^ 0x80000000u) >> (8 * pass)) & 255u;
 }
-__device__ __forceinline__ uint32_t digit_of(int64_t k, uint32_t shift) {
-  return (uint32_t)((((uint64_t)k ^ 0x8000000000000000ull) >> shift) & 255u);
+__device__ __forceinline__ uint32_t digit_of(int64_t k, uint32_t pass) {
+  const uint32_t w = pass < 4 ? (uint32_t)(uint64_t)k : (uint32_t)((uint64_t)k >> 32) ^ 0x80000000u;
+  return (w >> (8 * (pass & 3))) & 255u;
 }
 
-// the valid lanes of the wave whose digit equals this lane's
-__device__ __forceinline__ unsigned long long same_digit(uint32_t d, bool valid) {
-  unsigned long long m = __ballot(valid);
+// this lane's keys, 64 apart from `first` on (zero past n); a full tile loads unconditionally
+template <bool FULL, typename K, uint32_t ITEMS>
+__device__ __forceinline__ void digit_load(const K* in, uint64_t n, uint64_t first, K (&k)[ITEMS]) {
+  if (FULL) {
 #pragma unroll
-  for (uint32_t b = 0; b < 8; ++b) {
-    const bool bit = (d >> b) & 1u;
-    const unsigned long long v = __ballot(bit);
-    m &= bit ? v : ~v;
-  }
-  return m;
-}
-
-// this lane's keys of tile t (zero past n); a full tile loads unconditionally
-template <typename K>
-__device__ __forceinline__ void digit_load(const K* in, uint64_t n, uint64_t first, bool full,
-                                           K (&k)[kDigitItems]) {
-  if (full) {
-#pragma unroll
-    for (uint32_t j = 0; j < kDigitItems; ++j) k[j] = __builtin_nontemporal_load(in + first + j * 64);
+    for (uint32_t j = 0; j < ITEMS; ++j) k[j] = __builtin_nontemporal_load(in + first + j * 64);
   } else {
 #pragma unroll
-    for (uint32_t j = 0; j < kDigitItems; ++j) k[j] = first + j * 64 < n ? in[first + j * 64] : K(0);
+    for (uint32_t j = 0; j < ITEMS; ++j) k[j] = first + j * 64 < n ? in[first + j * 64] : K(0);
   }
 }
 
 // rank[j] = number of this wave's earlier keys with key j's digit; cnt[d] ends as the wave's
 // count of digit d (cnt is the wave's own row, zeroed by the caller)
-template <typename K>
-__device__ __forceinline__ void digit_rank(const K (&k)[kDigitItems], uint64_t n, uint64_t first,
-                                           uint32_t shift, uint32_t* cnt, uint32_t (&rank)[kDigitItems]) {
+template <bool FULL, typename K, uint32_t ITEMS>
+__device__ __forceinline__ void digit_rank(const K (&k)[ITEMS], uint64_t n, uint64_t first, uint32_t pass,
+                                           uint32_t* cnt, uint32_t (&rank)[ITEMS]) {
   const uint32_t lane = threadIdx.x & 63;
   const unsigned long long lower = (1ull << lane) - 1;
 #pragma unroll
-  for (uint32_t j = 0; j < kDigitItems; ++j) {
-    const bool valid = first + j * 64 < n;
-    const uint32_t d = digit_of(k[j], shift);
-    const unsigned long long peers = same_digit(d, valid);
+  for (uint32_t j = 0; j < ITEMS; ++j) {
+    const bool valid = FULL || first + j * 64 < n;
+    const uint32_t d = digit_of(k[j], pass);
+    const unsigned long long peers = same_id(d, 8, FULL ? ~0ull : __ballot(valid));
     const uint32_t below = (uint32_t)__popcll(peers & lower);
     const uint32_t c = valid ? cnt[d] : 0u;
     rank[j] = c + below;
@@ -185,168 +179,281 @@ __device__ __forceinline__ void digit_rank(const K (&k)[kDigitItems], uint64_t n
   }
 }
 
-template <typename K>
-__global__ void __launch_bounds__(kDigitThreads) k_digit_hist(const K* in, uint64_t n, uint32_t shift,
-                                                             uint32_t* hist) {
-  __shared__ uint32_t cnt[kDigitWaves][256];
+// For threads 0..255 (thread d: digit d), from the waves' counts cnt[w][d]: `tot` the tile's count
+// of d, `x` the inclusive sum of the counts within the thread's wave; the waves' sums go to wsum,
+// read after the caller's barrier.
+template <uint32_t WAVES>
+__device__ __forceinline__ void digit_totals(const uint32_t (*cnt)[256], uint32_t* wsum, uint32_t& tot, uint32_t& x) {
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t t = blockIdx.x;
-  for (uint32_t i = threadIdx.x; i < kDigitWaves * 256; i += kDigitThreads) (&cnt[0][0])[i] = 0;
-  __syncthreads();
-  const uint64_t first = t * kDigitTile + wave * kWaveKeys + lane;
-  K k[kDigitItems];
-  uint32_t rank[kDigitItems];
-  digit_load(in, n, first, (t + 1) * kDigitTile <= n, k);
-  digit_rank(k, n, first, shift, cnt[wave], rank);
-  __syncthreads();
-  if (threadIdx.x < 256) {
-    uint32_t c = 0;
-#pragma unroll
-    for (uint32_t w = 0; w < kDigitWaves; ++w) c += cnt[w][threadIdx.x];
-    hist[t * 256 + threadIdx.x] = c;
-  }
-}
-
-// Column scan of the tile-major histogram, in blocks of `per` tiles (at most kColBlocks blocks;
-// thread d of every launch handles digit d).  part holds kColBlocks * 256 words.
-constexpr uint32_t kColBlocks = 128;
-
-uint64_t col_per(uint64_t tiles) { return std::max<uint64_t>(1, (tiles + kColBlocks - 1) / kColBlocks); }
-
-// part[b * 256 + d] = block b's keys of digit d
-__global__ void __launch_bounds__(256) k_digit_colsum(const uint32_t* hist, uint64_t tiles, uint64_t per,
-                                                      unsigned long long* part) {
-  const uint64_t t0 = blockIdx.x * per, t1 = t0 + per < tiles ? t0 + per : tiles;
-  unsigned long long s = 0;
-  uint64_t t = t0;
-  for (; t + 8 <= t1; t += 8) {   // eight independent loads in flight
-    uint32_t v[8];
-#pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) v[u] = hist[(t + u) * 256 + threadIdx.x];
-#pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) s += v[u];
-  }
-  for (; t < t1; ++t) s += hist[t * 256 + threadIdx.x];
-  part[(uint64_t)blockIdx.x * 256 + threadIdx.x] = s;
-}
-
-// One workgroup: part[b * 256 + d] becomes the output position of block b's first key of digit d.
-__global__ void __launch_bounds__(256) k_digit_colbase(unsigned long long* part, uint32_t nb) {
-  __shared__ unsigned long long ws[4];
-  const uint32_t d = threadIdx.x, lane = d & 63, wave = d >> 6;
-  unsigned long long total = 0;
-  uint32_t b = 0;
-  for (; b + 8 <= nb; b += 8) {   // eight independent loads in flight
-    unsigned long long v[8];
-#pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) v[u] = part[(uint64_t)(b + u) * 256 + d];
-#pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) {
-      part[(uint64_t)(b + u) * 256 + d] = total;
-      total += v[u];
-    }
-  }
-  for (; b < nb; ++b) {
-    const unsigned long long v = part[(uint64_t)b * 256 + d];
-    part[(uint64_t)b * 256 + d] = total;
-    total += v;
-  }
-  unsigned long long x = total;   // exclusive scan of the digits' totals over the workgroup
-#pragma unroll
-  for (uint32_t o = 1; o < 64; o <<= 1) {
-    const unsigned long long y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) ws[wave] = x;
-  __syncthreads();
-  unsigned long long base = x - total;
-  for (uint32_t w = 0; w < wave; ++w) base += ws[w];
-  for (uint32_t b = 0; b < nb; ++b) part[(uint64_t)b * 256 + d] += base;
-}
-
-// offs[t * 256 + d] = output position of tile t's first key of digit d
-__global__ void __launch_bounds__(256) k_digit_colapply(const uint32_t* hist, uint64_t tiles, uint64_t per,
-                                                        const unsigned long long* part, unsigned long long* offs) {
-  const uint64_t t0 = blockIdx.x * per, t1 = t0 + per < tiles ? t0 + per : tiles;
-  unsigned long long run = part[(uint64_t)blockIdx.x * 256 + threadIdx.x];
-  uint64_t t = t0;
-  for (; t + 8 <= t1; t += 8) {
-    uint32_t v[8];
-#pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) v[u] = hist[(t + u) * 256 + threadIdx.x];
-#pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) {
-      offs[(t + u) * 256 + threadIdx.x] = run;
-      run += v[u];
-    }
-  }
-  for (; t < t1; ++t) {
-    offs[t * 256 + threadIdx.x] = run;
-    run += hist[t * 256 + threadIdx.x];
-  }
-}
-
-// offs[t * 256 + d] = output position of tile t's first key of digit d
-template <typename K>
-__global__ void __launch_bounds__(kDigitThreads) k_digit_scatter(const K* in, K* out, uint64_t n, uint32_t shift,
-                                                                const unsigned long long* offs) {
-  __shared__ K stage[kDigitTile];
-  __shared__ uint32_t cnt[kDigitWaves][256];
-  __shared__ uint32_t dstart[256];
-  __shared__ uint32_t wsum[4];
-  __shared__ unsigned long long gbase[256];
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t t = blockIdx.x;
-  for (uint32_t i = threadIdx.x; i < kDigitWaves * 256; i += kDigitThreads) (&cnt[0][0])[i] = 0;
-  __syncthreads();
-  const uint64_t first = t * kDigitTile + wave * kWaveKeys + lane;
-  const bool full = (t + 1) * kDigitTile <= n;
-  K k[kDigitItems];
-  uint32_t rank[kDigitItems];
-  digit_load(in, n, first, full, k);
-  digit_rank(k, n, first, shift, cnt[wave], rank);
-  __syncthreads();
-  // per digit: the waves' exclusive offsets, then the digits' exclusive offsets in the tile
-  uint32_t tot = 0;
+  tot = 0;
   if (threadIdx.x < 256) {
 #pragma unroll
-    for (uint32_t w = 0; w < kDigitWaves; ++w) {
-      const uint32_t c = cnt[w][threadIdx.x];
-      cnt[w][threadIdx.x] = tot;
-      tot += c;
-    }
+    for (uint32_t w = 0; w < WAVES; ++w) tot += cnt[w][threadIdx.x];
   }
-  uint32_t x = tot;
+  x = tot;
 #pragma unroll
   for (uint32_t o = 1; o < 64; o <<= 1) {
     const uint32_t y = __shfl_up(x, o, 64);
     if (lane >= o) x += y;
   }
   if (threadIdx.x < 256 && lane == 63) wsum[wave] = x;
+}
+
+// After the barrier, for the same threads: cnt[w][d] becomes the place in the sorted tile of wave
+// w's first key of digit d; returns the place of the tile's first key of d.
+template <uint32_t WAVES>
+__device__ __forceinline__ uint32_t digit_places(uint32_t (*cnt)[256], const uint32_t* wsum, uint32_t tot, uint32_t x) {
+  uint32_t e = x - tot;
+  for (uint32_t w = 0; w < threadIdx.x >> 6; ++w) e += wsum[w];
+  uint32_t at = e;
+#pragma unroll
+  for (uint32_t w = 0; w < WAVES; ++w) {
+    const uint32_t c = cnt[w][threadIdx.x];
+    cnt[w][threadIdx.x] = at;
+    at += c;
+  }
+  return e;
+}
+
+// Counts of all the keys' digits, part[(b * sizeof(K) + p) * 256 + d] for workgroup b, pass p, digit
+// d; also clears the look-back words and the tickets of the passes that follow.  A wave whose keys
+// share a digit (the high digits of small keys) adds its count at once instead of 64 times.
+template <typename K>
+__global__ void __launch_bounds__(kCountThreads) k_sweep_count(const K* in, uint64_t n, uint32_t* part,
+                                                     unsigned long long* status, uint64_t status_words,
+                                                     uint32_t* tickets) {
+  constexpr uint32_t P = sizeof(K), U = 8;
+  __shared__ uint32_t cnt[P][256];
+  for (uint32_t i = threadIdx.x; i < P * 256; i += kCountThreads) (&cnt[0][0])[i] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < P) tickets[threadIdx.x] = 0;
+  for (uint64_t i = blockIdx.x * (uint64_t)kCountThreads + threadIdx.x; i < status_words; i += (uint64_t)gridDim.x * kCountThreads) status[i] = 0;
   __syncthreads();
-  if (threadIdx.x < 256) {
-    uint32_t e = x - tot;
-    for (uint32_t w = 0; w < wave; ++w) e += wsum[w];
-    dstart[threadIdx.x] = e;
-    gbase[threadIdx.x] = offs[t * 256 + threadIdx.x] - e;
+  auto add = [&](K k) {
+#pragma unroll
+    for (uint32_t p = 0; p < P; ++p) {
+      const uint32_t d = digit_of(k, p);
+      const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
+      const unsigned long long active = __ballot(true), same = __ballot(d == d0);
+      if (same == active) {
+        if ((threadIdx.x & 63) == (uint32_t)__builtin_ctzll(active)) atomicAdd(&cnt[p][d], (uint32_t)__popcll(active));
+      } else {
+        atomicAdd(&cnt[p][d], 1u);
+      }
+    }
+  };
+  const uint64_t step = (uint64_t)gridDim.x * kCountThreads * U;
+  for (uint64_t base = blockIdx.x * (uint64_t)kCountThreads * U + threadIdx.x; base < n; base += step) {
+    if (base - threadIdx.x + (uint64_t)kCountThreads * U <= n) {
+      K k[U];
+#pragma unroll
+      for (uint32_t j = 0; j < U; ++j) k[j] = in[base + j * kCountThreads];
+#pragma unroll
+      for (uint32_t j = 0; j < U; ++j) add(k[j]);
+    } else {
+      for (uint32_t j = 0; j < U; ++j)
+        if (base + j * kCountThreads < n) add(in[base + j * kCountThreads]);
+    }
   }
   __syncthreads();
+  for (uint32_t i = threadIdx.x; i < P * 256; i += kCountThreads) part[blockIdx.x * (P * 256) + i] = (&cnt[0][0])[i];
+}
+
+// Workgroup p: base[p * 256 + d] = keys of the run whose digit in pass p is below d.
+__global__ void __launch_bounds__(1024) k_sweep_base(const uint32_t* part, uint32_t groups, unsigned long long* base) {
+  __shared__ unsigned long long seg[4][256];
+  __shared__ unsigned long long ws[4];
+  const uint32_t d = threadIdx.x & 255, q = threadIdx.x >> 8, lane = threadIdx.x & 63;
+  const uint32_t* col = part + blockIdx.x * 256 + d;
+  const uint32_t stride = gridDim.x * 256;
+  unsigned long long s = 0;
+  uint32_t g = q;
+  for (; g + 60 < groups; g += 64) {   // sixteen loads in flight
+    uint32_t v[16];
 #pragma unroll
-  for (uint32_t j = 0; j < kDigitItems; ++j)
-    if (first + j * 64 < n) {
-      const uint32_t d = digit_of(k[j], shift);
-      stage[dstart[d] + cnt[wave][d] + rank[j]] = k[j];
-    }
-  __syncthreads();
-  const uint32_t m = full ? kDigitTile : (uint32_t)(n - t * kDigitTile);
+    for (uint32_t u = 0; u < 16; ++u) v[u] = col[(uint64_t)(g + 4 * u) * stride];
 #pragma unroll
-  for (uint32_t j = 0; j < kDigitItems; ++j) {
-    const uint32_t p = j * kDigitThreads + threadIdx.x;
-    if (p < m) {
-      const K v = stage[p];
-      out[gbase[digit_of(v, shift)] + p] = v;
-    }
+    for (uint32_t u = 0; u < 16; ++u) s += v[u];
   }
+  for (; g < groups; g += 4) s += col[(uint64_t)g * stride];
+  seg[q][d] = s;
+  __syncthreads();
+  unsigned long long tot = 0, x = 0;
+  if (q == 0) {
+    tot = seg[0][d] + seg[1][d] + seg[2][d] + seg[3][d];
+    x = tot;
+#pragma unroll
+    for (uint32_t o = 1; o < 64; o <<= 1) {
+      const unsigned long long y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    if (lane == 63) ws[threadIdx.x >> 6] = x;
+  }
+  __syncthreads();
+  if (q == 0) {
+    unsigned long long b = x - tot;
+    for (uint32_t w = 0; w < threadIdx.x >> 6; ++w) b += ws[w];
+    base[blockIdx.x * 256 + d] = b;
+  }
+}
+
+// A look-back word: a tag in the top byte (2 * pass + 1: the tile's own count; 2 * pass + 2: the
+// digit's position after this tile) and the value below.  Tags differ from pass to pass, so the
+// words are cleared once per sort.  A word is written and read whole (64 bits, device scope), and
+// nothing else passes between workgroups through it, so no fence is needed.
+constexpr uint32_t kTagShift = 56;
+constexpr unsigned long long kTagValue = (1ull << kTagShift) - 1;
+constexpr uint32_t kLookWindow = 8;        // tiles read ahead in one look-back step
+constexpr uint32_t kLookSpins = 1u << 22;  // polls before a workgroup gives up (seconds; never in a sound run)
+
+__device__ __forceinline__ unsigned long long look_load(const unsigned long long* w) {
+  return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void look_store(unsigned long long* w, uint32_t tag, unsigned long long v) {
+  __hip_atomic_store(w, ((unsigned long long)tag << kTagShift) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Position of tile t's first key of digit d = threadIdx.x: the counts of the tiles before t, back to
+// the nearest one whose running position is known (tile 0 starts from the digit's base).  Tiles are
+// taken in ticket order, so every tile waited for is running or done and publishes its count before
+// it waits itself: the wait ends.  It is bounded all the same (`stall` is set, and the sort fails).
+__device__ __forceinline__ unsigned long long look_back(const unsigned long long* status, uint64_t t, uint32_t pass,
+                                                        uint32_t* stall) {
+  const uint32_t own = 2 * pass + 1, known = 2 * pass + 2;
+  unsigned long long sum = 0;
+  int64_t look = (int64_t)t - 1;
+  uint32_t spins = 0;
+  for (;;) {
+    unsigned long long w[kLookWindow];
+#pragma unroll
+    for (uint32_t i = 0; i < kLookWindow; ++i) {
+      const int64_t at = look - (int64_t)i;
+      w[i] = look_load(status + (uint64_t)(at > 0 ? at : 0) * 256 + threadIdx.x);
+    }
+    uint32_t took = 0;
+    bool done = false;
+#pragma unroll
+    for (uint32_t i = 0; i < kLookWindow; ++i) {
+      const uint32_t tag = (uint32_t)(w[i] >> kTagShift);
+      if (!done && took == i && (tag == own || tag == known)) {
+        sum += w[i] & kTagValue;
+        took = i + 1;
+        done = tag == known;    // tile 0 is always known, so nothing past it is taken
+      }
+    }
+    if (done) return sum;
+    look -= (int64_t)took;
+    if (took == 0 && ++spins >= kLookSpins) {
+      __hip_atomic_store(stall, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      return sum;
+    }
+    if (took == 0 && (spins & 4095u) == 4095u &&
+        __hip_atomic_load(stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0)
+      return sum;
+  }
+}
+
+// One digit pass over the run; tiles of kDigitThreads * ITEMS keys.  Smaller tiles for short runs,
+// so that they still fill the chip (digit_tile).
+template <typename K, uint32_t ITEMS>
+__global__ void __launch_bounds__(kDigitThreads) k_digit_sweep(const K* in, K* out, uint64_t n, uint32_t pass,
+                                                              const unsigned long long* base,
+                                                              unsigned long long* status, uint32_t* tickets,
+                                                              uint32_t* stall) {
+  constexpr uint32_t TILE = kDigitThreads * ITEMS;
+  __shared__ K stage[TILE];
+  __shared__ uint32_t cnt[kDigitWaves][256];
+  __shared__ uint32_t wsum[4];
+  __shared__ unsigned long long gbase[256];
+  __shared__ uint32_t ticket;
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (threadIdx.x == 0) ticket = atomicAdd(tickets + pass, 1u);
+  for (uint32_t i = threadIdx.x; i < kDigitWaves * 256; i += kDigitThreads) (&cnt[0][0])[i] = 0;
+  __syncthreads();
+  const uint64_t t = ticket;
+  const uint64_t first = t * TILE + wave * (64 * ITEMS) + lane;
+  auto tile = [&](auto whole) {
+    constexpr bool FULL = decltype(whole)::value;
+    K k[ITEMS];
+    uint32_t rank[ITEMS];
+    digit_load<FULL>(in, n, first, k);
+    digit_rank<FULL>(k, n, first, pass, cnt[wave], rank);
+    __syncthreads();
+    uint32_t tot, x;
+    digit_totals<kDigitWaves>(cnt, wsum, tot, x);
+    unsigned long long pos = 0;
+    if (threadIdx.x < 256) {
+      unsigned long long* mine = status + t * 256 + threadIdx.x;
+      if (t == 0) {
+        pos = base[pass * 256 + threadIdx.x];
+        look_store(mine, 2 * pass + 2, pos + tot);
+      } else {
+        look_store(mine, 2 * pass + 1, tot);
+      }
+    }
+    __syncthreads();
+    uint32_t e = 0;
+    if (threadIdx.x < 256) e = digit_places<kDigitWaves>(cnt, wsum, tot, x);
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < ITEMS; ++j)
+      if (FULL || first + j * 64 < n) stage[cnt[wave][digit_of(k[j], pass)] + rank[j]] = k[j];
+    if (threadIdx.x < 256) {
+      if (t != 0) {
+        pos = look_back(status, t, pass, stall);
+        look_store(status + t * 256 + threadIdx.x, 2 * pass + 2, pos + tot);
+      }
+      gbase[threadIdx.x] = pos - e;
+    }
+    __syncthreads();
+    const uint32_t m = FULL ? TILE : (uint32_t)(n - t * TILE);
+#pragma unroll
+    for (uint32_t j = 0; j < ITEMS; ++j) {
+      const uint32_t p = j * kDigitThreads + threadIdx.x;
+      if (FULL || p < m) {
+        const K v = stage[p];
+        out[gbase[digit_of(v, pass)] + p] = v;
+      }
+    }
+  };
+  if ((t + 1) * TILE <= n) tile(std::true_type{});
+  else tile(std::false_type{});
+}
+
+// A whole run of at most kLocalSortMax keys, sorted by one workgroup: every digit pass in LDS, one
+// read and one write of memory and one launch (the launches bound such a run).  A pass whose keys
+// all share the digit is left out.  in == out is fine: every key is read before one is written.
+template <typename K>
+__global__ void __launch_bounds__(1024) k_local_sort(const K* in, K* out, uint32_t n) {
+  constexpr uint32_t T = 1024, ITEMS = kLocalSortMax / T, W = T / 64;
+  __shared__ K stage[kLocalSortMax];
+  __shared__ uint32_t cnt[W][256];
+  __shared__ uint32_t wsum[4];
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t first = wave * (64 * ITEMS) + lane;
+  K k[ITEMS];
+  uint32_t rank[ITEMS];
+  digit_load<false>(in, (uint64_t)n, (uint64_t)first, k);
+  for (uint32_t pass = 0; pass < sizeof(K); ++pass) {
+    for (uint32_t i = threadIdx.x; i < W * 256; i += T) (&cnt[0][0])[i] = 0;
+    __syncthreads();
+    digit_rank<false>(k, (uint64_t)n, (uint64_t)first, pass, cnt[wave], rank);
+    __syncthreads();
+    uint32_t tot, x;
+    digit_totals<W>(cnt, wsum, tot, x);
+    if (__syncthreads_or(threadIdx.x < 256 && tot == n)) continue;   // one digit value: the order stands
+    if (threadIdx.x < 256) digit_places<W>(cnt, wsum, tot, x);
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < ITEMS; ++j)
+      if (first + j * 64 < n) stage[cnt[wave][digit_of(k[j], pass)] + rank[j]] = k[j];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < ITEMS; ++j)
+      if (first + j * 64 < n) k[j] = stage[first + j * 64];
+  }
+#pragma unroll
+  for (uint32_t j = 0; j < ITEMS; ++j)
+    if (first + j * 64 < n) out[first + j * 64] = k[j];
 }
 
 unsigned grid_of(const vx_ctx* ctx, uint64_t items, uint64_t per_block, uint64_t per_cu) {
@@ -408,41 +515,85 @@ void merge_cuts_t(const K* const* runs, const uint64_t* len, uint32_t n_runs, ui
   }
 }
 
-// LSD radix sort of rows keys from src (left unchanged) into dst, through alt: digit passes of 8
-// bits over the key's order-preserving image (int64: 8 passes, int32: 4), each a histogram
-// launch, the three-launch column scan and a tile scatter.  Passes alternate between dst and alt
-// so the last one writes dst.  hist holds 256 * digit_tiles(rows) entries, offs that many plus
-// 256 * kColBlocks (the column scan's block sums, after the offsets).
+// Device scratch of one run's radix sort: look-back words, digit bases, tickets (digit_tile's rule
+// needs at most 2048 bytes of words per 4096 keys up to 2^18 keys, and per 8192 keys beyond).
+uint64_t sweep_bytes(uint64_t rows) {
+  return 3072 * std::max<uint64_t>(1, (rows + 8191) / 8192) + 262144;
+}
+
+// Keys per tile of a digit pass.  A short run in large tiles leaves compute units idle; a long one in
+// small tiles writes shorter runs per digit and looks back over more tiles.  Sort kernels of one run,
+// int64 keys, us at tiles of 2048 / 4096 / 8192 / 16384: 20,000 keys 58 / 64 / 77 / 111; 262,144
+// keys - / 92 / 96 / 120; 1.0 M - / 141 / 130 / 148; 2.0 M - / 196 / 159 / 167; 4.0 M - / 299 / 249 /
+// 191; 16.0 M - / 844 / 714 / 566.
+uint32_t digit_tile(uint64_t rows) {
+  return rows <= (1ull << 16) ? 2048 : rows <= (1ull << 18) ? 4096 : rows <= (1ull << 21) ? 8192 : 16384;
+}
+
+struct SweepScratch {
+  unsigned long long* base;     // 8 * 256
+  uint32_t* tickets;            // 8
+  unsigned long long* status;   // 256 per tile
+  explicit SweepScratch(uint8_t* p)
+      : base((unsigned long long*)p), tickets((uint32_t*)(p + 16384)), status((unsigned long long*)(p + 16640)) {}
+};
+
+// LSD radix sort of rows keys from src into dst, through alt: digit passes of 8 bits over the key's
+// order-preserving image (int64: 8 passes, int32: 4).  Passes alternate between dst and alt so the
+// last one writes dst; the first writes alt, so src may be dst, and is left unchanged if it is not.
+// The digit counts of k_sweep_count sit in alt until the first pass overwrites it.  scratch holds
+// sweep_bytes(rows); *stall is a host-mapped word that the caller clears and reads when done.
+// *launches grows by the launches made.
 template <typename K>
-vx_status radix_sort_keys(const K* src, K* alt, K* dst, uint64_t rows, uint32_t* hist, unsigned long long* offs,
-                          vx_ctx* ctx, hipStream_t s) {
-  const uint32_t passes = sizeof(K);
-  const uint64_t tiles = digit_tiles(rows);
-  VX_CHECK(tiles < (1ull << 31), VX_EINVAL, "sort: run of %llu keys is too long", (unsigned long long)rows);
-  const uint64_t per = col_per(tiles);
-  const unsigned nb = (unsigned)((tiles + per - 1) / per);   // <= kColBlocks
-  unsigned long long* part = offs + 256 * tiles;
-  (void)ctx;
+vx_status radix_sort_keys(const K* src, K* alt, K* dst, uint64_t rows, uint8_t* scratch, uint32_t* stall,
+                          uint64_t* launches, hipStream_t s) {
+  constexpr uint32_t passes = sizeof(K);
+  VX_CHECK(rows < (1ull << 44), VX_EINVAL, "sort: run of %llu keys is too long", (unsigned long long)rows);
+  if (rows <= kLocalSortMax) {
+    hipLaunchKernelGGL(k_local_sort<K>, dim3(1), dim3(1024), 0, s, src, dst, (uint32_t)rows);
+    VX_HIP(hipGetLastError());
+    ++*launches;
+    return VX_OK;
+  }
+  const uint32_t tile = digit_tile(rows);
+  const uint64_t tiles = (rows + tile - 1) / tile;
+  SweepScratch w(scratch);
+  // 256 * sizeof(K) counts of 4 bytes per workgroup must fit alt: at most one workgroup per 2048 keys
+  const unsigned groups = (unsigned)std::min<uint64_t>(kCountGroups, rows / 2048);
+  uint32_t* part = (uint32_t*)alt;
+  hipLaunchKernelGGL(k_sweep_count<K>, dim3(groups), dim3(kCountThreads), 0, s, src, rows, part, w.status, tiles * 256,
+                     w.tickets);
+  hipLaunchKernelGGL(k_sweep_base, dim3(passes), dim3(1024), 0, s, part, groups, w.base);
   const K* in = src;
   for (uint32_t p = 0; p < passes; ++p) {
     K* out = ((passes - 1 - p) % 2 == 0) ? dst : alt;
-    hipLaunchKernelGGL(k_digit_hist<K>, dim3((unsigned)tiles), dim3(kDigitThreads), 0, s, in, rows, 8 * p, hist);
-    hipLaunchKernelGGL(k_digit_colsum, dim3(nb), dim3(256), 0, s, hist, tiles, per, part);
-    hipLaunchKernelGGL(k_digit_colbase, dim3(1), dim3(256), 0, s, part, nb);
-    hipLaunchKernelGGL(k_digit_colapply, dim3(nb), dim3(256), 0, s, hist, tiles, per, part, offs);
-    hipLaunchKernelGGL(k_digit_scatter<K>, dim3((unsigned)tiles), dim3(kDigitThreads), 0, s, in, out, rows, 8 * p,
-                       offs);
+    const dim3 grid((unsigned)tiles), block(kDigitThreads);
+    switch (tile) {
+      case 2048:
+        hipLaunchKernelGGL((k_digit_sweep<K, 2>), grid, block, 0, s, in, out, rows, p, w.base, w.status, w.tickets, stall);
+        break;
+      case 4096:
+        hipLaunchKernelGGL((k_digit_sweep<K, 4>), grid, block, 0, s, in, out, rows, p, w.base, w.status, w.tickets, stall);
+        break;
+      case 8192:
+        hipLaunchKernelGGL((k_digit_sweep<K, 8>), grid, block, 0, s, in, out, rows, p, w.base, w.status, w.tickets, stall);
+        break;
+      default:
+        hipLaunchKernelGGL((k_digit_sweep<K, 16>), grid, block, 0, s, in, out, rows, p, w.base, w.status, w.tickets, stall);
+        break;
+    }
     VX_HIP(hipGetLastError());
     in = out;
   }
+  *launches += 2 + passes;
   return VX_OK;
 }
 
-vx_status radix_sort_run(vx_ctx* ctx, const void* src, void* alt, void* dst, uint64_t rows, uint32_t ks,
-                         uint32_t* hist, unsigned long long* offs, hipStream_t s) {
+vx_status radix_sort_run(const void* src, void* alt, void* dst, uint64_t rows, uint32_t ks, uint8_t* scratch,
+                         uint32_t* stall, uint64_t* launches, hipStream_t s) {
   if (ks == 8)
-    return radix_sort_keys((const int64_t*)src, (int64_t*)alt, (int64_t*)dst, rows, hist, offs, ctx, s);
-  return radix_sort_keys((const int32_t*)src, (int32_t*)alt, (int32_t*)dst, rows, hist, offs, ctx, s);
+    return radix_sort_keys((const int64_t*)src, (int64_t*)alt, (int64_t*)dst, rows, scratch, stall, launches, s);
+  return radix_sort_keys((const int32_t*)src, (int32_t*)alt, (int32_t*)dst, rows, scratch, stall, launches, s);
 }
 
 uint64_t align_to(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
@@ -476,12 +627,16 @@ vx_status sort_impl(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {
     return VX_OK;
   }
   // run length: the largest power of two whose pass-1 buffers (2 pipeline buffers, one radix
-  // buffer, two staging runs) and digit histograms fit the free arena; pass 2 needs 4 runs' room
+  // buffer, two staging runs) and sort scratch fit the free arena; pass 2 needs 4 runs' room
   const uint64_t free0 = ctx->arena.capacity() - ctx->arena.used();
-  auto pass1_bytes = [&](uint64_t rows) {
-    return 5 * align_to(rows * ks, 256) + (uint64_t)256 * (digit_tiles(rows) * 12 + kColBlocks * 8) + (1ull << 20);
-  };
+  auto pass1_bytes = [&](uint64_t rows) { return 5 * align_to(rows * ks, 256) + sweep_bytes(rows) + (1ull << 20); };
+  // a device column that is one run is sorted where it lies and needs one buffer beside it
+  const uint64_t direct_bytes = align_to(n * ks, 256) + sweep_bytes(n) + 256;
+  uint32_t* stall = (uint32_t*)(ctx->host_small + kHostSmallWords - 1);
+  uint32_t* stall_dev = (uint32_t*)(ctx->host_small_dev + kHostSmallWords - 1);
+  *stall = 0;
   uint64_t C = d->chunk_rows;
+  if (!C && kc.where == Where::Device && direct_bytes <= ctx->arena.largest_free()) C = n;
   if (!C) {
     C = 1024;
     while (C * 2 <= n && pass1_bytes(C * 2) <= free0) C *= 2;
@@ -490,7 +645,6 @@ vx_status sort_impl(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {
   }
   VX_CHECK(C >= 1, VX_EINVAL, "sort: chunk_rows is 0");
   const uint64_t runs = (n + C - 1) / C;
-  const uint64_t tiles_max = digit_tiles(std::min(C, n));
   const uint64_t run_bytes = align_to(std::min(C, n) * ks, 256);
   // host scratch for the sorted runs (several runs only)
   uint8_t* hs = nullptr;
@@ -504,17 +658,42 @@ vx_status sort_impl(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {
   double sort_k_ms = 0;
   uint64_t launches = 0, sdma = 0;
   uint32_t nbuf_used = 0;
-  {
+  if (runs == 1 && kc.where == Where::Device) {
+    // no staging and no store: the passes go from the column to the buffer and back (16.0 M int64
+    // keys: the store of the staged run alone took 572 us, as it runs on few workgroups)
+    nbuf_used = d->n_buffers ? d->n_buffers : (uint32_t)env_u64("VX_BUFFERS", 2);
+    VX_CHECK(nbuf_used >= 2 && nbuf_used <= kMaxBuffers, VX_EINVAL, "pipeline: n_buffers %u outside 2..%u", nbuf_used,
+             kMaxBuffers);
     ArenaBlock blk;
     blk.a = &ctx->arena;
-    const uint64_t hist_bytes = align_to((uint64_t)256 * tiles_max * 4, 256);
-    blk.p = ctx->arena.alloc(3 * run_bytes + hist_bytes + (uint64_t)256 * (tiles_max + kColBlocks) * 8 + 256);
+    blk.p = ctx->arena.alloc(direct_bytes);
+    VX_CHECK(blk.p, VX_EBUDGET, "sort: no room for a run of %llu keys (radix buffer)", (unsigned long long)n);
+    hipEvent_t e0 = get_event(ctx), e1 = get_event(ctx);
+    auto direct = [&]() -> vx_status {
+      VX_CHECK(e0 && e1, VX_EHIP, "sort: no HIP event");
+      VX_HIP(hipEventRecord(e0, ctx->compute));
+      VX_TRY(radix_sort_run(out_dev, blk.p, out_dev, n, ks, blk.p + align_to(n * ks, 256), stall_dev, &launches,
+                            ctx->compute));
+      VX_HIP(hipEventRecord(e1, ctx->compute));
+      return VX_OK;
+    };
+    vx_status rs = direct();
+    const hipError_t se = hipStreamSynchronize(ctx->compute);
+    float ms = 0;
+    if (rs == VX_OK && se == hipSuccess && hipEventElapsedTime(&ms, e0, e1) == hipSuccess) sort_k_ms = ms;
+    put_event(ctx, e0);
+    put_event(ctx, e1);
+    VX_TRY(rs);
+    VX_HIP(se);
+  } else {
+    ArenaBlock blk;
+    blk.a = &ctx->arena;
+    blk.p = ctx->arena.alloc(3 * run_bytes + sweep_bytes(std::min(C, n)) + 256);
     VX_CHECK(blk.p, VX_EBUDGET, "sort: no room for runs of %llu keys (radix and staging buffers)",
              (unsigned long long)C);
     uint8_t* alt = blk.p;
     uint8_t* stage[2] = {blk.p + run_bytes, blk.p + 2 * run_bytes};
-    uint32_t* hist = (uint32_t*)(blk.p + 3 * run_bytes);
-    unsigned long long* offs = (unsigned long long*)(blk.p + 3 * run_bytes + hist_bytes);
+    uint8_t* scratch = blk.p + 3 * run_bytes;
     std::vector<PipeCol> cols(1);
     cols[0].info = kc;
     cols[0].may_copy = cols[0].copy = true;
@@ -534,9 +713,8 @@ vx_status sort_impl(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {
       kev.push_back(e0);
       kev.push_back(e1);
       VX_HIP(hipEventRecord(e0, ctx->compute));
-      VX_TRY(radix_sort_run(ctx, src, alt, stage[b], v.rows, ks, hist, offs, ctx->compute));
+      VX_TRY(radix_sort_run(src, alt, stage[b], v.rows, ks, scratch, stall_dev, &launches, ctx->compute));
       VX_HIP(hipEventRecord(e1, ctx->compute));
-      launches += 5 * ks;   // per digit pass: histogram, three scan launches, scatter
       VX_HIP(hipEventRecord(sorted_ev[b], ctx->compute));
       // a single run is the result: store it in place; otherwise to its rows of the scratch
       uint8_t* dst = (runs > 1 ? (uint8_t*)hs_dev : out_dev) + v.row0 * ks;
@@ -563,6 +741,7 @@ vx_status sort_impl(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {
     sdma = pipe.sdma_bytes();
   }
   const double pass1_ms = now_ms() - tp0;
+  VX_CHECK(*(volatile uint32_t*)stall == 0, VX_EHIP, "sort: a digit pass waited too long for the tiles before it");
 
   // ---------------- pass 2: regroup and merge
   const double tm0 = now_ms();

@@ -128,6 +128,22 @@ def test_sort_small_budget_auto_runs(gpu):
         c.close()
 
 
+@pytest.mark.parametrize("dtype", [np.int64, np.int32])
+@pytest.mark.parametrize("n", [2, 63, 1025, 8191, 8192, 8193, 5 * 2048, 1 << 16, (1 << 16) + 1, 1 << 18, (1 << 18) + 1,
+                               1 << 21, (1 << 21) + 1, 3 * (1 << 20) + 77])
+def test_sort_device_column_one_run(gpu, ctx, n, dtype):
+    """A device column in one run: the LDS sort and both sides of each tile size's limit, whole and
+    ragged last tiles; random keys, keys that share their high digits, and one repeated key."""
+    import torch
+    base = _keys(n, dtype, n)
+    for name, k in (("random", base), ("small", base & 1023), ("equal", np.full(n, -3, dtype))):
+        t = torch.from_numpy(k.copy()).cuda()
+        _say("sort device one run", n, dtype.__name__, name)
+        st = ctx.sort(t)
+        assert st["chunks"] == 1
+        assert np.array_equal(t.cpu().numpy(), np.sort(k))
+
+
 def test_sort_errors(gpu, ctx):
     bad = gpu.Col(None, 3, 0)
     d = gpu.SortDesc(bad, 10, 0, 0, 0)
