@@ -344,8 +344,8 @@ static unsigned grid1(const vx_ctx* ctx, uint64_t n) {
   return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>((n + 255) / 256, (uint64_t)ctx->cu_count * 8));
 }
 
-// LSD radix sort of m int64 keys (signed order) in 8-bit digits over the bits where the keys
-// differ; each digit pass is a stable multisplit.  Returns the buffer holding the result.
+// LSD radix sort of m int64 keys (signed order) in 8-bit digits, up to the highest in which the keys
+// differ.  Returns the buffer holding the result.
 static vx_status sort_i64(vx_ctx* ctx, long long* a, long long* b, uint64_t m, long long** sorted) {
   *sorted = a;
   if (m < 2) return VX_OK;
@@ -359,34 +359,11 @@ static vx_status sort_i64(vx_ctx* ctx, long long* a, long long* b, uint64_t m, l
   unsigned long long diff = hm[0] ^ hm[1];
   if (diff == 0) return VX_OK;
   uint32_t top = 63 - (uint32_t)__builtin_clzll(diff);
-  PartGeom g = part_geom(ctx, m);
   ArenaBlock scratch;
   scratch.a = &ctx->arena;
-  scratch.p = ctx->arena.alloc((uint64_t)256 * g.waves * 12);
+  scratch.p = ctx->arena.alloc(sort_scratch_bytes(m));
   VX_CHECK(scratch.p, VX_EBUDGET, "sort: no room for digit histograms");
-  uint32_t* hist = (uint32_t*)scratch.p;
-  unsigned long long* offs = (unsigned long long*)(scratch.p + (uint64_t)256 * g.waves * 4);
-  long long* src = a;
-  long long* dst = b;
-  for (uint32_t shift = 0; shift <= top; shift += 8) {
-    PartSpec ps{};
-    ps.fn = kPartBits;
-    ps.n_parts = 256;
-    ps.log2p = 8;
-    ps.shift = shift;
-    ps.flip_sign = 1;
-    PartIO io{};
-    io.key = src;
-    io.key_size = 8;
-    io.n = m;
-    io.out_key = dst;
-    VX_TRY(part_hist(ctx, ps, io, g, hist, nullptr, nullptr, nullptr, s));
-    VX_TRY(part_scan(ctx, hist, 256, g.waves, nullptr, offs, nullptr, s));
-    VX_TRY(part_scatter(ctx, ps, io, g, offs, s));
-    std::swap(src, dst);
-  }
-  *sorted = src;
-  return VX_OK;
+  return sort_keys_i64(ctx, a, b, m, top / 8 + 1, scratch.p, sorted, s);
 }
 
 struct Model {
@@ -627,14 +604,13 @@ vx_status cdf_splitters(vx_ctx* ctx, const ColInfo& key, uint64_t n, const vx_pa
   // the sorted sample)
   auto single_share = [&](const std::vector<int64_t>& sp, double* share) -> vx_status {
     const uint32_t np = (uint32_t)sp.size() + 1;
-    PartGeom g = part_geom(ctx, m);
     ArenaBlock b;
     b.a = &ctx->arena;
-    b.p = ctx->arena.alloc((uint64_t)np * g.waves * 4 + (uint64_t)np * 8 + sp.size() * 8 + 256);
+    b.p = ctx->arena.alloc(part_work_bytes(np, m) + (2 * (uint64_t)np + 1) * 8 + sp.size() * 8 + 256);
     VX_CHECK(b.p, VX_EBUDGET, "cdf: no room for sample histograms");
-    uint32_t* hist = (uint32_t*)b.p;
-    unsigned long long* tot = (unsigned long long*)(b.p + (uint64_t)np * g.waves * 4);
-    long long* spl = (long long*)(tot + np);
+    unsigned long long* tot = (unsigned long long*)b.p;
+    long long* spl = (long long*)(tot + 2 * (uint64_t)np + 1);
+    uint8_t* work = b.p + ((2 * (uint64_t)np + 1 + sp.size()) * 8 + 63) / 64 * 64;
     PartIO io{};
     io.key = sorted;
     io.key_size = 8;
@@ -645,8 +621,7 @@ vx_status cdf_splitters(vx_ctx* ctx, const ColInfo& key, uint64_t n, const vx_pa
     ps.n_parts = np;
     ps.splitters = spl;
     if (ps.n_split) VX_HIP(hipMemcpyAsync(spl, sp.data(), ps.n_split * 8, hipMemcpyHostToDevice, s));
-    fill_zero((uint64_t*)tot, np, s);
-    VX_TRY(part_hist(ctx, ps, io, g, hist, tot, nullptr, nullptr, s));
+    VX_TRY(part_count(ctx, ps, io, work, tot, false, tot + np, nullptr, nullptr, nullptr, s));
     std::vector<unsigned long long> h(np);
     VX_HIP(hipMemcpyAsync(h.data(), tot, np * 8, hipMemcpyDeviceToHost, s));
     VX_HIP(hipStreamSynchronize(s));
@@ -679,14 +654,14 @@ vx_status cdf_splitters(vx_ctx* ctx, const ColInfo& key, uint64_t n, const vx_pa
     while ((1u << l) < P) ++l;
     rep->radix_parts = 1u << l;
     uint32_t pr = std::max<uint32_t>(rep->radix_parts, (uint32_t)splitters->size() + 1);
-    PartGeom g = part_geom(ctx, m);
     ArenaBlock hb;
     hb.a = &ctx->arena;
-    hb.p = ctx->arena.alloc((uint64_t)pr * g.waves * 4 + (uint64_t)pr * 8 + splitters->size() * 8 + 256);
+    hb.p = ctx->arena.alloc(part_work_bytes(pr, m) + (2 * (uint64_t)pr + 1) * 8 + splitters->size() * 8 + 256);
     VX_CHECK(hb.p, VX_EBUDGET, "cdf: no room for sample histograms");
-    uint32_t* hist = (uint32_t*)hb.p;
-    unsigned long long* tot = (unsigned long long*)(hb.p + (uint64_t)pr * g.waves * 4);
-    long long* spl = (long long*)(tot + pr);
+    unsigned long long* tot = (unsigned long long*)hb.p;
+    unsigned long long* base = tot + pr;
+    long long* spl = (long long*)(base + pr + 1);
+    uint8_t* work = hb.p + ((2 * (uint64_t)pr + 1 + splitters->size()) * 8 + 63) / 64 * 64;
     PartIO io{};
     io.key = sorted;
     io.key_size = 8;
@@ -695,8 +670,7 @@ vx_status cdf_splitters(vx_ctx* ctx, const ColInfo& key, uint64_t n, const vx_pa
     ps.fn = kPartHash;
     ps.n_parts = rep->radix_parts;
     ps.log2p = l;
-    fill_zero((uint64_t*)tot, pr, s);
-    VX_TRY(part_hist(ctx, ps, io, g, hist, tot, nullptr, nullptr, s));
+    VX_TRY(part_count(ctx, ps, io, work, tot, false, base, nullptr, nullptr, nullptr, s));
     std::vector<unsigned long long> h(ps.n_parts);
     VX_HIP(hipMemcpyAsync(h.data(), tot, h.size() * 8, hipMemcpyDeviceToHost, s));
     VX_HIP(hipStreamSynchronize(s));
@@ -708,8 +682,7 @@ vx_status cdf_splitters(vx_ctx* ctx, const ColInfo& key, uint64_t n, const vx_pa
     pr2.splitters = spl;
     if (pr2.n_split)
       VX_HIP(hipMemcpyAsync(spl, splitters->data(), pr2.n_split * 8, hipMemcpyHostToDevice, s));
-    fill_zero((uint64_t*)tot, pr, s);
-    VX_TRY(part_hist(ctx, pr2, io, g, hist, tot, nullptr, nullptr, s));
+    VX_TRY(part_count(ctx, pr2, io, work, tot, false, base, nullptr, nullptr, nullptr, s));
     h.assign(pr2.n_parts, 0);
     VX_HIP(hipMemcpyAsync(h.data(), tot, h.size() * 8, hipMemcpyDeviceToHost, s));
     fill_zero((uint64_t*)tot, 1, s);

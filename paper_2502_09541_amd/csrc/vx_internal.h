@@ -102,7 +102,6 @@ struct vx_ctx {
   uint64_t* dev_acc = nullptr;
   uint64_t dev_acc_words = 0;
   unsigned int* dev_flags = nullptr;   // error flags written by kernels
-  uint64_t* dev_scan = nullptr;        // kScanTilesMax + 1 words: tile sums of the partition scan
   int cu_count = 256;
   uint64_t l2_bytes = 4u << 20;
   // pinned host mirror of results (dev_acc_words words), then kHostSmallWords words for small
@@ -145,8 +144,11 @@ void fill_zero(uint64_t* p, uint64_t words, hipStream_t s);
 // Estimated zero-copy wire bytes of reading `count` matching rows, of elsize bytes each,
 // spread over `n` rows: the touched lines of `line` bytes under independent selection.
 double zc_wire_bytes(uint64_t n, uint64_t count, int elsize, uint32_t line);
-constexpr uint32_t kScanTilesMax = 1024;
 constexpr uint64_t kHostSmallWords = 32;
+// A host-mapped word that a kernel's bounded wait sets when it gives up (its device address), and the
+// check of it once the streams are drained.
+inline uint32_t* stall_word(const vx_ctx* ctx) { return (uint32_t*)(ctx->host_small_dev + kHostSmallWords - 1); }
+vx_status check_stall(vx_ctx* ctx, const char* what);
 constexpr int kAccWords = 10;           // count + 8 sums + zero-copy granules per aggregate row
 
 }  // namespace vx

@@ -1,11 +1,11 @@
-// Stable multisplit: partition ids, per-wave histograms, exclusive scan, stable scatter.
+// Stable multisplit: partition ids, counts, stable scatter.
 //
-// Rows are split into contiguous wave tiles (wave w owns rows [w*T, (w+1)*T)).  Pass 1 counts
-// each wave's rows per partition into hist[p * W + w] (partition-major).  An exclusive scan
-// of that array gives every (partition, wave) pair its output offset, so partition p's rows
-// land contiguously, in input order.  Pass 2 walks each wave tile in 64-row steps: ten
-// ballots give each lane the mask of lanes with the same partition id, its rank among them
-// is a popcount, and a per-wave running counter in LDS advances by the step's count.
+// part_count counts the rows of every partition in one pass over the keys and turns the counts into
+// each partition's first position.  part_sweep then writes the rows to their places in one pass:
+// its workgroups take tiles of consecutive rows in order, rank a tile's rows by partition in input
+// order (ballots), find where each partition's rows go by look-back over the tiles before, sort the
+// tile by partition in LDS and write it in that order, so that a partition's rows of a tile are one
+// run of consecutive addresses.  Payload columns follow the keys through the same LDS buffer.
 #pragma once
 
 #include "vx_internal.h"
@@ -13,11 +13,10 @@
 namespace vx {
 
 constexpr uint32_t kMaxParts = 1024;
-constexpr uint32_t kMaxPartIdBits = 10;
 
 enum PartFn : uint32_t {
   kPartHash = 0,      // top log2 P bits of the MurmurHash3 64-bit finalizer
-  kPartBits = 1,      // raw key bits [shift, shift + log2 P); flip_sign orders signed keys
+  kPartBits = 1,      // raw key bits [shift, shift + log2 P)
   kPartRange = 2      // number of splitters <= key
 };
 
@@ -26,7 +25,6 @@ struct PartSpec {
   uint32_t n_parts;
   uint32_t log2p;
   uint32_t shift;
-  uint32_t flip_sign;
   uint32_t n_split;
   const long long* splitters;   // device, ascending
 };
@@ -54,14 +52,37 @@ __device__ __forceinline__ unsigned long long fmix64(unsigned long long h) {
   return h;
 }
 
+// The ids of N keys at once: the searches of the range splitters run side by side.
+template <uint32_t N, typename K>
+__device__ __forceinline__ void part_ids(const PartSpec& ps, const K (&k)[N], const long long* split, uint32_t (&id)[N]) {
+  if (ps.fn == kPartRange) {
+#pragma unroll
+    for (uint32_t j = 0; j < N; ++j) id[j] = 0;
+    for (uint32_t step = kMaxParts >> 1; step; step >>= 1) {
+      if (step > ps.n_split) continue;   // uniform
+#pragma unroll
+      for (uint32_t j = 0; j < N; ++j)
+        if (id[j] + step <= ps.n_split && split[id[j] + step - 1] <= (long long)k[j]) id[j] += step;
+    }
+    return;
+  }
+  if (ps.fn == kPartHash) {
+#pragma unroll
+    for (uint32_t j = 0; j < N; ++j)
+      id[j] = ps.log2p ? (uint32_t)(fmix64((unsigned long long)(long long)k[j]) >> (64 - ps.log2p)) : 0u;
+    return;
+  }
+#pragma unroll
+  for (uint32_t j = 0; j < N; ++j)
+    id[j] = (uint32_t)((unsigned long long)(long long)k[j] >> ps.shift) & (ps.n_parts - 1);
+}
+
 __device__ __forceinline__ uint32_t part_of(const PartSpec& ps, long long k, const long long* split) {
   if (ps.fn == kPartHash) {
     return ps.log2p ? (uint32_t)(fmix64((unsigned long long)k) >> (64 - ps.log2p)) : 0u;
   }
   if (ps.fn == kPartBits) {
-    unsigned long long u = (unsigned long long)k;
-    if (ps.flip_sign) u ^= 0x8000000000000000ull;
-    return (uint32_t)((u >> ps.shift) & (unsigned long long)(ps.n_parts - 1));
+    return (uint32_t)(((unsigned long long)k >> ps.shift) & (unsigned long long)(ps.n_parts - 1));
   }
   uint32_t lo = 0, hi = ps.n_split;
   while (lo < hi) {
@@ -72,32 +93,33 @@ __device__ __forceinline__ uint32_t part_of(const PartSpec& ps, long long k, con
   return lo;
 }
 
-// Launch geometry shared by hist and scatter: waves and rows per wave tile.
-struct PartGeom {
-  uint32_t blocks;
-  uint32_t waves;     // blocks * 4
-  uint64_t tile;      // rows per wave (multiple of 64)
-};
-
-PartGeom part_geom(const vx_ctx* ctx, uint64_t n);
-
 constexpr uint32_t kMaxSumSlots = 64;
 
-// hist: n_parts * waves uint32 (partition-major).  totals (optional, n_parts u64) accumulates
-// each partition's row count.  sums (optional): for partitions with sum_slot[p] >= 0 (a
-// device int array of n_parts entries, slots < kMaxSumSlots), the row count and the SUM of
-// payload 0 are added to sums[2*slot] and sums[2*slot+1].
-vx_status part_hist(vx_ctx* ctx, const PartSpec& ps, const PartIO& io, const PartGeom& g,
-                    uint32_t* hist, unsigned long long* totals, const int* sum_slot,
-                    unsigned long long* sums, hipStream_t s);
-// Exclusive scan of hist (n_parts * waves) into offs (uint64).  Without part_base, one scan
-// over the whole array (chunk-local clustering) and boundary (optional, n_parts + 1) receives
-// each partition's first offset and the total.  With part_base (device, n_parts u64), each
-// partition is scanned on its own and starts at part_base[p] (global placement).
-vx_status part_scan(vx_ctx* ctx, const uint32_t* hist, uint32_t n_parts, uint32_t waves,
-                    const unsigned long long* part_base, unsigned long long* offs,
-                    unsigned long long* boundary, hipStream_t s);
-vx_status part_scatter(vx_ctx* ctx, const PartSpec& ps, const PartIO& io, const PartGeom& g,
-                       const unsigned long long* offs, hipStream_t s);
+// Device scratch of part_count and part_sweep over at most `rows` rows per launch.
+uint64_t part_work_bytes(uint32_t n_parts, uint64_t rows);
+
+// Count the rows of every partition.  totals (n_parts u64) receives the counts, or has them added
+// when `accumulate`; base (n_parts + 1) the exclusive prefix of totals and its sum; host_totals
+// (optional, host-mapped) a copy of totals.  sums (optional): for partitions with sum_slot[p] >= 0
+// (a device int array of n_parts entries, slots < kMaxSumSlots), the row count and the SUM of
+// payload 0 are added to sums[2*slot] and sums[2*slot+1].  Leaves `work` ready for one part_sweep
+// over the same rows.
+vx_status part_count(vx_ctx* ctx, const PartSpec& ps, const PartIO& io, uint8_t* work, unsigned long long* totals,
+                     bool accumulate, unsigned long long* base, unsigned long long* host_totals, const int* sum_slot,
+                     unsigned long long* sums, hipStream_t s);
+// Write the rows of io to their places: partition p's from out_base + base[p] on, in input order.
+// next (optional, n_parts; may be base) receives the position after each partition's rows, the
+// base of the chunk that follows.  `work` comes from part_count over the same rows, or was made
+// ready by part_ready.
+vx_status part_sweep(vx_ctx* ctx, const PartSpec& ps, const PartIO& io, uint8_t* work, const unsigned long long* base,
+                     unsigned long long* next, hipStream_t s);
+vx_status part_ready(const PartSpec& ps, uint64_t rows, uint8_t* work, hipStream_t s);
+
+// LSD radix sort of `rows` int64 keys (signed order) that differ in their low 8 * passes bits only,
+// from a, with b as the second buffer; *sorted receives
+// the one that holds the result.  scratch holds sort_scratch_bytes(rows).
+uint64_t sort_scratch_bytes(uint64_t rows);
+vx_status sort_keys_i64(vx_ctx* ctx, long long* a, long long* b, uint64_t rows, uint32_t passes, uint8_t* scratch,
+                        long long** sorted, hipStream_t s);
 
 }  // namespace vx

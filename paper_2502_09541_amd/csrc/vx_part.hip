@@ -2,9 +2,12 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "vx_cdf.h"
+#include "vx_device.h"
+#include "vx_lookback.h"
 #include "vx_part.h"
 #include "vx_pipeline.h"
 
@@ -12,278 +15,357 @@ namespace vx {
 
 // ---------------------------------------------------------------- device side
 
-__device__ __forceinline__ long long load_any(const void* p, uint64_t i, uint32_t size) {
-  return size == 4 ? (long long)((const int*)p)[i] : ((const long long*)p)[i];
-}
+// Counting: workgroups take rows grid-stride, kCountItems keys per lane in flight, and count in LDS;
+// the counters are repeated over the lanes (as often as 4096 counters allow) so that a few large
+// partitions do not serialize a wave's additions.  part[g * P + p] receives workgroup g's counts.
+// Also clears the look-back words and the ticket of the sweep that follows.
+// Bound: the keys' read and the LDS additions; 16.0 M int64 keys in 256 hash partitions take 47 us
+// (2.7 TB/s; 147 us with one key per lane in flight and a ballot per id bit).
+constexpr uint32_t kCountThreads = 1024;
+constexpr uint32_t kCountItems = 8;
+constexpr uint32_t kCountGroups = 256;
+constexpr uint32_t kCountSlots = 4096;
 
-__device__ __forceinline__ void store_any(void* p, uint64_t i, uint32_t size, long long v) {
-  if (size == 4) ((int*)p)[i] = (int)v;
-  else ((long long*)p)[i] = v;
-}
-
-// mask of the active lanes whose id equals this lane's (all lanes must call it together)
-__device__ __forceinline__ unsigned long long peers_of(uint32_t pid, bool valid, uint32_t bits) {
-  unsigned long long peers = __ballot(valid);
-  for (uint32_t b = 0; b < bits; ++b) {
-    bool bit = (pid >> b) & 1u;
-    unsigned long long m = __ballot(bit);
-    peers &= bit ? m : ~m;
-  }
-  return peers;
-}
-
-__device__ __forceinline__ uint32_t id_bits(uint32_t n_parts) {
-  uint32_t b = 0;
-  while ((1u << b) < n_parts) ++b;
-  return b;
-}
-
-__global__ void __launch_bounds__(256) k_part_hist(PartSpec ps, PartIO io, uint64_t tile,
-                                                   uint32_t* hist, unsigned long long* totals,
-                                                   const int* sum_slot, unsigned long long* sums) {
+template <typename K>
+__global__ void __launch_bounds__(kCountThreads) k_part_count(PartSpec ps, PartIO io, uint32_t copies, uint32_t* part,
+                                                              unsigned long long* status, uint64_t status_words,
+                                                              uint32_t* ticket, const int* sum_slot,
+                                                              unsigned long long* sums) {
   __shared__ long long split[kMaxParts];
-  __shared__ uint32_t whist[4][kMaxParts];
+  __shared__ uint32_t cnt[kCountSlots];
   __shared__ unsigned long long ssum[kMaxSumSlots][2];
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t P = ps.n_parts;
+  const uint64_t n = io.n;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
+  for (uint64_t i = blockIdx.x * (uint64_t)kCountThreads + threadIdx.x; i < status_words;
+       i += (uint64_t)gridDim.x * kCountThreads)
+    status[i] = 0;
   if (ps.fn == kPartRange)
-    for (uint32_t j = threadIdx.x; j < ps.n_split; j += blockDim.x) split[j] = ps.splitters[j];
-  for (uint32_t j = threadIdx.x; j < 4 * kMaxParts; j += blockDim.x) (&whist[0][0])[j] = 0;
-  for (uint32_t j = threadIdx.x; j < 2 * kMaxSumSlots; j += blockDim.x) (&ssum[0][0])[j] = 0;
+    for (uint32_t j = threadIdx.x; j < ps.n_split; j += kCountThreads) split[j] = ps.splitters[j];
+  for (uint32_t j = threadIdx.x; j < kCountSlots; j += kCountThreads) cnt[j] = 0;
+  if (threadIdx.x < 2 * kMaxSumSlots) (&ssum[0][0])[threadIdx.x] = 0;
   __syncthreads();
-  const uint32_t bits = id_bits(ps.n_parts);
-  const uint64_t w = (uint64_t)blockIdx.x * 4 + wave;
-  const uint64_t r0 = w * tile;
-  const uint64_t r1 = r0 + tile < io.n ? r0 + tile : io.n;
-  for (uint64_t base = r0; base < r1; base += 64) {
-    uint64_t i = base + lane;
-    bool valid = i < r1;
-    long long k = valid ? load_any(io.key, i, io.key_size) : 0;
-    uint32_t pid = valid ? part_of(ps, k, split) : 0;
-    unsigned long long peers = peers_of(pid, valid, bits);
-    if (valid && (peers & ((1ull << lane) - 1)) == 0)
-      atomicAdd(&whist[wave][pid], (uint32_t)__popcll(peers));
-    if (sum_slot && valid) {
-      int slot = sum_slot[pid];
-      if (slot >= 0) {
-        atomicAdd(&ssum[slot][0], 1ull);
-        if (io.n_pay) atomicAdd(&ssum[slot][1], (unsigned long long)load_any(io.pay[0], i, io.pay_size[0]));
+  const K* key = (const K*)io.key;
+  uint32_t* mine = cnt + (threadIdx.x & (copies - 1)) * P;
+  const uint64_t block_rows = (uint64_t)kCountThreads * kCountItems;
+  for (uint64_t b0 = blockIdx.x * block_rows; b0 < n; b0 += gridDim.x * block_rows) {
+    const uint64_t i0 = b0 + threadIdx.x;
+    K k[kCountItems];
+    uint32_t id[kCountItems];
+    const bool whole = b0 + block_rows <= n;
+#pragma unroll
+    for (uint32_t j = 0; j < kCountItems; ++j)
+      k[j] = whole || i0 + j * kCountThreads < n ? key[i0 + j * kCountThreads] : K(0);
+    part_ids<kCountItems>(ps, k, split, id);
+#pragma unroll
+    for (uint32_t j = 0; j < kCountItems; ++j)
+      if (whole || i0 + j * kCountThreads < n) atomicAdd(mine + id[j], 1u);
+    if (sum_slot) {
+#pragma unroll
+      for (uint32_t j = 0; j < kCountItems; ++j) {
+        const uint64_t i = i0 + j * kCountThreads;
+        const int slot = i < n ? sum_slot[id[j]] : -1;
+        if (slot >= 0) {
+          atomicAdd(&ssum[slot][0], 1ull);
+          if (io.n_pay) atomicAdd(&ssum[slot][1], (unsigned long long)load_signed(io.pay[0], i, io.pay_size[0]));
+        }
       }
     }
   }
   __syncthreads();
-  const uint64_t W = (uint64_t)gridDim.x * 4;
-  for (uint32_t j = threadIdx.x; j < 4 * ps.n_parts; j += blockDim.x) {
-    uint32_t wv = j / ps.n_parts, p = j % ps.n_parts;
-    uint32_t c = whist[wv][p];
-    hist[(uint64_t)p * W + (uint64_t)blockIdx.x * 4 + wv] = c;
-    if (totals && c) atomicAdd(totals + p, (unsigned long long)c);
+  for (uint32_t p = threadIdx.x; p < P; p += kCountThreads) {
+    uint32_t c = 0;
+    for (uint32_t r = 0; r < copies; ++r) c += cnt[r * P + p];
+    part[(uint64_t)blockIdx.x * P + p] = c;
   }
-  if (sums)
-    for (uint32_t j = threadIdx.x; j < 2 * kMaxSumSlots; j += blockDim.x) {
-      unsigned long long v = (&ssum[0][0])[j];
-      if (v) atomicAdd(sums + j, v);
-    }
+  if (sum_slot && threadIdx.x < 2 * kMaxSumSlots) {
+    const unsigned long long v = (&ssum[0][0])[threadIdx.x];
+    if (v) atomicAdd(sums + threadIdx.x, v);
+  }
 }
 
-// single-block exclusive scan over count entries (partition-major hist)
-// Exclusive scan of the partition-major histogram, in three launches: per-tile sums, a scan of
-// the tile sums, and each tile rescanned from its base.  boundary[p] (optional) receives the
-// offset of entry p * waves, i.e. partition p's first row, and boundary[n_parts] the total.
-constexpr uint32_t kScanThreads = 256;
-
-// exclusive prefix of v over the block (256 threads); *total receives the block's sum
-__device__ __forceinline__ unsigned long long block_excl_scan(unsigned long long v, unsigned long long* ws,
-                                                              unsigned long long* total) {
+// One workgroup: totals[p] (+)= SUM over the counting workgroups of part[g * P + p], base = the
+// exclusive prefix of totals, base[P] = their sum.  The threads split the workgroups' rows into
+// 1024 / padded interleaved shares (padded: P rounded up to a power of two, at least 64).
+__global__ void __launch_bounds__(1024) k_part_base(const uint32_t* part, uint32_t groups, uint32_t P, uint32_t log2pad,
+                                                    unsigned long long* totals, uint32_t accumulate,
+                                                    unsigned long long* base, unsigned long long* host_totals) {
+  __shared__ unsigned long long sum[1024];
+  __shared__ unsigned long long ws[16];
+  const uint32_t pad = 1u << log2pad, p = threadIdx.x & (pad - 1), q = threadIdx.x >> log2pad, shares = 1024u >> log2pad;
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  unsigned long long x = v;
-  for (int o = 1; o < 64; o <<= 1) {
-    unsigned long long y = __shfl_up(x, o, 64);
-    if (lane >= (uint32_t)o) x += y;
+  unsigned long long s = 0;
+  if (p < P) {
+    uint32_t g = q;
+    for (; g + 15 * shares < groups; g += 16 * shares) {   // sixteen loads in flight
+      uint32_t v[16];
+#pragma unroll
+      for (uint32_t u = 0; u < 16; ++u) v[u] = part[(uint64_t)(g + u * shares) * P + p];
+#pragma unroll
+      for (uint32_t u = 0; u < 16; ++u) s += v[u];
+    }
+    for (; g < groups; g += shares) s += part[(uint64_t)g * P + p];
+  }
+  sum[threadIdx.x] = s;
+  __syncthreads();
+  unsigned long long tot = 0;
+  if (threadIdx.x < P) {
+    for (uint32_t r = 0; r < shares; ++r) tot += sum[r * pad + threadIdx.x];
+    if (accumulate) tot += totals[threadIdx.x];
+    totals[threadIdx.x] = tot;
+    if (host_totals) host_totals[threadIdx.x] = tot;
+  }
+  unsigned long long x = tot;
+#pragma unroll
+  for (uint32_t o = 1; o < 64; o <<= 1) {
+    const unsigned long long y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
   }
   if (lane == 63) ws[wave] = x;
   __syncthreads();
-  unsigned long long base = 0, tot = 0;
-  for (uint32_t w = 0; w < kScanThreads / 64; ++w) {
-    if (w < wave) base += ws[w];
-    tot += ws[w];
-  }
-  __syncthreads();
-  *total = tot;
-  return base + x - v;
-}
-
-__global__ void __launch_bounds__(kScanThreads) k_scan_tiles(const uint32_t* hist, uint64_t count, uint64_t tile,
-                                                             unsigned long long* tsum) {
-  __shared__ unsigned long long ws[kScanThreads / 64];
-  const uint64_t a = blockIdx.x * tile, e = a + tile < count ? a + tile : count;
-  unsigned long long s = 0;
-  for (uint64_t i = a + threadIdx.x; i < e; i += blockDim.x) s += hist[i];
-  unsigned long long tot = 0;
-  block_excl_scan(s, ws, &tot);
-  if (threadIdx.x == 0) tsum[blockIdx.x] = tot;
-}
-
-// tsum[0..nt) becomes its exclusive scan; tsum[nt] the total (nt <= 4 * kScanThreads)
-__global__ void __launch_bounds__(kScanThreads) k_scan_top(unsigned long long* tsum, uint32_t nt) {
-  __shared__ unsigned long long ws[kScanThreads / 64];
-  const uint32_t a = threadIdx.x * 4;
-  unsigned long long v[4], s = 0;
-  for (uint32_t j = 0; j < 4; ++j) {
-    v[j] = a + j < nt ? tsum[a + j] : 0ull;
-    s += v[j];
-  }
-  unsigned long long tot = 0;
-  unsigned long long run = block_excl_scan(s, ws, &tot);
-  for (uint32_t j = 0; j < 4; ++j)
-    if (a + j < nt) {
-      tsum[a + j] = run;
-      run += v[j];
-    }
-  if (threadIdx.x == 0) tsum[nt] = tot;
-}
-
-__global__ void __launch_bounds__(kScanThreads) k_scan_apply(const uint32_t* hist, uint64_t count, uint64_t tile,
-                                                             const unsigned long long* tsum, uint32_t nt,
-                                                             unsigned long long* offs, uint32_t n_parts,
-                                                             uint32_t waves, unsigned long long* boundary) {
-  __shared__ unsigned long long ws[kScanThreads / 64];
-  const uint64_t a = blockIdx.x * tile, e = a + tile < count ? a + tile : count;
-  const uint64_t per = (tile + kScanThreads - 1) / kScanThreads;
-  const uint64_t ta = a + threadIdx.x * per < e ? a + threadIdx.x * per : e;
-  const uint64_t te = ta + per < e ? ta + per : e;
-  unsigned long long s = 0;
-  for (uint64_t i = ta; i < te; ++i) s += hist[i];
-  unsigned long long tot = 0;
-  unsigned long long run = tsum[blockIdx.x] + block_excl_scan(s, ws, &tot);
-  for (uint64_t i = ta; i < te; ++i) {
-    offs[i] = run;
-    if (boundary && i % waves == 0) boundary[i / waves] = run;
-    run += hist[i];
-  }
-  if (boundary && blockIdx.x == 0 && threadIdx.x == 0) boundary[n_parts] = tsum[nt];
-}
-
-// one block per partition: offs[p*W + w] = base[p] + sum of hist[p*W + w'] for w' < w
-__global__ void __launch_bounds__(256) k_scan_seg(const uint32_t* hist, uint32_t waves,
-                                                  const unsigned long long* part_base,
-                                                  unsigned long long* offs) {
-  __shared__ unsigned long long part[256];
-  const uint64_t p = blockIdx.x;
-  const uint32_t per = (waves + blockDim.x - 1) / blockDim.x;
-  const uint32_t a = threadIdx.x * per, b = a + per < waves ? a + per : waves;
-  unsigned long long s = 0;
-  for (uint32_t i = a; i < b; ++i) s += hist[p * waves + i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long run = part_base[p];
-    for (uint32_t t = 0; t < blockDim.x; ++t) {
-      unsigned long long v = part[t];
-      part[t] = run;
-      run += v;
-    }
-  }
-  __syncthreads();
-  unsigned long long run = part[threadIdx.x];
-  for (uint32_t i = a; i < b; ++i) {
-    offs[p * waves + i] = run;
-    run += hist[p * waves + i];
+  unsigned long long b = x - tot;
+  for (uint32_t w = 0; w < wave; ++w) b += ws[w];
+  if (threadIdx.x < P) {
+    base[threadIdx.x] = b;
+    if (threadIdx.x == P - 1) base[P] = b + tot;
   }
 }
 
-__global__ void __launch_bounds__(256) k_part_scatter(PartSpec ps, PartIO io, uint64_t tile,
-                                                      const unsigned long long* offs) {
-  __shared__ long long split[kMaxParts];
-  __shared__ unsigned long long run[4][kMaxParts];
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t W = (uint64_t)gridDim.x * 4;
-  const uint64_t w = (uint64_t)blockIdx.x * 4 + wave;
+// The scatter.  A tile's rows are ranked by partition within each wave (same_id over BITS id bits
+// and a per-wave LDS counter), the waves' counts give every row its place in the sorted tile, and
+// the keys, then each payload column, go through LDS to consecutive addresses per partition.  The
+// splitters sit in the staging buffer until the ids are known.  E is the widest column's size.
+// Bound: the rows' read and write, with the ranking close behind.  16.0 M rows of 16 bytes into 256
+// partitions take 136 us (3.8 TB/s read and written; a large copy reaches 4.8): 425 us when each wave
+// placed 64 rows at a time into up to 64 partitions.
+constexpr uint32_t kSweepThreads = 1024;
+
+template <typename K, uint32_t E, uint32_t ITEMS, uint32_t BITS>
+__global__ void __launch_bounds__(kSweepThreads, 4) k_part_sweep(PartSpec ps, PartIO io, const unsigned long long* base,
+                                                                 unsigned long long* next, unsigned long long* status,
+                                                                 uint32_t* ticket, uint32_t* stall) {
+  constexpr uint32_t THREADS = kSweepThreads, MAXP = 1u << BITS, WAVES = THREADS / 64, TILE = THREADS * ITEMS,
+                     WROWS = 64 * ITEMS;
+  static_assert(THREADS >= MAXP && E >= sizeof(K) && TILE * E >= 8 * (MAXP - 1) && TILE <= (1u << 15), "tile shape");
+  using Id = typename std::conditional<BITS <= 8, uint8_t, uint16_t>::type;
+  __shared__ __align__(16) uint8_t stage[TILE * E];
+  __shared__ __align__(4) uint16_t cnt[WAVES][MAXP];
+  __shared__ Id id_at[TILE];
+  __shared__ unsigned long long gbase[MAXP];
+  __shared__ uint32_t wsum[MAXP / 64];
+  __shared__ uint32_t tile_no;
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, P = ps.n_parts;
+  if (threadIdx.x == 0) tile_no = atomicAdd(ticket, 1u);
   if (ps.fn == kPartRange)
-    for (uint32_t j = threadIdx.x; j < ps.n_split; j += blockDim.x) split[j] = ps.splitters[j];
-  for (uint32_t p = lane; p < ps.n_parts; p += 64) run[wave][p] = offs[(uint64_t)p * W + w];
+    for (uint32_t j = threadIdx.x; j < ps.n_split; j += THREADS) ((long long*)stage)[j] = ps.splitters[j];
+  for (uint32_t i = threadIdx.x; i < WAVES * MAXP / 2; i += THREADS) ((uint32_t*)&cnt[0][0])[i] = 0;
   __syncthreads();
-  const uint32_t bits = id_bits(ps.n_parts);
-  const uint64_t r0 = w * tile;
-  const uint64_t r1 = r0 + tile < io.n ? r0 + tile : io.n;
-  for (uint64_t base = r0; base < r1; base += 64) {
-    uint64_t i = base + lane;
-    bool valid = i < r1;
-    long long k = valid ? load_any(io.key, i, io.key_size) : 0;
-    uint32_t pid = valid ? part_of(ps, k, split) : 0;
-    unsigned long long peers = peers_of(pid, valid, bits);
-    if (valid) {
-      uint32_t rank = (uint32_t)__popcll(peers & ((1ull << lane) - 1));
-      uint64_t pos = io.out_base + run[wave][pid] + rank;
-      if (io.out_key) store_any(io.out_key, pos, io.key_size, k);
-      for (uint32_t c = 0; c < io.n_pay; ++c)
-        if (io.out_pay[c]) store_any(io.out_pay[c], pos, io.pay_size[c], load_any(io.pay[c], i, io.pay_size[c]));
+  const uint64_t t = tile_no, n = io.n;
+  const uint64_t first = t * TILE + wave * WROWS + lane;
+  auto tile = [&](auto whole_tile) {
+    constexpr bool FULL = decltype(whole_tile)::value;
+    K k[ITEMS];
+    uint32_t id[ITEMS];   // low half: the partition; high half: the place in the tile
+    const K* key = (const K*)io.key;
+#pragma unroll
+    for (uint32_t j = 0; j < ITEMS; ++j)
+      k[j] = FULL || first + j * 64 < n ? __builtin_nontemporal_load(key + first + j * 64) : K(0);
+    part_ids<ITEMS>(ps, k, (const long long*)stage, id);
+    const unsigned long long lower = (1ull << lane) - 1;
+#pragma unroll
+    for (uint32_t j = 0; j < ITEMS; ++j) {
+      const bool valid = FULL || first + j * 64 < n;
+      const unsigned long long peers = same_id(id[j], BITS, FULL ? ~0ull : __ballot(valid));
+      const uint32_t below = (uint32_t)__popcll(peers & lower);
+      const uint32_t c = valid ? cnt[wave][id[j]] : 0u;
+      // every lane has read cnt[] before the group's first lane advances it
+      __builtin_amdgcn_wave_barrier();
+      if (valid && below == 0) cnt[wave][id[j]] = (uint16_t)(c + (uint32_t)__popcll(peers));
+      __builtin_amdgcn_wave_barrier();
+      id[j] |= (c + below) << 16;
     }
-    // every lane has read run[] above; the group leader advances it
-    __builtin_amdgcn_wave_barrier();
-    if (valid && (peers & ((1ull << lane) - 1)) == 0) run[wave][pid] += (unsigned long long)__popcll(peers);
-    __builtin_amdgcn_wave_barrier();
-  }
-}
-
-// start[p] += add[p]; add[p] = 0
-__global__ void k_advance(unsigned long long* start, unsigned long long* add, uint32_t n) {
-  uint32_t p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < n) {
-    start[p] += add[p];
-    add[p] = 0;
-  }
+    __syncthreads();
+    // thread p: partition p's rows in the tile, published for the tiles that follow
+    uint32_t tot = 0;
+    unsigned long long pos = 0;
+    if (threadIdx.x < P) {
+#pragma unroll
+      for (uint32_t w = 0; w < WAVES; ++w) tot += cnt[w][threadIdx.x];
+      unsigned long long* word = status + t * P + threadIdx.x;
+      if (t == 0) {
+        pos = base[threadIdx.x];
+        look_store(word, 2, pos + tot);
+      } else {
+        look_store(word, 1, tot);
+      }
+    }
+    uint32_t x = tot;
+    if (threadIdx.x < MAXP) {
+#pragma unroll
+      for (uint32_t o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+      }
+      if (lane == 63) wsum[wave] = x;
+    }
+    __syncthreads();
+    uint32_t e = 0;
+    if (threadIdx.x < P) {   // the places of the waves' first rows of partition p
+      e = x - tot;
+      for (uint32_t w = 0; w < wave; ++w) e += wsum[w];
+      uint32_t at = e;
+#pragma unroll
+      for (uint32_t w = 0; w < WAVES; ++w) {
+        const uint32_t c = cnt[w][threadIdx.x];
+        cnt[w][threadIdx.x] = (uint16_t)at;
+        at += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < ITEMS; ++j)
+      if (FULL || first + j * 64 < n) {
+        const uint32_t p = id[j] & 0xffffu;
+        id[j] = (id[j] >> 16) + cnt[wave][p];   // now the place alone
+        ((K*)stage)[id[j]] = k[j];
+        id_at[id[j]] = (Id)p;
+      }
+    if (threadIdx.x < P) {
+      if (t != 0) {
+        pos = look_back(status + threadIdx.x, P, t, 0, stall);
+        look_store(status + t * P + threadIdx.x, 2, pos + tot);
+      }
+      gbase[threadIdx.x] = io.out_base + pos - e;
+      if (next && (t + 1) * TILE >= n) next[threadIdx.x] = pos + tot;
+    }
+    __syncthreads();
+    const uint32_t m = FULL ? TILE : (uint32_t)(n - t * TILE);
+#pragma unroll
+    for (uint32_t j = 0; j < ITEMS; ++j) {
+      const uint32_t q = j * THREADS + threadIdx.x;
+      if (FULL || q < m) ((K*)io.out_key)[gbase[id_at[q]] + q] = ((const K*)stage)[q];
+    }
+    for (uint32_t c = 0; c < io.n_pay; ++c) {
+      if (!io.out_pay[c]) continue;
+      auto column = [&](auto zero) {
+        using V = decltype(zero);
+        V v[ITEMS];
+        const V* src = (const V*)io.pay[c];
+#pragma unroll
+        for (uint32_t j = 0; j < ITEMS; ++j)
+          v[j] = FULL || first + j * 64 < n ? __builtin_nontemporal_load(src + first + j * 64) : V(0);
+        __syncthreads();   // the stage has been read
+#pragma unroll
+        for (uint32_t j = 0; j < ITEMS; ++j)
+          if (FULL || first + j * 64 < n) ((V*)stage)[id[j]] = v[j];
+        __syncthreads();
+#pragma unroll
+        for (uint32_t j = 0; j < ITEMS; ++j) {
+          const uint32_t q = j * THREADS + threadIdx.x;
+          if (FULL || q < m) ((V*)io.out_pay[c])[gbase[id_at[q]] + q] = ((const V*)stage)[q];
+        }
+      };
+      if (io.pay_size[c] == 8) {
+        if constexpr (E == 8) column((int64_t)0);
+      } else {
+        column((int32_t)0);
+      }
+    }
+  };
+  if ((t + 1) * TILE <= n) tile(std::true_type{});
+  else tile(std::false_type{});
 }
 
 // ---------------------------------------------------------------- host wrappers
 
-PartGeom part_geom(const vx_ctx* ctx, uint64_t n) {
-  PartGeom g;
-  uint64_t waves_wanted = (n + 64 * 16 - 1) / (64 * 16);      // >= 16 steps of 64 rows per wave
-  uint64_t blocks = (waves_wanted + 3) / 4;
-  uint64_t cap = (uint64_t)ctx->cu_count * 4;
-  if (blocks > cap) blocks = cap;
-  if (blocks < 1) blocks = 1;
-  g.blocks = (uint32_t)blocks;
-  g.waves = g.blocks * 4;
-  uint64_t tile = (n + g.waves - 1) / g.waves;
-  g.tile = (tile + 63) / 64 * 64;
-  if (g.tile == 0) g.tile = 64;
-  return g;
+// Rows per tile of the sweep.  Short inputs in large tiles leave compute units idle, long ones in small
+// tiles write shorter runs and look back further: whole calls over rows of 16 bytes, 256 partitions,
+// us at tiles of 2048 / 8192: 30,000 rows 42 / 45; 300,000 47 / 49; 600,000 54 / 53; 1.0 M 66 / 61;
+// 16.0 M 296 / 210.
+static uint32_t sweep_tile(uint64_t rows) { return rows <= (1ull << 19) ? 2048 : 8192; }
+
+// words first, so that every array is 8-byte aligned: the ticket, the look-back words, the counts
+static uint64_t sweep_words(uint32_t P, uint64_t rows) {
+  const uint32_t tile = sweep_tile(rows);
+  return (rows + tile - 1) / tile * P;
+}
+static uint32_t count_groups(uint64_t rows) {
+  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(kCountGroups, rows / 4096));
 }
 
-vx_status part_hist(vx_ctx* ctx, const PartSpec& ps, const PartIO& io, const PartGeom& g,
-                    uint32_t* hist, unsigned long long* totals, const int* sum_slot,
-                    unsigned long long* sums, hipStream_t s) {
-  hipLaunchKernelGGL(k_part_hist, dim3(g.blocks), dim3(256), 0, s, ps, io, g.tile, hist, totals,
-                     sum_slot, sums);
+// sizes grow with the rows except where the tile does, so a launch over fewer rows than planned for
+// is allowed the small tiles' words
+uint64_t part_work_bytes(uint32_t n_parts, uint64_t rows) {
+  const uint64_t words = std::max(sweep_words(n_parts, rows), sweep_words(n_parts, std::min<uint64_t>(rows, 1ull << 19)));
+  return 64 + words * 8 + (uint64_t)count_groups(rows) * n_parts * 4 + 8;
+}
+
+vx_status part_ready(const PartSpec& ps, uint64_t rows, uint8_t* work, hipStream_t s) {
+  fill_zero((uint64_t*)work, 8 + sweep_words(ps.n_parts, rows), s);
   VX_HIP(hipGetLastError());
   return VX_OK;
 }
 
-vx_status part_scan(vx_ctx* ctx, const uint32_t* hist, uint32_t n_parts, uint32_t waves,
-                    const unsigned long long* part_base, unsigned long long* offs,
-                    unsigned long long* boundary, hipStream_t s) {
-  if (part_base) {
-    hipLaunchKernelGGL(k_scan_seg, dim3(n_parts), dim3(256), 0, s, hist, waves, part_base, offs);
-  } else {
-    const uint64_t count = (uint64_t)n_parts * waves;
-    uint64_t tile = 4096;
-    while ((count + tile - 1) / tile > kScanTilesMax) tile *= 2;
-    const uint32_t nt = (uint32_t)std::max<uint64_t>(1, (count + tile - 1) / tile);
-    unsigned long long* tsum = (unsigned long long*)ctx->dev_scan;
-    hipLaunchKernelGGL(k_scan_tiles, dim3(nt), dim3(kScanThreads), 0, s, hist, count, tile, tsum);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanThreads), 0, s, tsum, nt);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nt), dim3(kScanThreads), 0, s, hist, count, tile, tsum, nt, offs,
-                       n_parts, waves, boundary);
-  }
-  VX_HIP(hipGetLastError());
-  return VX_OK;
-}
-
-vx_status part_scatter(vx_ctx* ctx, const PartSpec& ps, const PartIO& io, const PartGeom& g,
-                       const unsigned long long* offs, hipStream_t s) {
+vx_status part_count(vx_ctx* ctx, const PartSpec& ps, const PartIO& io, uint8_t* work, unsigned long long* totals,
+                     bool accumulate, unsigned long long* base, unsigned long long* host_totals, const int* sum_slot,
+                     unsigned long long* sums, hipStream_t s) {
   (void)ctx;
-  hipLaunchKernelGGL(k_part_scatter, dim3(g.blocks), dim3(256), 0, s, ps, io, g.tile, offs);
+  const uint32_t P = ps.n_parts, groups = count_groups(io.n);
+  const uint64_t words = sweep_words(P, io.n);
+  uint32_t* ticket = (uint32_t*)work;
+  unsigned long long* status = (unsigned long long*)(work + 64);
+  uint32_t* part = (uint32_t*)(status + words);
+  uint32_t copies = 32;
+  while (copies > 1 && copies * P > kCountSlots) copies >>= 1;
+  if (io.key_size == 8)
+    hipLaunchKernelGGL(k_part_count<int64_t>, dim3(groups), dim3(kCountThreads), 0, s, ps, io, copies, part, status,
+                       words, ticket, sum_slot, sums);
+  else
+    hipLaunchKernelGGL(k_part_count<int32_t>, dim3(groups), dim3(kCountThreads), 0, s, ps, io, copies, part, status,
+                       words, ticket, sum_slot, sums);
+  uint32_t log2pad = 6;
+  while ((1u << log2pad) < P) ++log2pad;
+  hipLaunchKernelGGL(k_part_base, dim3(1), dim3(1024), 0, s, part, groups, P, log2pad, totals, accumulate ? 1u : 0u,
+                     base, host_totals);
+  VX_HIP(hipGetLastError());
+  return VX_OK;
+}
+
+template <typename K, uint32_t E>
+static void launch_sweep(const PartSpec& ps, const PartIO& io, const unsigned long long* base, unsigned long long* next,
+                         unsigned long long* status, uint32_t* ticket, uint32_t* stall, hipStream_t s) {
+  const uint32_t tile = sweep_tile(io.n);
+  const dim3 grid((unsigned)((io.n + tile - 1) / tile));
+  const dim3 block(kSweepThreads);
+  // more than 256 partitions take wider ids, counters and ballots
+  if (ps.n_parts <= 256) {
+    if (tile == 2048)
+      hipLaunchKernelGGL((k_part_sweep<K, E, 2, 8>), grid, block, 0, s, ps, io, base, next, status, ticket, stall);
+    else
+      hipLaunchKernelGGL((k_part_sweep<K, E, 8, 8>), grid, block, 0, s, ps, io, base, next, status, ticket, stall);
+  } else {
+    if (tile == 2048)
+      hipLaunchKernelGGL((k_part_sweep<K, E, 2, 10>), grid, block, 0, s, ps, io, base, next, status, ticket, stall);
+    else
+      hipLaunchKernelGGL((k_part_sweep<K, E, 8, 10>), grid, block, 0, s, ps, io, base, next, status, ticket, stall);
+  }
+}
+
+vx_status part_sweep(vx_ctx* ctx, const PartSpec& ps, const PartIO& io, uint8_t* work, const unsigned long long* base,
+                     unsigned long long* next, hipStream_t s) {
+  if (io.n == 0) {
+    if (next && next != base) VX_HIP(hipMemcpyAsync(next, base, ps.n_parts * 8, hipMemcpyDeviceToDevice, s));
+    return VX_OK;
+  }
+  VX_CHECK((io.n + 2047) / 2048 < (1ull << 31), VX_EINVAL, "partition: %llu rows in one launch", (unsigned long long)io.n);
+  uint32_t* ticket = (uint32_t*)work;
+  unsigned long long* status = (unsigned long long*)(work + 64);
+  uint32_t* stall = stall_word(ctx);
+  bool wide = io.key_size == 8;
+  for (uint32_t c = 0; c < io.n_pay; ++c) wide |= io.out_pay[c] && io.pay_size[c] == 8;
+  if (io.key_size == 8) launch_sweep<int64_t, 8>(ps, io, base, next, status, ticket, stall, s);
+  else if (wide) launch_sweep<int32_t, 8>(ps, io, base, next, status, ticket, stall, s);
+  else launch_sweep<int32_t, 4>(ps, io, base, next, status, ticket, stall, s);
   VX_HIP(hipGetLastError());
   return VX_OK;
 }
@@ -373,15 +455,13 @@ static vx_status partition_impl(vx_ctx* ctx, const vx_partition_desc* d, vx_part
   VX_CHECK(out->n_parts_cap >= P, VX_ECAPACITY, "partition: %u partitions exceed n_parts_cap %u", P,
            out->n_parts_cap);
 
-  // device scratch: totals, base
+  // device scratch: totals, then the partitions' first positions
   ArenaBlock tot_mem;
   tot_mem.a = &ctx->arena;
   tot_mem.p = ctx->arena.alloc(2 * P * 8 + 8 * (P + 1));
   VX_CHECK(tot_mem.p, VX_EBUDGET, "partition: no room for histograms");
   unsigned long long* totals = (unsigned long long*)tot_mem.p;
-  unsigned long long* base = totals + P;
-  unsigned long long* bnd = base + P;
-  fill_zero((uint64_t*)totals, P, ctx->compute);
+  unsigned long long* bnd = totals + P;
 
   const bool scatter = d->out_key != nullptr;
   void* out_key = d->out_key;
@@ -401,33 +481,37 @@ static vx_status partition_impl(vx_ctx* ctx, const vx_partition_desc* d, vx_part
     }
   }
 
-  double tp0 = now_ms();
-  // pass A: histogram (per chunk when streamed)
+  // the counts land in host_acc (mapped), where the host reads them after the stream is drained
+  const unsigned long long* h = (const unsigned long long*)ctx->host_acc;
+  unsigned long long* h_dev = (unsigned long long*)(ctx->host_small_dev - ctx->dev_acc_words);
+  for (uint32_t p = 0; p < P; ++p) ctx->host_acc[p] = 0;
+  // Pass A counts every chunk; pass B scatters it from the running position of each partition.  A
+  // single chunk needs no second look at its rows: its counts give the positions at once.
+  bool counted_all = false;   // work is ready for the only chunk's sweep
+  ArenaBlock wmem;
+  wmem.a = &ctx->arena;
   auto run_pass = [&](bool do_scatter) -> vx_status {
-    std::vector<PipeCol> cols(1 + (do_scatter ? d->n_pay : 0));
+    std::vector<PipeCol> cols(1 + (scatter ? d->n_pay : 0));
     cols[0].info = kc;
     cols[0].may_copy = cols[0].copy = true;
-    for (uint32_t c = 0; do_scatter && c < d->n_pay; ++c) {
+    for (uint32_t c = 0; scatter && c < d->n_pay; ++c) {
       cols[1 + c].info = pc[c];
-      cols[1 + c].may_copy = cols[1 + c].copy = true;
+      cols[1 + c].may_copy = cols[1 + c].copy = do_scatter;
     }
     Pipeline pipe;
     VX_TRY(pipe.plan(ctx, n, 0, 0, cols));
-    // per-chunk scratch sized for the largest chunk
-    PartGeom g0 = part_geom(ctx, pipe.chunk_rows());
-    ArenaBlock hmem;
-    hmem.a = &ctx->arena;
-    hmem.p = ctx->arena.alloc((uint64_t)P * g0.waves * (4 + 8));
-    VX_CHECK(hmem.p, VX_EBUDGET, "partition: no room for per-wave histograms");
-    uint32_t* hist = (uint32_t*)hmem.p;
-    unsigned long long* offs = (unsigned long long*)(hmem.p + (uint64_t)P * g0.waves * 4);
+    if (!wmem.p) {
+      wmem.p = ctx->arena.alloc(part_work_bytes(P, pipe.chunk_rows()));
+      VX_CHECK(wmem.p, VX_EBUDGET, "partition: no room for the partition scratch");
+    }
     auto kernel = [&](const ChunkView& v) -> vx_status {
       PartIO io{};
       io.key = (v.global_mask & 1u) ? (const uint8_t*)v.ptr[0] + v.row0 * kc.elsize : v.ptr[0];
       io.key_size = (uint32_t)kc.elsize;
       io.n = v.rows;
-      PartGeom g = part_geom(ctx, v.rows);
-      if (!do_scatter) return part_hist(ctx, ps, io, g, hist, totals, nullptr, nullptr, ctx->compute);
+      if (!do_scatter)
+        VX_TRY(part_count(ctx, ps, io, wmem.p, totals, v.index > 0, bnd, h_dev, nullptr, nullptr, ctx->compute));
+      if (!do_scatter && !(scatter && counted_all)) return VX_OK;
       io.n_pay = d->n_pay;
       for (uint32_t c = 0; c < d->n_pay; ++c) {
         io.pay[c] = ((v.global_mask >> (1 + c)) & 1u) ? (const uint8_t*)v.ptr[1 + c] + v.row0 * pc[c].elsize
@@ -437,29 +521,22 @@ static vx_status partition_impl(vx_ctx* ctx, const vx_partition_desc* d, vx_part
       }
       io.out_key = out_key;
       io.out_base = 0;
-      // global placement: bnd[p] is the running start of partition p (its boundary plus the
-      // rows of p in earlier chunks); base receives this chunk's counts and then advances bnd
-      VX_TRY(part_hist(ctx, ps, io, g, hist, base, nullptr, nullptr, ctx->compute));
-      VX_TRY(part_scan(ctx, hist, P, g.waves, bnd, offs, nullptr, ctx->compute));
-      VX_TRY(part_scatter(ctx, ps, io, g, offs, ctx->compute));
-      hipLaunchKernelGGL(k_advance, dim3((P + 255) / 256), dim3(256), 0, ctx->compute, bnd, base, P);
-      VX_HIP(hipGetLastError());
-      return VX_OK;
+      if (do_scatter) VX_TRY(part_ready(ps, v.rows, wmem.p, ctx->compute));
+      return part_sweep(ctx, ps, io, wmem.p, bnd, bnd, ctx->compute);
     };
+    if (!do_scatter) {
+      counted_all = pipe.n_chunks() == 1 && !pipe.streamed();
+      for (uint32_t c = 0; c < d->n_pay; ++c) counted_all &= pc[c].where == Where::Device;
+    }
     VX_TRY(pipe.run(kernel));
     VX_HIP(hipStreamSynchronize(ctx->compute));
     return VX_OK;
   };
   VX_TRY(run_pass(false));
-  std::vector<unsigned long long> h(P);
-  VX_HIP(hipMemcpy(h.data(), totals, P * 8, hipMemcpyDeviceToHost));
   std::vector<unsigned long long> b(P + 1, 0);
   for (uint32_t p = 0; p < P; ++p) b[p + 1] = b[p] + h[p];
-  if (scatter) {
-    VX_HIP(hipMemcpy(bnd, b.data(), P * 8, hipMemcpyHostToDevice));
-    fill_zero((uint64_t*)base, P, ctx->compute);
-    VX_TRY(run_pass(true));
-  }
+  if (scatter && !counted_all) VX_TRY(run_pass(true));
+  VX_TRY(check_stall(ctx, "partition"));
   for (uint32_t p = 0; p < P; ++p) out->hist[p] = h[p];
   for (uint32_t p = 0; p <= P; ++p) out->boundary[p] = b[p];
   out->n_parts = P;
@@ -473,7 +550,6 @@ static vx_status partition_impl(vx_ctx* ctx, const vx_partition_desc* d, vx_part
   out->est_imbalance_radix = rep.imbalance_radix;
   out->est_imbalance_range = rep.imbalance_range;
   out->final_loss = rep.final_loss;
-  (void)tp0;
   return VX_OK;
 }
 

@@ -455,12 +455,12 @@ vx_status cluster_side(vx_ctx* ctx, const PartSpec& ps, const int* sum_slot_dev,
   const uint32_t P = ps.n_parts;
   uint64_t row_bytes = (uint64_t)sd.key.elsize;
   for (uint32_t c = 0; c < sd.n_pay; ++c) row_bytes += (uint64_t)sd.pay[c].elsize;
-  // staging for clustered chunks (double-buffered against the write-back), per-wave
-  // histograms, offsets, per-chunk boundaries and singleton sums
-  PartGeom g0 = part_geom(ctx, sd.chunk_rows);
+  // staging for clustered chunks (double-buffered against the write-back), partition scratch,
+  // per-chunk boundaries and singleton sums
   // (a device-resident clustered copy is scattered into directly: no staging, no write-back)
   uint64_t stage_bytes = sd.on_device ? 0 : align_up(sd.chunk_rows * row_bytes + 256 * (1 + kMaxPay), 256);
-  uint64_t scratch = 2 * stage_bytes + (uint64_t)P * g0.waves * 12 +
+  const uint64_t work_bytes = align_up(part_work_bytes(P, sd.chunk_rows), 256);
+  uint64_t scratch = 2 * stage_bytes + work_bytes + (uint64_t)P * 8 +
                      std::max<uint64_t>(sd.n_chunks, 1) * (P + 1) * 8 + 2 * kMaxSumSlots * 8 + 1024;
   ArenaBlock blk;
   blk.a = &ctx->arena;
@@ -468,9 +468,9 @@ vx_status cluster_side(vx_ctx* ctx, const PartSpec& ps, const int* sum_slot_dev,
   VX_CHECK(blk.p, VX_EBUDGET, "partitioned join: no room for the partition pass scratch (%llu B)",
            (unsigned long long)scratch);
   uint8_t* stage[2] = {blk.p, blk.p + stage_bytes};
-  uint32_t* hist = (uint32_t*)(blk.p + 2 * stage_bytes);
-  unsigned long long* offs = (unsigned long long*)((uint8_t*)hist + (uint64_t)P * g0.waves * 4);
-  unsigned long long* bnd = offs + (uint64_t)P * g0.waves;
+  uint8_t* work = blk.p + 2 * stage_bytes;
+  unsigned long long* totals = (unsigned long long*)(work + work_bytes);
+  unsigned long long* bnd = totals + P;
   unsigned long long* sums = bnd + std::max<uint64_t>(sd.n_chunks, 1) * (P + 1);
   fill_zero((uint64_t*)sums, 2 * kMaxSumSlots, ctx->compute);
   hipEvent_t done[2] = {get_event(ctx), get_event(ctx)};
@@ -496,11 +496,10 @@ vx_status cluster_side(vx_ctx* ctx, const PartSpec& ps, const int* sum_slot_dev,
       io.out_pay[c] = sd.on_device ? sd.clu_pay[c] + v.row0 * sd.pay[c].elsize : out + off;
       off += align_up(v.rows * sd.pay[c].elsize, 256);
     }
-    PartGeom g = part_geom(ctx, v.rows);
-    VX_TRY(part_hist(ctx, ps, io, g, hist, nullptr, sum_slot_dev, sum_slot_dev ? sums : nullptr,
-                     ctx->compute));
-    VX_TRY(part_scan(ctx, hist, P, g.waves, nullptr, offs, bnd + v.index * (P + 1), ctx->compute));
-    VX_TRY(part_scatter(ctx, ps, io, g, offs, ctx->compute));
+    unsigned long long* at = bnd + v.index * (P + 1);   // the chunk's boundary array
+    VX_TRY(part_count(ctx, ps, io, work, totals, false, at, nullptr, sum_slot_dev, sum_slot_dev ? sums : nullptr,
+                      ctx->compute));
+    VX_TRY(part_sweep(ctx, ps, io, work, at, nullptr, ctx->compute));
     if (sd.on_device) return VX_OK;
     VX_HIP(hipEventRecord(done[b], ctx->compute));
     // write the clustered chunk back to host memory at the chunk's own rows
@@ -524,6 +523,7 @@ vx_status cluster_side(vx_ctx* ctx, const PartSpec& ps, const int* sum_slot_dev,
     put_event(ctx, wrote[b]);
   }
   VX_TRY(st);
+  VX_TRY(check_stall(ctx, "partition pass"));
   sd.sdma = pipe.sdma_bytes();
   sd.bnd.assign(sd.n_chunks * (P + 1), 0);
   sd.slot_sums.assign(2 * kMaxSumSlots, 0);

@@ -191,6 +191,14 @@ void fill_zero(uint64_t* p, uint64_t words, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)blocks), dim3(256), 0, s, p, words);
 }
 
+vx_status check_stall(vx_ctx* ctx, const char* what) {
+  volatile uint32_t* w = (volatile uint32_t*)(ctx->host_small + kHostSmallWords - 1);
+  const bool stalled = *w != 0;
+  *w = 0;
+  VX_CHECK(!stalled, VX_EHIP, "%s: a tile waited too long for the tiles before it", what);
+  return VX_OK;
+}
+
 double zc_wire_bytes(uint64_t n, uint64_t count, int elsize, uint32_t line) {
   if (n == 0 || count == 0) return 0.0;
   double s = (double)count / (double)n;
@@ -235,7 +243,7 @@ vx_status vx_ctx_create(int device, void* arena, uint64_t arena_bytes, void* str
     c->l2_bytes = (uint64_t)pr.l2CacheSize;
   }
   c->dev_acc_words = kAccRows * kAccWords;
-  const uint64_t scratch_bytes = c->dev_acc_words * 8 + 256 + (kScanTilesMax + 1) * 8;
+  const uint64_t scratch_bytes = c->dev_acc_words * 8 + 256;
   uint8_t* scratch = c->arena.alloc(scratch_bytes);
   if (!scratch) {
     delete c;
@@ -245,7 +253,6 @@ vx_status vx_ctx_create(int device, void* arena, uint64_t arena_bytes, void* str
   }
   c->dev_acc = (uint64_t*)scratch;
   c->dev_flags = (unsigned int*)(scratch + c->dev_acc_words * 8);
-  c->dev_scan = (uint64_t*)(scratch + c->dev_acc_words * 8 + 256);
   if (stream) {
     c->compute = (hipStream_t)stream;
   } else {
@@ -269,6 +276,7 @@ vx_status vx_ctx_create(int device, void* arena, uint64_t arena_bytes, void* str
     return VX_EHIP;
   }
   c->host_small = c->host_acc + c->dev_acc_words;
+  std::memset(c->host_small, 0, kHostSmallWords * 8);
   void* mapped = nullptr;
   if (hipHostGetDevicePointer(&mapped, c->host_acc, 0) != hipSuccess || !mapped) {
     (void)hipGetLastError();

@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "vx_device.h"
+#include "vx_lookback.h"
 #include "vx_part.h"
 #include "vx_pipeline.h"
 
@@ -296,62 +297,6 @@ __global__ void __launch_bounds__(1024) k_sweep_base(const uint32_t* part, uint3
   }
 }
 
-// A look-back word: a tag in the top byte (2 * pass + 1: the tile's own count; 2 * pass + 2: the
-// digit's position after this tile) and the value below.  Tags differ from pass to pass, so the
-// words are cleared once per sort.  A word is written and read whole (64 bits, device scope), and
-// nothing else passes between workgroups through it, so no fence is needed.
-constexpr uint32_t kTagShift = 56;
-constexpr unsigned long long kTagValue = (1ull << kTagShift) - 1;
-constexpr uint32_t kLookWindow = 8;        // tiles read ahead in one look-back step
-constexpr uint32_t kLookSpins = 1u << 22;  // polls before a workgroup gives up (seconds; never in a sound run)
-
-__device__ __forceinline__ unsigned long long look_load(const unsigned long long* w) {
-  return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void look_store(unsigned long long* w, uint32_t tag, unsigned long long v) {
-  __hip_atomic_store(w, ((unsigned long long)tag << kTagShift) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Position of tile t's first key of digit d = threadIdx.x: the counts of the tiles before t, back to
-// the nearest one whose running position is known (tile 0 starts from the digit's base).  Tiles are
-// taken in ticket order, so every tile waited for is running or done and publishes its count before
-// it waits itself: the wait ends.  It is bounded all the same (`stall` is set, and the sort fails).
-__device__ __forceinline__ unsigned long long look_back(const unsigned long long* status, uint64_t t, uint32_t pass,
-                                                        uint32_t* stall) {
-  const uint32_t own = 2 * pass + 1, known = 2 * pass + 2;
-  unsigned long long sum = 0;
-  int64_t look = (int64_t)t - 1;
-  uint32_t spins = 0;
-  for (;;) {
-    unsigned long long w[kLookWindow];
-#pragma unroll
-    for (uint32_t i = 0; i < kLookWindow; ++i) {
-      const int64_t at = look - (int64_t)i;
-      w[i] = look_load(status + (uint64_t)(at > 0 ? at : 0) * 256 + threadIdx.x);
-    }
-    uint32_t took = 0;
-    bool done = false;
-#pragma unroll
-    for (uint32_t i = 0; i < kLookWindow; ++i) {
-      const uint32_t tag = (uint32_t)(w[i] >> kTagShift);
-      if (!done && took == i && (tag == own || tag == known)) {
-        sum += w[i] & kTagValue;
-        took = i + 1;
-        done = tag == known;    // tile 0 is always known, so nothing past it is taken
-      }
-    }
-    if (done) return sum;
-    look -= (int64_t)took;
-    if (took == 0 && ++spins >= kLookSpins) {
-      __hip_atomic_store(stall, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      return sum;
-    }
-    if (took == 0 && (spins & 4095u) == 4095u &&
-        __hip_atomic_load(stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0)
-      return sum;
-  }
-}
-
 // One digit pass over the run; tiles of kDigitThreads * ITEMS keys.  Smaller tiles for short runs,
 // so that they still fill the chip (digit_tile).
 template <typename K, uint32_t ITEMS>
@@ -399,7 +344,7 @@ __global__ void __launch_bounds__(kDigitThreads) k_digit_sweep(const K* in, K* o
       if (FULL || first + j * 64 < n) stage[cnt[wave][digit_of(k[j], pass)] + rank[j]] = k[j];
     if (threadIdx.x < 256) {
       if (t != 0) {
-        pos = look_back(status, t, pass, stall);
+        pos = look_back(status + threadIdx.x, 256, t, pass, stall);
         look_store(status + t * 256 + threadIdx.x, 2 * pass + 2, pos + tot);
       }
       gbase[threadIdx.x] = pos - e;
@@ -538,16 +483,16 @@ struct SweepScratch {
       : base((unsigned long long*)p), tickets((uint32_t*)(p + 16384)), status((unsigned long long*)(p + 16640)) {}
 };
 
-// LSD radix sort of rows keys from src into dst, through alt: digit passes of 8 bits over the key's
-// order-preserving image (int64: 8 passes, int32: 4).  Passes alternate between dst and alt so the
-// last one writes dst; the first writes alt, so src may be dst, and is left unchanged if it is not.
-// The digit counts of k_sweep_count sit in alt until the first pass overwrites it.  scratch holds
-// sweep_bytes(rows); *stall is a host-mapped word that the caller clears and reads when done.
+// LSD radix sort of rows keys from src into dst, through alt: `passes` digit passes of 8 bits, from the
+// low byte of the key's order-preserving image up (the keys agree in what is left out).  Passes
+// alternate between dst and alt so that the last one writes dst.  With an even number the first
+// writes alt, so src may be dst; with an odd number src may be alt.  The digit counts of
+// k_sweep_count sit in the buffer that the first pass writes.  scratch holds sweep_bytes(rows);
+// *stall is the context's stall word.
 // *launches grows by the launches made.
 template <typename K>
-vx_status radix_sort_keys(const K* src, K* alt, K* dst, uint64_t rows, uint8_t* scratch, uint32_t* stall,
-                          uint64_t* launches, hipStream_t s) {
-  constexpr uint32_t passes = sizeof(K);
+vx_status radix_sort_keys(const K* src, K* alt, K* dst, uint64_t rows, uint32_t passes, uint8_t* scratch,
+                          uint32_t* stall, uint64_t* launches, hipStream_t s) {
   VX_CHECK(rows < (1ull << 44), VX_EINVAL, "sort: run of %llu keys is too long", (unsigned long long)rows);
   if (rows <= kLocalSortMax) {
     hipLaunchKernelGGL(k_local_sort<K>, dim3(1), dim3(1024), 0, s, src, dst, (uint32_t)rows);
@@ -558,12 +503,12 @@ vx_status radix_sort_keys(const K* src, K* alt, K* dst, uint64_t rows, uint8_t* 
   const uint32_t tile = digit_tile(rows);
   const uint64_t tiles = (rows + tile - 1) / tile;
   SweepScratch w(scratch);
-  // 256 * sizeof(K) counts of 4 bytes per workgroup must fit alt: at most one workgroup per 2048 keys
+  // 256 * sizeof(K) counts of 4 bytes per workgroup must fit a buffer: at most one workgroup per 2048 keys
   const unsigned groups = (unsigned)std::min<uint64_t>(kCountGroups, rows / 2048);
-  uint32_t* part = (uint32_t*)alt;
+  uint32_t* part = (uint32_t*)(passes % 2 ? dst : alt);
   hipLaunchKernelGGL(k_sweep_count<K>, dim3(groups), dim3(kCountThreads), 0, s, src, rows, part, w.status, tiles * 256,
                      w.tickets);
-  hipLaunchKernelGGL(k_sweep_base, dim3(passes), dim3(1024), 0, s, part, groups, w.base);
+  hipLaunchKernelGGL(k_sweep_base, dim3(sizeof(K)), dim3(1024), 0, s, part, groups, w.base);
   const K* in = src;
   for (uint32_t p = 0; p < passes; ++p) {
     K* out = ((passes - 1 - p) % 2 == 0) ? dst : alt;
@@ -592,8 +537,8 @@ vx_status radix_sort_keys(const K* src, K* alt, K* dst, uint64_t rows, uint8_t* 
 vx_status radix_sort_run(const void* src, void* alt, void* dst, uint64_t rows, uint32_t ks, uint8_t* scratch,
                          uint32_t* stall, uint64_t* launches, hipStream_t s) {
   if (ks == 8)
-    return radix_sort_keys((const int64_t*)src, (int64_t*)alt, (int64_t*)dst, rows, scratch, stall, launches, s);
-  return radix_sort_keys((const int32_t*)src, (int32_t*)alt, (int32_t*)dst, rows, scratch, stall, launches, s);
+    return radix_sort_keys((const int64_t*)src, (int64_t*)alt, (int64_t*)dst, rows, 8, scratch, stall, launches, s);
+  return radix_sort_keys((const int32_t*)src, (int32_t*)alt, (int32_t*)dst, rows, 4, scratch, stall, launches, s);
 }
 
 uint64_t align_to(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
@@ -632,9 +577,7 @@ vx_status sort_impl(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {
   auto pass1_bytes = [&](uint64_t rows) { return 5 * align_to(rows * ks, 256) + sweep_bytes(rows) + (1ull << 20); };
   // a device column that is one run is sorted where it lies and needs one buffer beside it
   const uint64_t direct_bytes = align_to(n * ks, 256) + sweep_bytes(n) + 256;
-  uint32_t* stall = (uint32_t*)(ctx->host_small + kHostSmallWords - 1);
-  uint32_t* stall_dev = (uint32_t*)(ctx->host_small_dev + kHostSmallWords - 1);
-  *stall = 0;
+  uint32_t* stall_dev = stall_word(ctx);
   uint64_t C = d->chunk_rows;
   if (!C && kc.where == Where::Device && direct_bytes <= ctx->arena.largest_free()) C = n;
   if (!C) {
@@ -741,7 +684,7 @@ vx_status sort_impl(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {
     sdma = pipe.sdma_bytes();
   }
   const double pass1_ms = now_ms() - tp0;
-  VX_CHECK(*(volatile uint32_t*)stall == 0, VX_EHIP, "sort: a digit pass waited too long for the tiles before it");
+  VX_TRY(check_stall(ctx, "sort"));
 
   // ---------------- pass 2: regroup and merge
   const double tm0 = now_ms();
@@ -900,6 +843,21 @@ vx_status sort_impl(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {
 }
 
 }  // namespace
+
+uint64_t sort_scratch_bytes(uint64_t rows) {
+  if (rows <= kLocalSortMax) return 0;
+  return 16640 + (rows + digit_tile(rows) - 1) / digit_tile(rows) * 2048;
+}
+
+vx_status sort_keys_i64(vx_ctx* ctx, long long* a, long long* b, uint64_t rows, uint32_t passes, uint8_t* scratch,
+                        long long** sorted, hipStream_t s) {
+  uint64_t launches = 0;
+  int64_t *src = (int64_t*)a, *other = (int64_t*)b;
+  int64_t* dst = passes % 2 ? other : src;
+  *sorted = (long long*)dst;
+  return radix_sort_keys(src, passes % 2 ? src : other, dst, rows, passes, scratch, stall_word(ctx), &launches, s);
+}
+
 }  // namespace vx
 
 extern "C" vx_status vx_sort(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {

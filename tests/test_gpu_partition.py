@@ -71,6 +71,33 @@ def test_radix_hash_device_scatter(gpu, ctx, P):
         assert np.array_equal(o.cpu().numpy(), e)
 
 
+@pytest.mark.parametrize("n", [1, 63, 2048, 2049, 1 << 19, (1 << 19) + 1, (1 << 19) + 5 * 8192])
+@pytest.mark.parametrize("method,P", [("radix_bits", 1), ("radix_hash", 4), ("radix_bits", 256), ("range", 257),
+                                      ("radix_hash", 512), ("range", 1000)])
+def test_scatter_tile_edges(gpu, ctx, method, P, n):
+    """Both tile sizes of the scatter and a row past each, both widths of its counters (256
+    partitions and 1024), every mix of 4- and 8-byte keys and payloads, none and four payloads."""
+    rng = np.random.default_rng(n + P)
+    bits = (P - 1).bit_length()
+    for kt, pts in ((np.int64, [np.int64]), (np.int64, [np.int32]), (np.int32, [np.int64]), (np.int32, [np.int32]),
+                    (np.int32, []), (np.int64, [np.int32, np.int64, np.int64, np.int32])):
+        key = rng.integers(0, 1 << 14, n).astype(kt)
+        key[: n // 3] = key[0]
+        pay = [rng.integers(-2**31, 2**31, n).astype(t) for t in pts]
+        spl = np.arange(1, P, dtype=np.int64) * 13
+        wide = key.astype(np.int64)
+        ids = (oracle.part_ids_range(wide, spl) if method == "range" else
+               oracle.part_ids_hash(wide, bits) if method == "radix_hash" else oracle.part_ids_bits(wide, 2, bits))
+        ok, op = _torch_empty_like(key), [_torch_empty_like(p) for p in pay]
+        _say("scatter tile edges", method, P, n, kt.__name__, [t.__name__ for t in pts])
+        r = ctx.partition(dev(key), [dev(p) for p in pay], method=method, n_parts=P, shift=2,
+                          splitters=spl if method == "range" else None, out_key=ok, out_pays=op)
+        h, b, ck, cp = _expect(ids, P, key, pay)
+        assert r["n_parts"] == P and np.array_equal(r["hist"], h) and np.array_equal(r["boundary"], b)
+        assert np.array_equal(ok.cpu().numpy(), ck)
+        assert all(np.array_equal(o.cpu().numpy(), e) for o, e in zip(op, cp))
+
+
 def test_radix_bits_host_streamed_scatter(gpu, ctx, monkeypatch):
     """Host-resident input in many chunks, written to host memory by zero-copy stores."""
     monkeypatch.setenv("VX_CHUNK_BYTES", str(8 * 40_000))
