@@ -2,10 +2,9 @@
 // one-hidden-layer ReLU network trained with Adam by hand-written forward/backward kernels,
 // and splitter extraction.
 //
-// Training is bit-reproducible: every wave owns a fixed contiguous slice of the sample and
-// accumulates its gradient in FP64 in sample order; per-wave partials are summed in wave order
-// by one thread per parameter.  Lane j of a wave is hidden unit j, so a sample's forward pass
-// is one FMA per lane and a fixed butterfly sum across the wave.
+// Training is bit-reproducible: every workgroup owns a fixed contiguous slice of the sample and
+// accumulates its gradient in FP64 in sample order; the slices' partials are summed in a fixed
+// order.  A sample's forward pass is one lane's, its hidden units summed as a fixed tree.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -162,128 +161,179 @@ __global__ void k_mlp_forward(const float* x, uint64_t n, const float* params, f
     y[i] = mlp_eval(x[i], p);
 }
 
-// One forward/backward pass of the mean squared error over the wave's slice of samples.
-// partial[w * kPartialStride + c]: gradient component c (w1, b1, w2, b2), then the squared-
-// error sum, all FP64.
-constexpr int kGradUnroll = 4;
+// One forward/backward pass of the mean squared error; workgroup w takes the slice of per_slice samples
+// from w * per_slice on.  partial[c * slices + w]: gradient component c (w1, b1, w2, b2), then the
+// squared-error sum, all FP64 and added in sample order.
+//
+// Forward: one sample per lane, its 64 hidden units summed as a fixed tree (units 32 apart, then 16,
+// ... 1).  The tree's first level is one fused multiply-add per unit, whose addend is the partner's
+// rounded product, so units 0..31 and units 32..63 each see an output value of their own (the two
+// orders of that addition); a unit's gradient uses its half's value, b2 and the loss the first half's.
+// Backward: hidden unit j on lane j; one wave adds w2's components, one b1's, one w1's, one b2's and
+// the loss, each through the slice in sample order.
+// Bound: the backward chains of FP64 additions, 256 dependent ones per component (their order is part
+// of the result).  Over 42,000 samples 9.9 us; one wave per slice, with a six-step exchange between
+// lanes for every sample, took 37 us.  A training step of both launches: 40.9 -> 12.2 us there,
+// 91 -> 64 us over 1.0 M samples.
+constexpr uint32_t kSliceBatch = 256;
+
+// f(r[s], x[s]) for s = 0 .. m - 1 in order, with eight samples read ahead of the eight in work.
+template <typename F>
+__device__ __forceinline__ void each_sample(uint32_t m, const double* r, const float* x, F f) {
+  constexpr uint32_t U = 8;
+  double ra[U], rb[U];
+  float xa[U], xb[U];
+  auto read = [&](uint32_t s, double (&rr)[U], float (&xx)[U]) {
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      rr[u] = r[s + u];
+      xx[u] = x[s + u];
+    }
+  };
+  auto work = [&](const double (&rr)[U], const float (&xx)[U]) {
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) f(rr[u], xx[u]);
+  };
+  uint32_t s = 0;
+  if (m >= U) read(0, ra, xa);
+  for (; s + 3 * U <= m; s += 2 * U) {
+    read(s + U, rb, xb);
+    work(ra, xa);
+    read(s + 2 * U, ra, xa);
+    work(rb, xb);
+  }
+  if (s + U <= m) {
+    work(ra, xa);
+    s += U;
+  }
+  for (; s < m; ++s) f(r[s], x[s]);
+}
 
 __global__ void __launch_bounds__(256) k_mlp_grad(const float* x, const float* t, uint64_t n,
-                                                  const float* params, uint64_t per_wave,
+                                                  const float* params, uint64_t per_slice,
                                                   double* partial) {
-  const uint32_t j = threadIdx.x & 63;
-  const uint64_t w = __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const float w1 = params[j], b1 = params[kHidden + j], w2 = params[2 * kHidden + j];
+  static_assert(kHidden == 64, "a hidden unit per lane");
+  __shared__ float4 pa[32], pb[32];              // {w1, b1, w2, -} of unit j and of unit j + 32
+  __shared__ float lx[kSliceBatch];
+  __shared__ double lr[2][kSliceBatch], le[kSliceBatch];
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+  const float w1 = params[lane], b1 = params[kHidden + lane], w2 = params[2 * kHidden + lane];
   const float b2 = params[3 * kHidden];
-  const double scale = 2.0 / (double)n;
-  double aw1 = 0, ab1 = 0, aw2 = 0, ab2 = 0, al = 0;
-  const uint64_t i0 = w * per_wave;
-  const uint64_t i1 = i0 + per_wave < n ? i0 + per_wave : n;
-  uint64_t i = i0;
-  for (; i + kGradUnroll <= i1; i += kGradUnroll) {
-    float xs[kGradUnroll], ts[kGradUnroll], z[kGradUnroll], h[kGradUnroll], ps[kGradUnroll];
+  if (threadIdx.x < 32) pa[lane] = make_float4(w1, b1, w2, 0.0f);
+  else if (threadIdx.x < 64) pb[lane - 32] = make_float4(w1, b1, w2, 0.0f);
+  const double scale = 2.0 / (double)n, w2d = (double)w2;
+  const uint64_t i0 = blockIdx.x * per_slice;
+  const uint64_t i1 = i0 + per_slice < n ? i0 + per_slice : n;
+  double acc = 0, loss = 0;   // wave 0: w2, wave 1: b1, wave 2: w1, wave 3: b2 and the loss
+  for (uint64_t base = i0; base < i1; base += kSliceBatch) {
+    const uint32_t m = (uint32_t)(i1 - base < kSliceBatch ? i1 - base : kSliceBatch);
+    __syncthreads();   // the parameters are there, the last batch has been read
+    if (threadIdx.x < m) {
+      const float xs = x[base + threadIdx.x];
+      const double ts = (double)t[base + threadIdx.x];
+      float lo[32], hi[32];
 #pragma unroll
-    for (int u = 0; u < kGradUnroll; ++u) {
-      xs[u] = x[i + u];
-      ts[u] = t[i + u];
-      z[u] = fmaf(w1, xs[u], b1);
-      h[u] = z[u] > 0.0f ? z[u] : 0.0f;
-      ps[u] = w2 * h[u];
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-      for (int u = 0; u < kGradUnroll; ++u) ps[u] += __shfl_xor(ps[u], o, 64);
-#pragma unroll
-    for (int u = 0; u < kGradUnroll; ++u) {
-      float y = b2 + ps[u];
-      double e = (double)y - (double)ts[u];
-      double r = e * scale;
-      aw2 += r * (double)h[u];
-      if (z[u] > 0.0f) {
-        double g = r * (double)w2;
-        ab1 += g;
-        aw1 += g * (double)xs[u];
+      for (int j = 0; j < 32; ++j) {
+        const float4 a = pa[j], b = pb[j];
+        const float ha = fmaxf(fmaf(a.x, xs, a.y), 0.0f), hb = fmaxf(fmaf(b.x, xs, b.y), 0.0f);
+        lo[j] = fmaf(a.z, ha, __fmul_rn(b.z, hb));
+        hi[j] = fmaf(b.z, hb, __fmul_rn(a.z, ha));
       }
-      ab2 += r;
-      al += e * e;
+#pragma unroll
+      for (int o = 16; o > 0; o >>= 1)
+#pragma unroll
+        for (int j = 0; j < o; ++j) {
+          lo[j] += lo[j + o];
+          hi[j] += hi[j + o];
+        }
+      const double el = (double)(b2 + lo[0]) - ts, eh = (double)(b2 + hi[0]) - ts;
+      lx[threadIdx.x] = xs;
+      le[threadIdx.x] = el;
+      lr[0][threadIdx.x] = el * scale;
+      lr[1][threadIdx.x] = eh * scale;
     }
+    __syncthreads();
+    // uniform per wave; `keep` holds a conditional sum's value out of a branch, so that the reads of
+    // the samples ahead are not cut off by one
+    auto keep = [](double v) {
+      asm volatile("" : "+v"(v));
+      return v;
+    };
+    if (wave == 0)
+      each_sample(m, lr[half], lx, [&](double r, float xs) { acc = fma(r, (double)fmaxf(fmaf(w1, xs, b1), 0.0f), acc); });
+    else if (wave == 1)
+      each_sample(m, lr[half], lx, [&](double r, float xs) {
+        const double v = keep(fma(r, w2d, acc));
+        acc = fmaf(w1, xs, b1) > 0.0f ? v : acc;
+      });
+    else if (wave == 2)
+      each_sample(m, lr[half], lx, [&](double r, float xs) {
+        const double v = keep(fma(r * w2d, (double)xs, acc));
+        acc = fmaf(w1, xs, b1) > 0.0f ? v : acc;
+      });
+    else
+      each_sample(m, le, lx, [&](double e, float) {
+        acc = fma(scale, e, acc);
+        loss = fma(e, e, loss);
+      });
   }
-  for (; i < i1; ++i) {
-    float xs = x[i], ts = t[i];
-    float z = fmaf(w1, xs, b1);
-    float h = z > 0.0f ? z : 0.0f;
-    float ps = w2 * h;
-    for (int o = 32; o > 0; o >>= 1) ps += __shfl_xor(ps, o, 64);
-    float y = b2 + ps;
-    double e = (double)y - (double)ts;
-    double r = e * scale;
-    aw2 += r * (double)h;
-    if (z > 0.0f) {
-      double g = r * (double)w2;
-      ab1 += g;
-      aw1 += g * (double)xs;
-    }
-    ab2 += r;
-    al += e * e;
-  }
-  double* out = partial + w * kPartialStride;
-  out[j] = aw1;
-  out[kHidden + j] = ab1;
-  out[2 * kHidden + j] = aw2;
-  if (j == 0) {
-    out[3 * kHidden] = ab2;
-    out[3 * kHidden + 1] = al;
+  double* out = partial + blockIdx.x;   // a component's partials lie side by side
+  const uint64_t stride = gridDim.x;
+  if (wave == 0) out[(2 * kHidden + lane) * stride] = acc;
+  else if (wave == 1) out[(kHidden + lane) * stride] = acc;
+  else if (wave == 2) out[lane * stride] = acc;
+  else if (lane == 0) {
+    out[3 * kHidden * stride] = acc;
+    out[(3 * kHidden + 1) * stride] = loss;
   }
 }
 
-// grad[c] = SUM over waves of partial[w][c] in a fixed order (block c: thread t adds waves
-// t, t + 256, ... in turn, then a fixed tree over the threads); grad[kModelParams] = loss.
-__global__ void __launch_bounds__(256) k_mlp_reduce(const double* partial, uint32_t waves, uint64_t n,
-                                                    double* grad) {
+// The sum of component c over the slices in a fixed order (thread t adds slices t, t + 256, ... in
+// turn, then a fixed tree over the threads: 128 apart, 64, ... 1), in thread 0.
+__device__ __forceinline__ double slice_sum(const double* partial, uint32_t slices, uint32_t c) {
   __shared__ double red[256];
-  const uint32_t c = blockIdx.x;
+  const double* p = partial + (uint64_t)c * slices;
   double s = 0;
-  for (uint32_t w = threadIdx.x; w < waves; w += blockDim.x) s += partial[(uint64_t)w * kPartialStride + c];
+  for (uint32_t w = threadIdx.x; w < slices; w += 256) s += p[w];
   red[threadIdx.x] = s;
   __syncthreads();
-  for (uint32_t h = 128; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) grad[c] = c == kModelParams ? red[0] / (double)n : red[0];
+  if (threadIdx.x >= 64) return 0;
+  double v = (red[threadIdx.x] + red[threadIdx.x + 128]) + (red[threadIdx.x + 64] + red[threadIdx.x + 192]);
+#pragma unroll
+  for (int h = 32; h > 0; h >>= 1) v += __shfl_down(v, h, 64);
+  return v;
 }
 
-// One training step's second half: block c reduces gradient component c over the waves (the
-// fixed order of k_mlp_reduce) and applies Adam (Kingma and Ba, 2015) to parameter c, on FP32
-// parameters and moments evaluated in FP64 (components are independent).
-__global__ void __launch_bounds__(256) k_mlp_reduce_adam(const double* partial, uint32_t waves, uint64_t n,
+// grad[c] = SUM over slices of component c (block c); grad[kModelParams] = loss.
+__global__ void __launch_bounds__(256) k_mlp_reduce(const double* partial, uint32_t slices, uint64_t n,
+                                                    double* grad) {
+  const uint32_t c = blockIdx.x;
+  const double v = slice_sum(partial, slices, c);
+  if (threadIdx.x == 0) grad[c] = c == kModelParams ? v / (double)n : v;
+}
+
+// One training step's second half: block c reduces gradient component c over the slices and applies
+// Adam (Kingma and Ba, 2015) to parameter c, on FP32 parameters and moments evaluated in FP64
+// (components are independent).
+__global__ void __launch_bounds__(256) k_mlp_reduce_adam(const double* partial, uint32_t slices, uint64_t n,
                                                          double* grad, float* params, float* m, float* v,
                                                          double lr, double b1, double b2, double eps, double c1,
                                                          double c2) {
-  __shared__ double red[256];
   const uint32_t c = blockIdx.x;
-  double s = 0;
-  for (uint32_t w = threadIdx.x; w < waves; w += blockDim.x) s += partial[(uint64_t)w * kPartialStride + c];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (uint32_t h = 128; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-    __syncthreads();
-  }
+  const double sum = slice_sum(partial, slices, c);
   if (threadIdx.x != 0) return;
   if (c == kModelParams) {
-    grad[c] = red[0] / (double)n;
+    grad[c] = sum / (double)n;
     return;
   }
-  grad[c] = red[0];
-  const double g = (double)(float)red[0];
+  grad[c] = sum;
+  const double g = (double)(float)sum;
   const double mj = b1 * (double)m[c] + (1.0 - b1) * g;
   const double vj = b2 * (double)v[c] + (1.0 - b2) * g * g;
   m[c] = (float)mj;
   v[c] = (float)vj;
   params[c] = (float)((double)params[c] - lr * (mj / c1) / (sqrt(vj / c2) + eps));
 }
-
 
 // c = the number of quantiles j/P (1 <= j < P) the value reaches; first[c] = min row reaching c
 __global__ void k_cross(const float* x, const float* t, uint64_t m, const float* params,
@@ -371,9 +421,9 @@ struct Model {
   float* m;
   float* v;
   double* grad;       // device [kPartialStride]
-  double* partial;    // device [waves * kPartialStride]
-  uint32_t waves;
-  uint64_t per_wave;
+  double* partial;    // device [slices * kPartialStride]
+  uint32_t slices;
+  uint64_t per_slice;
 };
 
 static void init_params(float* p) {
@@ -385,18 +435,18 @@ static void init_params(float* p) {
   p[3 * kHidden] = 0.0f;
 }
 
-static void model_geometry(const vx_ctx* ctx, uint64_t n, uint32_t* waves, uint64_t* per_wave) {
+static void model_geometry(const vx_ctx* ctx, uint64_t n, uint32_t* slices, uint64_t* per_slice) {
   uint64_t wv = std::min<uint64_t>((uint64_t)ctx->cu_count * 16, std::max<uint64_t>(1, (n + 255) / 256));
   wv = (wv + 3) / 4 * 4;
-  *per_wave = std::max<uint64_t>(1, (n + wv - 1) / wv);
-  *waves = (uint32_t)wv;
+  *per_slice = std::max<uint64_t>(1, (n + wv - 1) / wv);
+  *slices = (uint32_t)wv;
 }
 
 static vx_status grad_pass(vx_ctx* ctx, const Model& md, const float* x, const float* t, uint64_t n) {
   hipStream_t s = ctx->compute;
-  hipLaunchKernelGGL(k_mlp_grad, dim3(md.waves / 4), dim3(256), 0, s, x, t, n, md.params, md.per_wave,
+  hipLaunchKernelGGL(k_mlp_grad, dim3(md.slices), dim3(256), 0, s, x, t, n, md.params, md.per_slice,
                      md.partial);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(kPartialStride), dim3(256), 0, s, md.partial, md.waves, n, md.grad);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3(kPartialStride), dim3(256), 0, s, md.partial, md.slices, n, md.grad);
   VX_HIP(hipGetLastError());
   return VX_OK;
 }
@@ -410,9 +460,9 @@ static vx_status train(vx_ctx* ctx, Model& md, const float* x, const float* t, u
   for (uint32_t st = 1; st <= steps; ++st) {
     const double lr_t = lr * 0.5 * (1.0 + std::cos(M_PI * (double)(st - 1) / (double)steps));
     double c1 = 1.0 - std::pow(b1, (double)st), c2 = 1.0 - std::pow(b2, (double)st);
-    hipLaunchKernelGGL(k_mlp_grad, dim3(md.waves / 4), dim3(256), 0, ctx->compute, x, t, n, md.params,
-                       md.per_wave, md.partial);
-    hipLaunchKernelGGL(k_mlp_reduce_adam, dim3(kPartialStride), dim3(256), 0, ctx->compute, md.partial, md.waves,
+    hipLaunchKernelGGL(k_mlp_grad, dim3(md.slices), dim3(256), 0, ctx->compute, x, t, n, md.params,
+                       md.per_slice, md.partial);
+    hipLaunchKernelGGL(k_mlp_reduce_adam, dim3(kPartialStride), dim3(256), 0, ctx->compute, md.partial, md.slices,
                        n, md.grad, md.params, md.m, md.v, lr_t, b1, b2, eps, c1, c2);
   }
   VX_HIP(hipGetLastError());
@@ -429,8 +479,8 @@ struct ModelMem {
   ArenaBlock blk;
   Model md{};
   vx_status alloc(vx_ctx* ctx, uint64_t n) {
-    model_geometry(ctx, n, &md.waves, &md.per_wave);
-    uint64_t bytes = 3 * 1024 + 2 * kPartialStride * 8 + (uint64_t)md.waves * kPartialStride * 8;
+    model_geometry(ctx, n, &md.slices, &md.per_slice);
+    uint64_t bytes = 3 * 1024 + 2 * kPartialStride * 8 + (uint64_t)md.slices * kPartialStride * 8;
     blk.a = &ctx->arena;
     blk.p = ctx->arena.alloc(bytes);
     VX_CHECK(blk.p, VX_EBUDGET, "cdf: no room for the model scratch");

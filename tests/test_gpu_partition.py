@@ -294,6 +294,27 @@ def test_cdf_gradient_parity(gpu, ctx, seed):
     assert abs(loss_g - loss_o) <= 1e-6 * loss_o
 
 
+@pytest.mark.parametrize("n", [1, 5, 8, 23, 24, 25, 255, 256, 257, 3 * 256 + 1, 1_060_007])
+def test_cdf_gradient_slices(gpu, ctx, n):
+    """The gradient at the edges of a slice (256 samples) and of the eight samples read ahead within
+    it, empty slices, and slices of two batches, each component within the bound above.  With
+    |dy_i| from that bound, the loss is off by at most (1/n) sum (2 |e_i| |dy_i| + dy_i^2)."""
+    import torch
+    rng = np.random.default_rng(n)
+    x = np.sort(rng.random(n)).astype(np.float32)
+    t = ((np.arange(n) + 0.5) / n).astype(np.float32)
+    p = np.concatenate([rng.normal(1, 0.3, 64), -rng.random(64), rng.normal(0, 0.05, 64), [0.01]]).astype(np.float32)
+    _say("cdf gradient slices", n)
+    loss_g, g_g = ctx.cdf_loss_grad(torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda(), p)
+    loss_o, g_o = oracle.mlp_loss_grad(p, x, t)
+    u = 2.0**-24
+    err = np.abs(g_g.astype(np.float64) - g_o)
+    assert np.all(err <= _grad_bound(p, x, t) + u * np.abs(g_o) + 1e-30)
+    dy = _fwd_bound(p, x)      # 66 roundings a term: no less than the kernel's 8
+    e = np.abs(oracle.mlp_forward(p, x) - t.astype(np.float64))
+    assert abs(loss_g - loss_o) <= np.mean(2 * e * dy + dy * dy) + 1e-12 * loss_o
+
+
 def test_cdf_train_deterministic_and_descends(gpu, ctx):
     import torch
     rng = np.random.default_rng(3)
