@@ -83,8 +83,12 @@ __global__ void k_pj_init(uint32_t* slots, uint64_t capacity, uint32_t key_size,
 }
 
 // Add (cnt, sum) to key k's record; returns the slot index when this call claimed a new slot,
-// else ~0.
-template <typename K>
+// else ~0.  LOOK: read the slot first.  A slot goes from empty to its key once, so only one seen empty
+// needs the compare-and-swap; that saves an atomic for a key that is there, but costs a read of a
+// line under contention for keys that every workgroup adds (rows go with it, LDS entries without:
+// 8.0 M rows, four of each key: 1049 us without, 871 with; Zipf(1.5) keys with it on both: 390 us
+// against 273).
+template <bool LOOK, typename K>
 __device__ __forceinline__ uint64_t preagg_claim_add(const TableView& t, K k, unsigned long long cnt,
                                                      unsigned long long sum, unsigned int* flags) {
   using U = typename KeyTraits<K>::U;
@@ -98,12 +102,13 @@ __device__ __forceinline__ uint64_t preagg_claim_add(const TableView& t, K k, un
   uint64_t h = slot_of(key_bits(k), t.log2cap);
   for (uint64_t step = 0; step <= t.mask; ++step) {
     uint8_t* slot = t.slots + (h << kSlotShift);
-    U prev = atomicCAS((U*)slot, kEmpty, kb);
-    if (prev == kEmpty || prev == kb) {
+    U prev = LOOK ? __hip_atomic_load((U*)slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : kEmpty;
+    const bool claimed = prev == kEmpty && (prev = atomicCAS((U*)slot, kEmpty, kb)) == kEmpty;
+    if (claimed || prev == kb) {
       unsigned long long* w = (unsigned long long*)(slot + 8);
       atomicAdd(w, cnt);
       if (t.n_pay) atomicAdd(w + 1, sum);
-      return prev == kEmpty ? h : ~0ull;
+      return claimed ? h : ~0ull;
     }
     h = (h + 1) & t.mask;
   }
@@ -129,69 +134,145 @@ constexpr int kPjLds = 1024;
 constexpr int kPjTile = 4096;
 constexpr int kPjLdsProbes = 16;  // past this, a row goes straight to the global table
 
-// Pre-aggregate one partition's build segments (read in place: device memory or mapped host
-// memory) into the transient table: a per-tile LDS table absorbs repeated keys, its entries are
-// then added to the global table.  Every slot claimed in the global table is appended to
-// `claims` (*n_claims counts them: the partition's distinct keys), a tile at a time through an
-// LDS buffer, so the shared counter sees one atomic per tile; claims may be null (no list).
+// What a workgroup building tables keeps in LDS.
+struct PjBuildLds {
+  unsigned long long sst[kMaxSegs], spre[kMaxSegs + 1];
+  unsigned long long lkey[kPjLds], lcnt[kPjLds], lsum[kPjLds];
+  uint32_t lclaim[kPjTile + kPjLds];   // a tile claims at most one slot per row + per entry
+  uint32_t n_lclaim;
+  unsigned long long claim_base;
+};
+
+__device__ __forceinline__ void pj_load_segs(PjBuildLds& l, const SegList& sl) {
+  for (uint32_t j = threadIdx.x; j < sl.nseg; j += blockDim.x) l.sst[j] = sl.start[j];
+  for (uint32_t j = threadIdx.x; j <= sl.nseg; j += blockDim.x) l.spre[j] = sl.prefix[j];
+  __syncthreads();
+}
+
+// Pre-aggregate the tile of rows [base, base + kPjTile) of the segment list (read in place: device
+// memory or mapped host memory) into t: a per-tile LDS table absorbs repeated keys, its entries are
+// then added to the global table.  *n_claims grows by the slots claimed in the global table, and
+// `claims` (unless null) receives them, a tile at a time through an LDS buffer.
+template <typename K>
+__device__ __forceinline__ void pj_build_tile(PjBuildLds& l, const TableView& t, const void* key, const void* pay0,
+                                              uint32_t pay_size, const SegList& sl, uint64_t base, unsigned int* flags,
+                                              uint32_t* claims, unsigned long long* n_claims) {
+  const unsigned long long kFree = ~0ull;
+  for (int j = threadIdx.x; j < kPjLds; j += blockDim.x) {
+    l.lkey[j] = kFree;
+    l.lcnt[j] = 0;
+    l.lsum[j] = 0;
+  }
+  if (threadIdx.x == 0) l.n_lclaim = 0;
+  __syncthreads();
+  uint64_t end = base + kPjTile < sl.total ? base + kPjTile : sl.total;
+  uint32_t sg = seg_find(l.spre, sl.nseg, sl.base + base);
+  for (uint64_t i = base + threadIdx.x; i < end; i += blockDim.x) {
+    sg = seg_advance(l.spre, sl.nseg, sg, sl.base + i);
+    uint64_t src = l.sst[sg] + (sl.base + i - l.spre[sg]);
+    K k = load_key<K>(key, src);
+    unsigned long long v = t.n_pay ? (unsigned long long)load_signed(pay0, src, pay_size) : 0ull;
+    unsigned long long kb = (unsigned long long)(long long)k;
+    bool placed = false;
+    // a whole wave of one key is one addition, not 64 to one address (8.0 M rows of one key: 149 us
+    // without, 131 with)
+    unsigned long long c = 1;
+    const unsigned long long same = __ballot(kb == __shfl(kb, 0, 64));
+    if (same == ~0ull) {
+      c = 64;
+      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+      placed = (threadIdx.x & 63) != 0;
+    }
+    if (kb != kFree && !placed) {
+      uint32_t h = (uint32_t)slot_of(kb, 10);
+      for (int s = 0; s < kPjLdsProbes; ++s) {
+        uint32_t j = (h + s) & (kPjLds - 1);
+        unsigned long long prev = atomicCAS(&l.lkey[j], kFree, kb);
+        if (prev == kFree || prev == kb) {
+          atomicAdd(&l.lcnt[j], c);
+          atomicAdd(&l.lsum[j], v);
+          placed = true;
+          break;
+        }
+      }
+    }
+    append_claims(placed ? ~0ull : preagg_claim_add<true, K>(t, k, c, v, flags), l.lclaim, &l.n_lclaim);
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < kPjLds; j += blockDim.x)
+    append_claims(l.lkey[j] != kFree ? preagg_claim_add<false, K>(t, (K)(long long)l.lkey[j], l.lcnt[j], l.lsum[j], flags)
+                                     : ~0ull,
+                  l.lclaim, &l.n_lclaim);
+  __syncthreads();
+  if (n_claims) {   // uniform across the workgroup
+    if (threadIdx.x == 0) l.claim_base = l.n_lclaim ? atomicAdd(n_claims, (unsigned long long)l.n_lclaim) : 0ull;
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; claims && j < l.n_lclaim; j += blockDim.x) claims[l.claim_base + j] = l.lclaim[j];
+  }
+  __syncthreads();
+}
+
+// One partition's table: its tiles grid-stride.
 template <typename K>
 __global__ void __launch_bounds__(256) k_pj_build(TableView t, const void* key, const void* pay0,
                                                   uint32_t pay_size, SegList sl, unsigned int* flags,
                                                   uint32_t* claims, unsigned long long* n_claims) {
-  __shared__ unsigned long long sst[kMaxSegs], spre[kMaxSegs + 1];
-  __shared__ unsigned long long lkey[kPjLds], lcnt[kPjLds], lsum[kPjLds];
-  __shared__ uint32_t lclaim[kPjTile + kPjLds];   // a tile claims at most one slot per row + per entry
-  __shared__ uint32_t n_lclaim;
-  __shared__ unsigned long long claim_base;
-  const unsigned long long kFree = ~0ull;
-  for (uint32_t j = threadIdx.x; j < sl.nseg; j += blockDim.x) sst[j] = sl.start[j];
-  for (uint32_t j = threadIdx.x; j <= sl.nseg; j += blockDim.x) spre[j] = sl.prefix[j];
-  __syncthreads();
-  for (uint64_t base = (uint64_t)blockIdx.x * kPjTile; base < sl.total;
-       base += (uint64_t)gridDim.x * kPjTile) {
-    for (int j = threadIdx.x; j < kPjLds; j += blockDim.x) {
-      lkey[j] = kFree;
-      lcnt[j] = 0;
-      lsum[j] = 0;
-    }
-    if (threadIdx.x == 0) n_lclaim = 0;
-    __syncthreads();
-    uint64_t end = base + kPjTile < sl.total ? base + kPjTile : sl.total;
-    uint32_t sg = seg_find(spre, sl.nseg, sl.base + base);
-    for (uint64_t i = base + threadIdx.x; i < end; i += blockDim.x) {
-      sg = seg_advance(spre, sl.nseg, sg, sl.base + i);
-      uint64_t src = sst[sg] + (sl.base + i - spre[sg]);
-      K k = load_key<K>(key, src);
-      unsigned long long v = t.n_pay ? (unsigned long long)load_signed(pay0, src, pay_size) : 0ull;
-      unsigned long long kb = (unsigned long long)(long long)k;
-      bool placed = false;
-      if (kb != kFree) {
-        uint32_t h = (uint32_t)slot_of(kb, 10);
-        for (int s = 0; s < kPjLdsProbes; ++s) {
-          uint32_t j = (h + s) & (kPjLds - 1);
-          unsigned long long prev = atomicCAS(&lkey[j], kFree, kb);
-          if (prev == kFree || prev == kb) {
-            atomicAdd(&lcnt[j], 1ull);
-            atomicAdd(&lsum[j], v);
-            placed = true;
-            break;
-          }
-        }
+  __shared__ PjBuildLds l;
+  pj_load_segs(l, sl);
+  for (uint64_t base = (uint64_t)blockIdx.x * kPjTile; base < sl.total; base += (uint64_t)gridDim.x * kPjTile)
+    pj_build_tile<K>(l, t, key, pay0, pay_size, sl, base, flags, claims, n_claims);
+}
+
+// A partition's table and rows, for the launch that builds every partition's table.
+struct PjJob {
+  uint8_t* slots;
+  uint32_t log2cap, p, nseg, reserved;
+  uint64_t rows;
+  uint64_t tile0;    // tiles of the jobs before it
+};
+
+// Every partition's table in one launch: workgroup b takes the tiles [b * tiles / grid, ...) of all
+// the jobs in turn.  distinct[p] receives partition p's distinct keys.
+template <typename K>
+__global__ void __launch_bounds__(256) k_pj_build_all(const PjJob* jobs, uint32_t n_jobs, uint64_t tiles,
+                                                      const void* key, const void* pay0, uint32_t pay_size,
+                                                      uint32_t n_pay, unsigned long long* side_all,
+                                                      const unsigned long long* segs, uint64_t seg_stride,
+                                                      unsigned int* flags, unsigned long long* distinct) {
+  __shared__ PjBuildLds l;
+  const uint64_t t0 = blockIdx.x * tiles / gridDim.x, t1 = (blockIdx.x + 1ull) * tiles / gridDim.x;
+  uint32_t at = ~0u;
+  TableView t{};
+  SegList sl{};
+  for (uint64_t tile = t0; tile < t1; ++tile) {
+    uint32_t j = at;
+    if (at == ~0u || (at + 1 < n_jobs && jobs[at + 1].tile0 <= tile)) {   // the last job that starts at or before it
+      uint32_t lo = 0, hi = n_jobs;
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (jobs[mid].tile0 <= tile) lo = mid;
+        else hi = mid;
       }
-      append_claims(placed ? ~0ull : preagg_claim_add<K>(t, k, 1ull, v, flags), lclaim, &n_lclaim);
+      j = lo;
     }
-    __syncthreads();
-    for (int j = threadIdx.x; j < kPjLds; j += blockDim.x)
-      append_claims(lkey[j] != kFree ? preagg_claim_add<K>(t, (K)(long long)lkey[j], lcnt[j], lsum[j], flags)
-                                     : ~0ull,
-                    lclaim, &n_lclaim);
-    __syncthreads();
-    if (claims) {   // uniform across the workgroup
-      if (threadIdx.x == 0) claim_base = n_lclaim ? atomicAdd(n_claims, (unsigned long long)n_lclaim) : 0ull;
-      __syncthreads();
-      for (uint32_t j = threadIdx.x; j < n_lclaim; j += blockDim.x) claims[claim_base + j] = lclaim[j];
+    if (j != at) {   // uniform across the workgroup
+      at = j;
+      const PjJob q = jobs[at];
+      t.slots = q.slots;
+      t.log2cap = q.log2cap;
+      t.mask = (1ull << q.log2cap) - 1;
+      t.slot_shift = kSlotShift;
+      t.side = side_all + (uint64_t)q.p * kSideWords;
+      t.n_pay = n_pay;
+      sl.start = segs + q.p * seg_stride;
+      sl.prefix = sl.start + (kMaxSegs + 1);
+      sl.nseg = q.nseg;
+      sl.total = q.rows;
+      sl.base = 0;
+      pj_load_segs(l, sl);
     }
-    __syncthreads();
+    pj_build_tile<K>(l, t, key, pay0, pay_size, sl, (tile - jobs[at].tile0) * kPjTile, flags, nullptr,
+                     distinct + jobs[at].p);
   }
 }
 
@@ -293,12 +374,18 @@ __global__ void __launch_bounds__(256) k_pj_stream(const void* keys, uint64_t n,
     if (lacc[j]) mine[j] += lacc[j];
 }
 
-// out[j] = SUM over blocks of acc[b][j]
-__global__ void k_pj_reduce(const unsigned long long* acc, uint32_t blocks, uint32_t width,
-                            unsigned long long* out) {
-  for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < width; j += gridDim.x * blockDim.x) {
-    unsigned long long s = 0;
-    for (uint32_t b = 0; b < blocks; ++b) s += acc[(uint64_t)b * width + j];
+// out[j] = SUM over blocks of acc[b][j]: sixteen columns per workgroup, the rows in sixteen shares.
+__global__ void __launch_bounds__(256) k_pj_reduce(const unsigned long long* acc, uint32_t blocks, uint32_t width,
+                                                   unsigned long long* out) {
+  __shared__ unsigned long long sum[16][16];
+  const uint32_t c = threadIdx.x & 15, q = threadIdx.x >> 4, j = blockIdx.x * 16 + c;
+  unsigned long long s = 0;
+  if (j < width)
+    for (uint32_t b = q; b < blocks; b += 16) s += acc[(uint64_t)b * width + j];
+  sum[q][c] = s;
+  __syncthreads();
+  if (q == 0 && j < width) {
+    for (uint32_t r = 1; r < 16; ++r) s += sum[r][c];
     out[j] = s;
   }
 }
@@ -645,7 +732,10 @@ vx_status join_partitioned(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_ou
       const double part_rows = (double)B.n * rep.max_share * 1.25 + 1024.0;
       const double tbytes = 32.0 * 2.0 * 1.25 * part_rows;
       plan_compact = 32.0 * 1.8 * rep.distinct_share * ns_rows;
-      const double pipe_bytes = 3.0 * (64 << 20) * 2.0 + (512 << 20);
+      // the probe pipeline's buffers and room to spare: 896 MiB, or a quarter of a smaller arena (at
+      // 1 GiB the clustered copy of 8 M rows then stays on the device: 22.0 -> 19.0 ms a join)
+      const double pipe_bytes = std::min(3.0 * (64 << 20) * 2.0 + (512 << 20),
+                                         std::max(192.0 * (1 << 20), (double)ctx->arena.capacity() / 4));
       // pass 1 holds the clustered copy beside its own chunk buffers; pass 2 gets those back
       uint64_t row_bytes = (uint64_t)ks;
       for (uint32_t c = 0; c < B.n_pay; ++c) row_bytes += (uint64_t)bs.pay[c].elsize;
@@ -703,19 +793,35 @@ vx_status join_partitioned(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_ou
     return c;
   };
   const uint64_t tcap_max = pow2_at_least(max_rows + max_rows / 4);
+  // When a table for every partition fits, sized for all of its rows to be distinct, they are all
+  // built in place by one launch.  Otherwise the partitions take turns in a transient table and are
+  // compacted, with a round trip each to size the compact table (8.0 M build rows in 177 table
+  // partitions, clustered copy on the host: 21 ms of builds, one launch 2.8 ms).
+  uint64_t all_bytes = 0, all_tiles = 0;
+  for (uint32_t p = 0; p < P; ++p)
+    if (slot[p] < 0 && brows[p]) all_bytes += pow2_at_least(brows[p] + brows[p] / 4) << kSlotShift;
   const unsigned G = (unsigned)ctx->cu_count * 2;   // probe-stream grid (fixed: accumulator rows)
   const uint64_t seg_stride = 2 * (uint64_t)(kMaxSegs + 1);
   uint8_t* mem_t = nullptr;
-  ArenaBlock tmem, aux;
-  tmem.a = aux.a = &ctx->arena;
-  tmem.p = ctx->arena.alloc((tcap_max << kSlotShift) + 256 + tcap_max * 4);
-  VX_CHECK(tmem.p, VX_EBUDGET,
-           "partitioned join: the largest partition (%llu build rows, %llu transient slots) does not fit "
-           "the arena; use more partitions", (unsigned long long)max_rows, (unsigned long long)tcap_max);
-  mem_t = tmem.p;
-  uint32_t* claims = (uint32_t*)(mem_t + (tcap_max << kSlotShift) + 256);   // slots claimed by a build
+  ArenaBlock tmem, aux, cmem;
+  tmem.a = aux.a = cmem.a = &ctx->arena;
   const uint64_t aux_words = (uint64_t)P * kSideWords + (uint64_t)P + (uint64_t)P +
-                             (uint64_t)G * 3 * P + 3ull * P + (uint64_t)P * seg_stride + 8;
+                             (uint64_t)G * 3 * P + 3ull * P + (uint64_t)P * seg_stride + (uint64_t)P + 8 +
+                             (uint64_t)P * sizeof(PjJob) / 8;
+  const uint64_t chunk_bytes = env_u64("VX_CHUNK_BYTES", 64ull << 20) + 256;
+  const uint64_t probe_buffers = Q.n_buffers ? Q.n_buffers : std::max<uint64_t>(2, env_u64("VX_BUFFERS", 2));
+  const uint64_t probe_bytes = qs.key.where != Where::Host ? 0
+                               : probe_buffers * (std::max<uint64_t>(chunk_bytes, std::min(Q.chunk_rows, Q.n) * ks) + 512);
+  const bool build_all = ctx->arena.largest_free() >= all_bytes + aux_words * 8 + (1u << 20) + probe_bytes;
+  uint32_t* claims = nullptr;   // slots claimed by a build in the transient table
+  if (!build_all) {
+    tmem.p = ctx->arena.alloc((tcap_max << kSlotShift) + 256 + tcap_max * 4);
+    VX_CHECK(tmem.p, VX_EBUDGET,
+             "partitioned join: the largest partition (%llu build rows, %llu transient slots) does not fit "
+             "the arena; use more partitions", (unsigned long long)max_rows, (unsigned long long)tcap_max);
+    mem_t = tmem.p;
+    claims = (uint32_t*)(mem_t + (tcap_max << kSlotShift) + 256);
+  }
   aux.p = ctx->arena.alloc(aux_words * 8);
   VX_CHECK(aux.p, VX_EBUDGET, "partitioned join: no room for the partition directory");
   unsigned long long* side_all = (unsigned long long*)aux.p;
@@ -724,10 +830,12 @@ vx_status join_partitioned(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_ou
   unsigned long long* accb = tab_slots + 2 * (uint64_t)P;    // tab_log2 takes P/2 words; P words reserved
   unsigned long long* acc_out = accb + (uint64_t)G * 3 * P;
   unsigned long long* segdev = acc_out + 3ull * P;
-  unsigned long long* distinct = segdev + (uint64_t)P * seg_stride;   // claims in the transient table
+  unsigned long long* distinct = segdev + (uint64_t)P * seg_stride;   // claims in the table(s) being built
+  PjJob* jobs_dev = (PjJob*)(distinct + P + 8);
   fill_zero((uint64_t*)aux.p, aux_words, ctx->compute);
-  hipLaunchKernelGGL(k_pj_init, dim3(grid_for(ctx, tcap_max)), dim3(256), 0, ctx->compute, (uint32_t*)mem_t,
-                     tcap_max, (uint32_t)ks, (unsigned long long*)nullptr);
+  if (!build_all)
+    hipLaunchKernelGGL(k_pj_init, dim3(grid_for(ctx, tcap_max)), dim3(256), 0, ctx->compute, (uint32_t*)mem_t,
+                       tcap_max, (uint32_t)ks, (unsigned long long*)nullptr);
   fill_zero((uint64_t*)ctx->dev_flags, 1, ctx->compute);
   // build segment lists of every partition: [p][start | prefix]
   std::vector<unsigned long long> hseg((uint64_t)P * seg_stride, 0);
@@ -743,6 +851,13 @@ vx_status join_partitioned(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_ou
     }
   }
   VX_HIP(hipMemcpyAsync(segdev, hseg.data(), hseg.size() * 8, hipMemcpyHostToDevice, ctx->compute));
+  // the tables of the one-launch build come first, so that the pipeline's buffers take what is left
+  uint64_t cbytes = 0;
+  if (build_all) {
+    cbytes = std::max<uint64_t>(all_bytes, 4096);
+    cmem.p = ctx->arena.alloc(cbytes);
+    VX_CHECK(cmem.p, VX_EBUDGET, "partitioned join: no room left for the partition tables");
+  }
   // probe pipeline (keys only).  On the device plan pass 2 reads HBM and leaves the host link
   // idle, so the pipeline takes every chunk buffer the arena spares beside the expected
   // compact tables and starts their copies before the builds.
@@ -751,22 +866,21 @@ vx_status join_partitioned(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_ou
   qcols[0].may_copy = qcols[0].copy = true;
   uint32_t qbuf = Q.n_buffers;
   if (bs.on_device && plan_compact > 0 && qs.key.where == Where::Host && Q.n_buffers == 0) {
-    const uint64_t chunk_bytes = env_u64("VX_CHUNK_BYTES", 64ull << 20) + 256;
     // buffers fill holes first (first fit); the compact tables then need one contiguous block
-    const double spare = (double)(ctx->arena.capacity() - ctx->arena.used()) - 1.05 * plan_compact -
-                         (double)(512u << 20);
+    const double spare = build_all ? (double)(ctx->arena.capacity() - ctx->arena.used()) - (double)(1u << 20)
+                                   : (double)(ctx->arena.capacity() - ctx->arena.used()) - 1.05 * plan_compact -
+                                         (double)(512u << 20);
     qbuf = (uint32_t)std::max<double>(2.0, std::min<double>((double)kMaxBuffers, spare / (double)chunk_bytes));
   }
   Pipeline pipe;
   VX_TRY(pipe.plan(ctx, Q.n, Q.chunk_rows, qbuf, qcols));
-  // compact tables: most of what is left
-  ArenaBlock cmem;
-  cmem.a = &ctx->arena;
-  uint64_t cbytes = ctx->arena.largest_free() / 256 * 256;
-  cbytes = cbytes > (1u << 20) ? cbytes - (1u << 20) : 0;
-  VX_CHECK(cbytes >= 4096, VX_EBUDGET, "partitioned join: no room left for the partition tables");
-  cmem.p = ctx->arena.alloc(cbytes);
-  VX_CHECK(cmem.p, VX_EBUDGET, "partitioned join: no room left for the partition tables");
+  if (!build_all) {   // compact tables: most of what is left
+    cbytes = ctx->arena.largest_free() / 256 * 256;
+    cbytes = cbytes > (1u << 20) ? cbytes - (1u << 20) : 0;
+    VX_CHECK(cbytes >= 4096, VX_EBUDGET, "partitioned join: no room left for the partition tables");
+    cmem.p = ctx->arena.alloc(cbytes);
+    VX_CHECK(cmem.p, VX_EBUDGET, "partitioned join: no room left for the partition tables");
+  }
 
   const uint8_t* dk_b = bs.clu_key;
   const uint8_t* dp_b = B.n_pay ? bs.clu_pay[0] : nullptr;
@@ -806,7 +920,42 @@ vx_status join_partitioned(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_ou
   bool any_resident = false;
   double dmx = 0, dtot = 0;   // distinct build keys of the table partitions
   uint32_t dparts = 0;
-  for (uint32_t p = 0; p < P; ++p) {
+  std::vector<PjJob> jobs;
+  if (build_all) {
+    for (uint32_t p = 0; p < P; ++p) {
+      if (slot[p] >= 0 || brows[p] == 0) continue;
+      const uint64_t cap = pow2_at_least(brows[p] + brows[p] / 4);
+      PjJob q{};
+      q.slots = cmem.p + cused;
+      while ((1ull << q.log2cap) < cap) ++q.log2cap;
+      q.p = p;
+      q.nseg = (uint32_t)sb_of[p];
+      q.rows = nb_of[p];
+      q.tile0 = all_tiles;
+      jobs.push_back(q);
+      h_slots[p] = (unsigned long long)(uintptr_t)q.slots;
+      h_log2[p] = q.log2cap;
+      cused += cap << kSlotShift;
+      all_tiles += (q.rows + kPjTile - 1) / kPjTile;
+    }
+  }
+  if (!jobs.empty()) {
+    const uint64_t slots_all = cused >> kSlotShift;
+    VX_HIP(hipMemcpyAsync(jobs_dev, jobs.data(), jobs.size() * sizeof(PjJob), hipMemcpyHostToDevice, ctx->compute));
+    hipLaunchKernelGGL(k_pj_init, dim3(grid_for(ctx, slots_all)), dim3(256), 0, ctx->compute, (uint32_t*)cmem.p,
+                       slots_all, (uint32_t)ks, (unsigned long long*)nullptr);
+    const unsigned gb = (unsigned)std::min<uint64_t>(all_tiles, (uint64_t)ctx->cu_count * 3);
+    if (k64)
+      hipLaunchKernelGGL(k_pj_build_all<int64_t>, dim3(gb), dim3(256), 0, ctx->compute, jobs_dev, (uint32_t)jobs.size(),
+                         all_tiles, dk_b, dp_b, psz, B.n_pay, side_all, segdev, seg_stride, ctx->dev_flags, distinct);
+    else
+      hipLaunchKernelGGL(k_pj_build_all<int32_t>, dim3(gb), dim3(256), 0, ctx->compute, jobs_dev, (uint32_t)jobs.size(),
+                         all_tiles, dk_b, dp_b, psz, B.n_pay, side_all, segdev, seg_stride, ctx->dev_flags, distinct);
+    VX_HIP(hipGetLastError());
+    any_resident = true;
+    launches += 2;
+  }
+  for (uint32_t p = 0; p < P && !build_all; ++p) {
     if (slot[p] >= 0 || brows[p] == 0) continue;
     const uint64_t nb = nb_of[p];
     TableView t{};
@@ -876,12 +1025,19 @@ vx_status join_partitioned(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_ou
   const double tb1 = now_ms();
   if (any_resident || stream_passes == 0) VX_TRY(stream_probe());
   launches += pipe.kernel_launches();
-  hipLaunchKernelGGL(k_pj_reduce, dim3((3 * P + 255) / 256), dim3(256), 0, ctx->compute, accb, G, 3 * P, acc_out);
+  hipLaunchKernelGGL(k_pj_reduce, dim3((3 * P + 15) / 16), dim3(256), 0, ctx->compute, accb, G, 3 * P, acc_out);
   VX_HIP(hipGetLastError());
   std::vector<unsigned long long> accs(3ull * P);
   VX_HIP(hipMemcpyAsync(accs.data(), acc_out, accs.size() * 8, hipMemcpyDeviceToHost, ctx->compute));
+  std::vector<unsigned long long> nd_of(P, 0);
+  if (build_all) VX_HIP(hipMemcpyAsync(nd_of.data(), distinct, P * 8, hipMemcpyDeviceToHost, ctx->compute));
   VX_HIP(hipStreamSynchronize(ctx->compute));
   VX_TRY(check_flags(ctx, "partitioned join"));
+  for (const PjJob& q : jobs) {
+    dmx = std::max(dmx, (double)nd_of[q.p]);
+    dtot += (double)nd_of[q.p];
+    ++dparts;
+  }
   double join_ms = now_ms() - tj0;
   if (trace)
     fprintf(stderr, "[vx] partitioned join: pass 1 %.1f ms; pass 2 builds until %.1f ms, probe stream %.1f ms, "

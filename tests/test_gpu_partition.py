@@ -502,6 +502,26 @@ def test_partitioned_join_per_partition_radix(gpu, ctx):
     assert [sum(x) % (1 << 64) for x in zip(*per)] == got
 
 
+@pytest.mark.parametrize("budget_mib", [24, 40, 96])
+@pytest.mark.parametrize("method", ["quantile", "radix_hash"])
+def test_partitioned_join_budgets(gpu, budget_mib, method, monkeypatch):
+    """The tables of all partitions in one launch (the largest budget), or one partition after the
+    other through the transient table; several chunks per side; 8-byte keys with a payload, 4-byte
+    keys (the empty marker among them) without."""
+    monkeypatch.setenv("VX_CHUNK_BYTES", str(8 * 60_000))
+    bk, bp, pk = _zipf_join(500_000, 700_001, 17)
+    b4, p4 = (bk % 100_003).astype(np.int32), (pk % 100_003).astype(np.int32)
+    b4[::999] = p4[::777] = np.iinfo(np.int32).min
+    with gpu.Context(budget_mib << 20) as c:
+        for b, pays, p in ((bk, [bp], pk), (b4, [], p4)):
+            _say("partitioned budgets", budget_mib, method, b.dtype)
+            got, st, used, per = c.join_partitioned(pinned(gpu, b), [pinned(gpu, x) for x in pays], pinned(gpu, p),
+                                                    method=method, n_parts=64, seed=3, per_partition=True)
+            assert got == oracle.join_agg(b, pays, p, [])
+            assert [sum(x) % (1 << 64) for x in zip(*per)] == got
+            assert st["imbalance_distinct"] >= 1.0
+
+
 def test_partitioned_join_edges(gpu, ctx):
     i64 = np.iinfo(np.int64)
     _say("partitioned edges")
