@@ -1218,9 +1218,18 @@ vx_status join_radix(vx_ctx* ctx, const vx_radix_join* d, vx_join_out* out) {
     const uint64_t hA = side_clustered_bytes(as), hB = side_clustered_bytes(bs);
     const uint64_t rb = std::max(side_row_bytes(as), side_row_bytes(bs));
     const uint64_t exp_rows = (uint64_t)(1.05 * (double)A.n / P) + 64;
-    const uint64_t pass1_est = 4 * std::min<uint64_t>(std::max(A.n, Bd.n), 1ull << 23) * rb + (64ull << 20);
+    const uint64_t rows = std::max(A.n, Bd.n);
+    const uint64_t chunk = std::min(rows, std::max((rows + kMaxSegs - 1) / kMaxSegs,
+                                                   env_u64("VX_CHUNK_BYTES", 64ull << 20) / 8));
+    // In the arena the clustered tables cross the link once instead of three times.  That takes room for
+    // them beside pass 1's two chunk buffers, and then beside a table of at least a quarter of the
+    // expected size: building a partition in up to four slices reads its B rows again from device
+    // memory, at some 40 G rows/s, where the host copy costs 2 x 16 bytes a row of a 57 GB/s link
+    // (2^24 + 2^24 rows in a 1 GiB arena, two slices a partition: 26.7 -> 13.7 ms).
+    const uint64_t pass1_need = 2 * (chunk * rb + 1024) + part_work_bytes(P, chunk) + (32ull << 20);
+    const uint64_t pass2_need = table_bytes(exp_rows) / 4 + 2ull * P * 2 * (kMaxSegs + 1) * 8 + (32ull << 20);
     const bool dev = d->placement == 2 ||
-                     (d->placement == 0 && hA + hB + 512 + table_bytes(exp_rows) + pass1_est + (256ull << 20) <= free0);
+                     (d->placement == 0 && hA + hB + 512 + std::max(pass1_need, pass2_need) <= free0);
     as.on_device = bs.on_device = dev;
     uint8_t* base = nullptr;
     if (dev) {

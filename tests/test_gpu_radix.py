@@ -61,6 +61,28 @@ def test_radix_join_recipe_one_partition(gpu, ctx):
     assert st["zc_bytes"] == na * 16 + nb * 16
 
 
+@pytest.mark.parametrize("mult", [1, 2])
+@pytest.mark.parametrize("budget_mib,device", [(64, False), (80, True)])
+def test_radix_join_auto_placement(gpu, budget_mib, device, mult, monkeypatch):
+    """The automatic placement on both sides of its rule: clustered copies in host memory, or in the
+    arena beside a smaller table.  Even keys (mult 2) all fall into partition 0, which then takes
+    several slices."""
+    monkeypatch.setenv("VX_CHUNK_BYTES", str(8 * 100_000))
+    rng = np.random.default_rng(mult)
+    n = 1_000_000
+    ak = rng.permutation(n).astype(np.int64) * mult
+    bk = rng.integers(0, n, n + 333).astype(np.int64) * mult
+    av, bv = rng.integers(0, 1 << 32, n), rng.integers(0, 1 << 32, n + 333)
+    _say("radix auto placement", budget_mib, mult)
+    with gpu.Context(budget_mib << 20) as c:
+        got, st = c.join_radix(pinned(gpu, ak), [pinned(gpu, av)], pinned(gpu, bk), [pinned(gpu, bv)])
+    a_of = np.zeros(n, np.uint64)
+    a_of[ak // mult] = av.astype(np.uint64)
+    assert got == [n + 333, int(a_of[bk // mult].sum(dtype=np.uint64)), int(bv.astype(np.uint64).sum(dtype=np.uint64))]
+    assert st["n_parts"] >= 2 and (st["zc_bytes"] == 0) == device
+    assert st["chunks"] > (1 if mult == 2 else st["n_parts"] - 1)
+
+
 @pytest.mark.parametrize("placement", [1, 2])
 def test_radix_join_clustered(gpu, ctx, placement, monkeypatch):
     """Both tables clustered into 16 partitions by raw key bits over several pass-1 chunks (ragged
