@@ -108,7 +108,10 @@ struct vx_ctx {
   // readbacks (error flags) that are read beside it
   uint64_t* host_acc = nullptr;
   uint64_t* host_small = nullptr;
-  uint64_t* host_small_dev = nullptr;  // host_small as the device sees it: kernels store there directly
+  // host_acc and host_small as the device sees them: kernels store small results there themselves,
+  // which saves a copy's launch and its wait
+  uint64_t* host_acc_dev = nullptr;
+  uint64_t* host_small_dev = nullptr;
   // device-to-host copies of intermediate results (partition pass write-back)
   hipStream_t d2h = nullptr;
   // pinned host memory for intermediates that live in CPU memory (grow-only, kept until destroy)
@@ -141,10 +144,28 @@ void put_event(vx_ctx* ctx, hipEvent_t e);
 // Zero a device range on a stream with a fill kernel (no memset nodes: safe to capture).
 void fill_zero(uint64_t* p, uint64_t words, hipStream_t s);
 
+// Several device ranges filled by one launch.  A range is 16-byte aligned and a multiple of 16 bytes;
+// every `period` 32-bit words (a power of two) start with v0, v1 and are zero else.
+struct FillList {
+  static constexpr uint32_t kMax = 16;
+  struct Job {
+    void* p;
+    uint64_t quads;
+    uint32_t period, v0, v1, reserved;
+  } job[kMax];
+  uint32_t n = 0;
+  void pattern(void* p, uint64_t bytes, uint32_t period, uint32_t v0, uint32_t v1);
+  void zero(void* p, uint64_t bytes) { pattern(p, bytes, 4, 0, 0); }
+  vx_status launch(hipStream_t s);
+};
+
 // Estimated zero-copy wire bytes of reading `count` matching rows, of elsize bytes each,
 // spread over `n` rows: the touched lines of `line` bytes under independent selection.
 double zc_wire_bytes(uint64_t n, uint64_t count, int elsize, uint32_t line);
 constexpr uint64_t kHostSmallWords = 32;
+// dev_flags is the first of kFlagBytes bytes: the error flags, then at kFlagCount two counters of the
+// builds' duplicate checks
+constexpr uint64_t kFlagBytes = 256, kFlagCount = 64;
 // A host-mapped word that a kernel's bounded wait sets when it gives up (its device address), and the
 // check of it once the streams are drained.
 inline uint32_t* stall_word(const vx_ctx* ctx) { return (uint32_t*)(ctx->host_small_dev + kHostSmallWords - 1); }

@@ -19,25 +19,6 @@
 
 namespace vx {
 
-// ---------------------------------------------------------------- table init
-
-// Every slot gets the empty-marker key and zero payloads.  The slots are written as 16-byte
-// stores of four 32-bit words; a slot is 2^k >= 2 words and the capacity is >= 64, so the word
-// count is a multiple of 4.  The marker is INT32_MIN in word 0 of an int32 key, and for an int64
-// key (little-endian INT64_MIN) word 0 is zero and word 1 holds 0x80000000.
-__global__ void k_init_slots(uint32_t* slots, uint64_t capacity, uint32_t slot_words,
-                             uint32_t key_size) {
-  const uint32_t key_word = key_size == 4 ? 0 : 1;
-  const uint64_t quads = capacity * slot_words / 4;
-  for (uint64_t q = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; q < quads;
-       q += (uint64_t)gridDim.x * blockDim.x) {
-    uint32_t v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = ((4 * q + j) & (slot_words - 1)) == key_word ? 0x80000000u : 0u;
-    ((uint4*)slots)[q] = make_uint4(v[0], v[1], v[2], v[3]);
-  }
-}
-
 // ---------------------------------------------------------------- build (unique keys)
 
 struct BuildCols {
@@ -367,12 +348,83 @@ struct ProbeCols {
 constexpr int kGranuleWord = 9;
 static_assert(kGranuleWord < kAccWords, "the granule count needs its own accumulator word");
 
+// What a probe launch does besides probing, for a one-shot join of a single chunk.
+struct ProbeFinish {
+  uint32_t count;             // count the build's filled slots (direct) or presence bytes (dense) into
+                              // accumulator kGranuleWord: the duplicate check, spread over the probe
+  uint32_t publish;           // the last workgroup to finish stores the accumulators to host[0 ..
+  unsigned long long* host;   // kAccWords), side[0] and the flags after them
+  const unsigned int* flags;
+};
+
+// Accumulators of a launch that publishes: kAccCopies rows of kAccStride words, a row per line and
+// workgroup b adding to row b mod kAccCopies, each with a ticket in word kAccWords, and the rows'
+// ticket after them.  All the workgroups of such a launch end at about the same time, and 2048 of
+// them adding to one line (and taking one ticket) wait for each other: the probe of 2^24 rows took 84
+// us with one row, 70 with these
+constexpr uint32_t kAccCopies = 32, kAccStride = 16;
+constexpr uint64_t kAccPublishBytes = (kAccCopies * kAccStride + 2) * 8;
+
+template <typename K, int LAYOUT>
+__device__ __forceinline__ unsigned long long filled_share(const TableView& t) {
+  const uint64_t first = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
+  unsigned long long c = 0;
+  if (LAYOUT == kLayoutDense) {
+    const uint64_t words = t.direct_range / 4;
+    for (uint64_t w = first; w < words; w += step) {
+      const uint32_t v = ((const uint32_t*)t.present)[w];   // the bytes are 0 or 1
+      c += (v & 0xffu) + ((v >> 8) & 0xffu) + ((v >> 16) & 0xffu) + (v >> 24);
+    }
+    for (uint64_t b = words * 4 + first; b < t.direct_range; b += step) c += t.present[b];
+  } else {
+    using U = typename KeyTraits<K>::U;
+    for (uint64_t s = first; s < t.direct_range; s += step)
+      c += *(const U*)(t.slots + (s << t.slot_shift)) != KeyTraits<K>::kEmpty;
+  }
+  return c;
+}
+
+// After block_flush: the last workgroup of the launch stores the sums where the host reads them (a
+// copy launch and its wait cost more than the tickets).  Only atomics pass between the workgroups, so
+// all that is needed is that a wave's additions are done before it takes its ticket; a device fence
+// would write back an XCD's L2 for every workgroup (2048 of them: the probe of 2^24 rows took 106 us
+// with it).
+__device__ __forceinline__ void publish_last(const ProbeFinish& f, const TableView& t, unsigned long long* acc) {
+  if (threadIdx.x >= 64) return;   // the wave that added the workgroup's sums
+  const uint32_t rows = gridDim.x < kAccCopies ? gridDim.x : kAccCopies;
+  uint32_t last = 0;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (threadIdx.x == 0) {
+    const uint32_t r = blockIdx.x % kAccCopies, members = (gridDim.x - r + kAccCopies - 1) / kAccCopies;
+    if (atomicAdd((unsigned int*)(acc + r * kAccStride + kAccWords), 1u) == members - 1)
+      last = atomicAdd((unsigned int*)(acc + kAccCopies * kAccStride), 1u) == rows - 1;
+  }
+  if (!__shfl(last, 0, 64)) return;
+  if (threadIdx.x < kAccWords) {
+    unsigned long long s = 0;
+    for (uint32_t r = 0; r < rows; ++r) s += atomicAdd(acc + r * kAccStride + threadIdx.x, 0ull);
+    f.host[threadIdx.x] = s;
+  } else if (threadIdx.x == kAccWords) {
+    f.host[kAccWords] = t.side[0];
+  } else if (threadIdx.x == kAccWords + 1) {
+    f.host[kAccWords + 1] = *f.flags;
+  }
+}
+
+// One wave: the same for a keyed table's probe, from its one accumulator row.
+__global__ void __launch_bounds__(64) k_publish(const unsigned long long* acc, const unsigned long long* side,
+                                                const unsigned int* flags, unsigned long long* host) {
+  if (threadIdx.x < kAccWords) host[threadIdx.x] = acc[threadIdx.x];
+  else if (threadIdx.x == kAccWords) host[kAccWords] = side[0];
+  else if (threadIdx.x == kAccWords + 1) host[kAccWords + 1] = *flags;
+}
+
 // LAYOUT: the table's layout (t.direct: hash, direct or dense), fixed at compile time so that the
 // hash loop carries no test of it.
 // COUNT: count the zero-copy granules of the gathers (compiled in only when asked for: the count
 // slows the gather loop by about 4%).
 template <typename K, bool PREAGG, int ITEMS, int LAYOUT, bool COUNT>
-__global__ void __launch_bounds__(256) k_probe(TableView t, ProbeCols q, unsigned long long* acc_out) {
+__global__ void __launch_bounds__(256) k_probe(TableView t, ProbeCols q, unsigned long long* acc_out, ProbeFinish f) {
   using U = typename KeyTraits<K>::U;
   const U kEmpty = KeyTraits<K>::kEmpty;
   constexpr int NACC = kAccWords;
@@ -472,7 +524,16 @@ __global__ void __launch_bounds__(256) k_probe(TableView t, ProbeCols q, unsigne
     }
   }
   acc[kGranuleWord] = (threadIdx.x & 63) == 0 ? granules : 0;   // once per wave
-  block_flush<NACC>(acc, NACC, acc_out);
+  if constexpr (!COUNT && LAYOUT != kLayoutHash)
+    if (f.count) acc[kGranuleWord] = filled_share<K, LAYOUT>(t);
+  // only the dense layout publishes from here: the keyed probes' loops lose a fifth of their speed to
+  // it (12.0 M int64 keys in 2^22 slots, 271 -> 328 us), so a launch of its own does it for them
+  if constexpr (LAYOUT == kLayoutDense) {
+    block_flush<NACC>(acc, NACC, f.publish ? acc_out + blockIdx.x % kAccCopies * kAccStride : acc_out);
+    if (f.publish) publish_last(f, t, acc_out);
+  } else {
+    block_flush<NACC>(acc, NACC, acc_out);
+  }
 }
 
 // Where k_probe_rows writes the join's rows (device-visible addresses: device memory or mapped
@@ -760,7 +821,7 @@ static vx_status plan_table(int32_t key_type, uint32_t flags, const int32_t* pay
 
 vx_status make_table(vx_ctx* ctx, int32_t key_type, uint32_t flags, const int32_t* pay_types,
                      uint32_t n_pay, uint64_t expected_rows, float load_factor, vx_table** out,
-                     const KeyRange* kr) {
+                     const KeyRange* kr, FillList* fills) {
   *out = nullptr;
   TableView v{};
   uint64_t cap = 0;
@@ -792,16 +853,16 @@ vx_status make_table(vx_ctx* ctx, int32_t key_type, uint32_t flags, const int32_
   t->flags = flags;
   for (uint32_t p = 0; p < n_pay; ++p) t->pay_type[p] = (uint32_t)pay_types[p];
   t->view = v;
+  FillList own;
+  FillList& fl = fills ? *fills : own;
   if (dense) {
     // every payload slot is written by the build; the presence bytes and the side record start at zero
-    fill_zero((uint64_t*)v.present, (bits_bytes + 256) / 8, ctx->compute);
-  } else {
-    const uint64_t quads = cap * slot_bytes / 16;   // 16-byte stores of k_init_slots
-    uint64_t blocks = std::min<uint64_t>((quads + 255) / 256, 8192);
-    hipLaunchKernelGGL(k_init_slots, dim3((unsigned)blocks), dim3(256), 0, ctx->compute,
-                       (uint32_t*)mem, cap, slot_bytes / 4, (uint32_t)ks);
-    fill_zero((uint64_t*)v.side, 32, ctx->compute);
+    fl.zero(v.present, bits_bytes + 256);
+  } else {   // the empty marker: word 0 of a 4-byte key, word 1 of an 8-byte one (little-endian)
+    fl.pattern(mem, slots_bytes, slot_bytes / 4, ks == 4 ? 0x80000000u : 0u, ks == 4 ? 0u : 0x80000000u);
+    fl.zero(v.side, 256);
   }
+  if (!fills) (void)own.launch(ctx->compute);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     ctx->arena.release(mem);
@@ -844,7 +905,7 @@ static unsigned grid_for(vx_ctx* ctx, uint64_t work_items, uint64_t per_block, u
 vx_status key_range(vx_ctx* ctx, int32_t key_type, const void* dev_keys, uint64_t n, KeyRange* out) {
   *out = KeyRange{};
   if (n == 0) return VX_OK;
-  unsigned long long* mm = (unsigned long long*)ctx->dev_acc;   // free between executor steps
+  unsigned long long* mm = (unsigned long long*)ctx->host_acc_dev;   // free between executor steps
   const unsigned g = grid_for(ctx, n, 256 * 16, 2);
   VX_CHECK(3ull * g <= ctx->dev_acc_words, VX_EINVAL, "key range: %u workgroups exceed the scratch", g);
   if (key_type == VX_I64)
@@ -852,8 +913,7 @@ vx_status key_range(vx_ctx* ctx, int32_t key_type, const void* dev_keys, uint64_
   else
     hipLaunchKernelGGL(k_key_range<int32_t>, dim3(g), dim3(256), 0, ctx->compute, (const int32_t*)dev_keys, n, mm);
   VX_HIP(hipGetLastError());
-  const unsigned long long* h = (const unsigned long long*)ctx->host_acc;   // pinned: a direct copy
-  VX_HIP(hipMemcpyAsync(ctx->host_acc, mm, 3 * (uint64_t)g * 8, hipMemcpyDeviceToHost, ctx->compute));
+  const unsigned long long* h = (const unsigned long long*)ctx->host_acc;
   VX_HIP(hipStreamSynchronize(ctx->compute));
   unsigned long long mn = ~0ull, mx = 0, empties = 0;
   for (unsigned b = 0; b < g; ++b) {
@@ -871,7 +931,7 @@ vx_status key_range(vx_ctx* ctx, int32_t key_type, const void* dev_keys, uint64_
 }
 
 vx_status table_insert(vx_ctx* ctx, vx_table* t, const ColInfo& key, const ColInfo* pays,
-                       uint64_t n, hipStream_t s, int group_lanes) {
+                       uint64_t n, hipStream_t s, int group_lanes, bool cleared, bool count) {
   if (n == 0) return VX_OK;
   BuildCols c{};
   c.key = key.dev;
@@ -886,27 +946,30 @@ vx_status table_insert(vx_ctx* ctx, vx_table* t, const ColInfo& key, const ColIn
     else hipLaunchKernelGGL(k_build_preagg<int32_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
   } else if (t->view.direct == kLayoutDense) {
     VX_CHECK(t->n_rows == 0, VX_EINVAL, "build: a dense table takes its rows in one insert");
-    unsigned long long* cnt = (unsigned long long*)ctx->dev_acc;
-    fill_zero((uint64_t*)cnt, 2, s);
+    unsigned long long* cnt = (unsigned long long*)((uint8_t*)ctx->dev_flags + kFlagCount);
+    if (!cleared) fill_zero((uint64_t*)cnt, 2, s);
     const unsigned g = grid_for(ctx, n, 256, 8);
     const unsigned gc = grid_for(ctx, t->view.direct_range, 256 * 16, 2);
     if (k64) hipLaunchKernelGGL(k_build_dense<int64_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
     else hipLaunchKernelGGL(k_build_dense<int32_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
-    hipLaunchKernelGGL(k_dense_count, dim3(gc), dim3(256), 0, s, (const uint8_t*)t->view.present, t->view.direct_range,
+    if (count)
+      hipLaunchKernelGGL(k_dense_count, dim3(gc), dim3(256), 0, s, (const uint8_t*)t->view.present, t->view.direct_range,
                        cnt, n, ctx->dev_flags);
   } else if (t->view.direct) {
     // one insert per direct table: the duplicate check counts every slot against every row
     VX_CHECK(t->n_rows == 0, VX_EINVAL, "build: a direct table takes its rows in one insert");
-    unsigned long long* cnt = (unsigned long long*)ctx->dev_acc;
-    fill_zero((uint64_t*)cnt, 2, s);
+    unsigned long long* cnt = (unsigned long long*)((uint8_t*)ctx->dev_flags + kFlagCount);
+    if (!cleared) fill_zero((uint64_t*)cnt, 2, s);
     const unsigned g = grid_for(ctx, n, 256, 8);
     const unsigned gc = grid_for(ctx, t->view.direct_range, 256 * 16, 2);
     if (k64) {
       hipLaunchKernelGGL(k_build_direct<int64_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
-      hipLaunchKernelGGL(k_direct_count<int64_t>, dim3(gc), dim3(256), 0, s, t->view, cnt, n, ctx->dev_flags);
+      if (count)
+        hipLaunchKernelGGL(k_direct_count<int64_t>, dim3(gc), dim3(256), 0, s, t->view, cnt, n, ctx->dev_flags);
     } else {
       hipLaunchKernelGGL(k_build_direct<int32_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
-      hipLaunchKernelGGL(k_direct_count<int32_t>, dim3(gc), dim3(256), 0, s, t->view, cnt, n, ctx->dev_flags);
+      if (count)
+        hipLaunchKernelGGL(k_direct_count<int32_t>, dim3(gc), dim3(256), 0, s, t->view, cnt, n, ctx->dev_flags);
     }
   } else {
     unsigned g = grid_for(ctx, n, 256, 8);
@@ -942,57 +1005,59 @@ static int dense_items() {
 
 template <typename K, int LAYOUT, bool COUNT>
 static void launch_probe_count(const vx_table* t, const ProbeCols& q, unsigned long long* acc, hipStream_t s,
-                               unsigned g) {
+                               unsigned g, const ProbeFinish& f) {
   constexpr int ITEMS = 4;
   if constexpr (LAYOUT == kLayoutDense) {   // dense tables hold unique keys
     switch (dense_items()) {
       case 16:
-        hipLaunchKernelGGL((k_probe<K, false, 16, LAYOUT, COUNT>), dim3(g), dim3(256), 0, s, t->view, q, acc);
+        hipLaunchKernelGGL((k_probe<K, false, 16, LAYOUT, COUNT>), dim3(g), dim3(256), 0, s, t->view, q, acc, f);
         break;
       case 4:
-        hipLaunchKernelGGL((k_probe<K, false, 4, LAYOUT, COUNT>), dim3(g), dim3(256), 0, s, t->view, q, acc);
+        hipLaunchKernelGGL((k_probe<K, false, 4, LAYOUT, COUNT>), dim3(g), dim3(256), 0, s, t->view, q, acc, f);
         break;
       default:
-        hipLaunchKernelGGL((k_probe<K, false, 8, LAYOUT, COUNT>), dim3(g), dim3(256), 0, s, t->view, q, acc);
+        hipLaunchKernelGGL((k_probe<K, false, 8, LAYOUT, COUNT>), dim3(g), dim3(256), 0, s, t->view, q, acc, f);
         break;
     }
   }
   else if (t->view.preagg)
-    hipLaunchKernelGGL((k_probe<K, true, ITEMS, LAYOUT, COUNT>), dim3(g), dim3(256), 0, s, t->view, q, acc);
+    hipLaunchKernelGGL((k_probe<K, true, ITEMS, LAYOUT, COUNT>), dim3(g), dim3(256), 0, s, t->view, q, acc, f);
   else
-    hipLaunchKernelGGL((k_probe<K, false, ITEMS, LAYOUT, COUNT>), dim3(g), dim3(256), 0, s, t->view, q, acc);
+    hipLaunchKernelGGL((k_probe<K, false, ITEMS, LAYOUT, COUNT>), dim3(g), dim3(256), 0, s, t->view, q, acc, f);
 }
 
 template <typename K, int LAYOUT>
 static void launch_probe_as(const vx_table* t, const ProbeCols& q, unsigned long long* acc, hipStream_t s,
-                            const RowsOut* ro, unsigned g) {
+                            const RowsOut* ro, unsigned g, const ProbeFinish& f) {
   if (ro)
     hipLaunchKernelGGL((k_probe_rows<K, 4, LAYOUT>), dim3(g), dim3(256), 0, s, t->view, q, acc, *ro);
   else if (q.zc_count)
-    launch_probe_count<K, LAYOUT, true>(t, q, acc, s, g);
+    launch_probe_count<K, LAYOUT, true>(t, q, acc, s, g, f);
   else
-    launch_probe_count<K, LAYOUT, false>(t, q, acc, s, g);
+    launch_probe_count<K, LAYOUT, false>(t, q, acc, s, g, f);
 }
 
 static vx_status launch_probe(vx_ctx* ctx, const vx_table* t, const ProbeCols& q,
-                              unsigned long long* acc, hipStream_t s, const RowsOut* ro = nullptr) {
+                              unsigned long long* acc, hipStream_t s, const RowsOut* ro, const ProbeFinish& f) {
   if (q.n == 0) return VX_OK;
   const unsigned g = grid_for(ctx, q.n, 256 * 4, 8);
   const bool k64 = t->key_type == VX_I64;
   switch (t->view.direct) {
     case kLayoutDense:
-      if (k64) launch_probe_as<int64_t, kLayoutDense>(t, q, acc, s, ro, g);
-      else launch_probe_as<int32_t, kLayoutDense>(t, q, acc, s, ro, g);
+      if (k64) launch_probe_as<int64_t, kLayoutDense>(t, q, acc, s, ro, g, f);
+      else launch_probe_as<int32_t, kLayoutDense>(t, q, acc, s, ro, g, f);
       break;
     case kLayoutDirect:
-      if (k64) launch_probe_as<int64_t, kLayoutDirect>(t, q, acc, s, ro, g);
-      else launch_probe_as<int32_t, kLayoutDirect>(t, q, acc, s, ro, g);
+      if (k64) launch_probe_as<int64_t, kLayoutDirect>(t, q, acc, s, ro, g, f);
+      else launch_probe_as<int32_t, kLayoutDirect>(t, q, acc, s, ro, g, f);
       break;
     default:
-      if (k64) launch_probe_as<int64_t, kLayoutHash>(t, q, acc, s, ro, g);
-      else launch_probe_as<int32_t, kLayoutHash>(t, q, acc, s, ro, g);
+      if (k64) launch_probe_as<int64_t, kLayoutHash>(t, q, acc, s, ro, g, f);
+      else launch_probe_as<int32_t, kLayoutHash>(t, q, acc, s, ro, g, f);
       break;
   }
+  if (f.publish && t->view.direct != kLayoutDense)
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, acc, t->view.side, f.flags, f.host);
   VX_HIP(hipGetLastError());
   return VX_OK;
 }
@@ -1014,10 +1079,15 @@ static bool choose_zero_copy(int32_t late_mat, double sel, uint64_t rows, uint64
   return wire < 0.95 * es;
 }
 
-// check_build: the table's build left its error flags unread (build_impl's defer_check); they
-// are read back with the results and turned into the build's error.
+// What a one-shot join's build left to its probe.
+struct Deferred {
+  bool flags = false;         // the build's error flags are unread: read with the results
+  bool count = false;         // the duplicate check of a direct or dense table is not made: the probe makes it
+  bool acc_cleared = false;   // the accumulators and tickets of a publishing launch are zero
+};
+
 vx_status probe_impl(vx_ctx* ctx, const vx_table* t, const vx_probe_desc* d, vx_agg* out,
-                     vx_stats* st, vx_join_rows* rows, bool check_build = false) {
+                     vx_stats* st, vx_join_rows* rows, const Deferred& build = Deferred()) {
   double t0 = now_ms();
   VX_CHECK(d->key.type == t->key_type, VX_EINVAL, "probe: key type %d differs from the table's %d",
            d->key.type, t->key_type);
@@ -1052,7 +1122,11 @@ vx_status probe_impl(vx_ctx* ctx, const vx_table* t, const vx_probe_desc* d, vx_
     VX_CHECK(n_chunks <= d->chunk_aggs_cap && n_chunks <= acc_rows_cap, VX_ECAPACITY,
              "probe: %llu chunks exceed chunk_aggs_cap %llu", (unsigned long long)n_chunks,
              (unsigned long long)d->chunk_aggs_cap);
-  fill_zero((uint64_t*)ctx->dev_acc, acc_rows * kAccWords, ctx->compute);
+  // a single chunk of device memory: the probe's last workgroup hands the results to the host
+  const bool publish = n_chunks == 1 && !pipe.streamed() && !rows;
+  static_assert(kAccWords < kAccStride, "a row's ticket follows its accumulators");
+  if (!publish || !build.acc_cleared)
+    fill_zero((uint64_t*)ctx->dev_acc, publish ? kAccPublishBytes / 8 : acc_rows * kAccWords, ctx->compute);
 
   // output rows (vx_probe_rows): device-visible addresses of the caller's columns and a counter
   RowsOut ro{};
@@ -1111,8 +1185,15 @@ vx_status probe_impl(vx_ctx* ctx, const vx_table* t, const vx_probe_desc* d, vx_
       }
     }
     q.zc_shift = zc_shift;
+    ProbeFinish f{};
+    f.count = build.count && v.index == 0;
+    if (publish) {
+      f.publish = 1;
+      f.host = (unsigned long long*)ctx->host_acc_dev;
+      f.flags = ctx->dev_flags;
+    }
     return launch_probe(ctx, t, q, (unsigned long long*)ctx->dev_acc + (v.index % acc_rows) * kAccWords,
-                        ctx->compute, rows ? &ro : nullptr);
+                        ctx->compute, rows ? &ro : nullptr, f);
   };
   Pipeline::DecideFn decide = nullptr;
   bool any_host_pay = false;
@@ -1133,16 +1214,29 @@ vx_status probe_impl(vx_ctx* ctx, const vx_table* t, const vx_probe_desc* d, vx_
   double tk0 = now_ms();
   vx_status status = pipe.run(kernel, decide);
   if (status != VX_OK) return status;   // the pipeline's destructor drains both streams
-  VX_HIP(hipMemcpyAsync(ctx->host_acc, ctx->dev_acc, acc_rows * kAccWords * 8, hipMemcpyDeviceToHost,
-                        ctx->compute));
-  if (rows) VX_HIP(hipMemcpyAsync(&rows->n_out, ro.count, 8, hipMemcpyDeviceToHost, ctx->compute));
-  if (check_build)
-    VX_HIP(hipMemcpyAsync(ctx->host_small, ctx->dev_flags, 4, hipMemcpyDeviceToHost, ctx->compute));
+  if (!publish) {
+    VX_HIP(hipMemcpyAsync(ctx->host_acc, ctx->dev_acc, acc_rows * kAccWords * 8, hipMemcpyDeviceToHost, ctx->compute));
+    if (rows) VX_HIP(hipMemcpyAsync(&rows->n_out, ro.count, 8, hipMemcpyDeviceToHost, ctx->compute));
+    if (build.flags) {
+      VX_HIP(hipMemcpyAsync(ctx->host_small, ctx->dev_flags, 4, hipMemcpyDeviceToHost, ctx->compute));
+      VX_HIP(hipMemcpyAsync(ctx->host_small + 1, t->view.side, 8, hipMemcpyDeviceToHost, ctx->compute));
+    }
+  }
   VX_HIP(hipStreamSynchronize(ctx->compute));
-  unsigned int build_flags = 0;
-  if (check_build) std::memcpy(&build_flags, ctx->host_small, 4);
-  VX_CHECK(!(build_flags & kFlagDup), VX_EDUPKEY, "vx_join_agg: duplicate key in a build declared unique");
-  VX_CHECK(!(build_flags & kFlagFull), VX_ECAPACITY, "vx_join_agg: hash table full (internal sizing error)");
+  if (build.flags) {
+    uint64_t build_flags = publish ? ctx->host_acc[kAccWords + 1] : 0, side = publish ? ctx->host_acc[kAccWords] : 0;
+    if (!publish) {
+      std::memcpy(&build_flags, ctx->host_small, 4);
+      side = ctx->host_small[1];
+    }
+    if (build.count) {   // fewer filled slots than rows: two rows shared a key
+      uint64_t filled = t->view.direct == kLayoutDirect ? side : 0;
+      for (uint64_t r = 0; r < acc_rows; ++r) filled += ctx->host_acc[r * kAccWords + kGranuleWord];
+      if (filled != t->n_rows) build_flags |= kFlagDup;
+    }
+    VX_CHECK(!(build_flags & kFlagDup), VX_EDUPKEY, "vx_join_agg: duplicate key in a build declared unique");
+    VX_CHECK(!(build_flags & kFlagFull), VX_ECAPACITY, "vx_join_agg: hash table full (internal sizing error)");
+  }
   double tk1 = now_ms();
   std::vector<unsigned long long> total(kAccWords, 0);
   for (uint64_t r = 0; r < acc_rows; ++r)
@@ -1190,9 +1284,10 @@ vx_status probe_impl(vx_ctx* ctx, const vx_table* t, const vx_probe_desc* d, vx_
   return VX_OK;
 }
 
-// defer_check: leave the build's error flags for the caller to read with its own results (one
-// host round trip less); the table is returned even if they will show a repeated key.
-vx_status build_impl(vx_ctx* ctx, const vx_build_desc* d, vx_table** out, double* ms, bool defer_check) {
+// defer (one-shot joins): leave the build's error flags for the probe to read with its own results
+// (one host round trip less), and with `fold` the duplicate check of a direct or dense table for it
+// to make beside its own work; the table is returned even if they will show a repeated key.
+vx_status build_impl(vx_ctx* ctx, const vx_build_desc* d, vx_table** out, double* ms, Deferred* defer, bool fold) {
   double t0 = now_ms();
   VX_CHECK(d != nullptr && out != nullptr, VX_EINVAL, "vx_build: null argument");
   *out = nullptr;
@@ -1217,10 +1312,15 @@ vx_status build_impl(vx_ctx* ctx, const vx_build_desc* d, vx_table** out, double
     VX_TRY(key_range(ctx, d->key.type, kc.dev, d->n, &kr));
   kr.allow_dense = kind == VX_UNIQUE;
   vx_table* t = nullptr;
-  VX_TRY(make_table(ctx, d->key.type, kind, pt, d->n_pay, d->n, d->load_factor, &t, &kr));
-  fill_zero((uint64_t*)ctx->dev_flags, 1, ctx->compute);
-  vx_status st = table_insert(ctx, t, kc, pc, d->n, ctx->compute, build_group_lanes());
-  if (st == VX_OK && !defer_check) st = check_flags(ctx, "vx_build");
+  FillList fills;
+  VX_TRY(make_table(ctx, d->key.type, kind, pt, d->n_pay, d->n, d->load_factor, &t, &kr, &fills));
+  fills.zero(ctx->dev_flags, kFlagBytes);
+  if (defer) fills.zero(ctx->dev_acc, kAccPublishBytes);   // the probe's accumulators and tickets
+  vx_status st = fills.launch(ctx->compute);
+  fold &= defer && d->n && !t->view.preagg && t->view.direct != kLayoutHash;
+  if (st == VX_OK) st = table_insert(ctx, t, kc, pc, d->n, ctx->compute, build_group_lanes(), true, !fold);
+  if (defer) *defer = Deferred{true, fold, true};
+  if (st == VX_OK && !defer) st = check_flags(ctx, "vx_build");
   if (st != VX_OK) {
     ctx->arena.release(t->mem);
     delete t;
@@ -1245,7 +1345,7 @@ extern "C" {
 vx_status vx_build(vx_ctx* ctx, const vx_build_desc* d, vx_table** out) {
   VX_CHECK(ctx != nullptr, VX_EINVAL, "vx_build: ctx is NULL");
   release_cached(ctx);
-  return build_impl(ctx, d, out, nullptr, false);
+  return build_impl(ctx, d, out, nullptr, nullptr, false);
 }
 
 vx_status vx_table_destroy(vx_table* t) {
@@ -1281,9 +1381,12 @@ vx_status vx_join_agg(vx_ctx* ctx, const vx_join_desc* d, vx_join_out* out) {
     case VX_JOIN_PLAIN: {
       double t0 = now_ms(), bms = 0;
       vx_table* t = nullptr;
-      // the build's flags are read with the probe's results: one host round trip for both
-      VX_TRY(build_impl(ctx, &d->u.plain.build, &t, &bms, true));
-      vx_status st = probe_impl(ctx, t, &d->u.plain.probe, &out->agg, &out->stats, nullptr, true);
+      // the build's flags are read with the probe's results: one host round trip for both.  A probe
+      // that counts zero-copy granules needs the accumulator word of the duplicate check.
+      const vx_probe_desc& pd = d->u.plain.probe;
+      Deferred defer;
+      VX_TRY(build_impl(ctx, &d->u.plain.build, &t, &bms, &defer, pd.n != 0 && !(pd.flags & VX_PROBE_COUNT_ZC)));
+      vx_status st = probe_impl(ctx, t, &pd, &out->agg, &out->stats, nullptr, defer);
       vx_table_destroy(t);
       out->stats.build_ms = bms;
       out->stats.total_ms = now_ms() - t0;
@@ -1362,12 +1465,9 @@ static unsigned grid_cu(int cu, uint64_t work_items, uint64_t per_block, unsigne
 }
 
 template <typename K>
-static void noalloc_launch(const TableView& v, uint64_t cap, uint32_t slot_bytes, const BuildCols& bc, uint64_t nb,
+static void noalloc_launch(const TableView& v, const BuildCols& bc, uint64_t nb,
                            const ProbeCols& q, int cu, unsigned long long* out, hipStream_t s) {
   unsigned int* flags = (unsigned int*)(out + 9);
-  const uint64_t quads = cap * slot_bytes / 16;
-  hipLaunchKernelGGL(k_init_slots, dim3(grid_cu(cu, quads, 256, 32)), dim3(256), 0, s, (uint32_t*)v.slots, cap,
-                     slot_bytes / 4, (uint32_t)sizeof(K));
   if (nb) {
     if (v.preagg)
       hipLaunchKernelGGL(k_build_preagg<K>, dim3(grid_cu(cu, nb, kPreaggTile, 3)), dim3(256), 0, s, v, bc, nb, flags);
@@ -1377,9 +1477,9 @@ static void noalloc_launch(const TableView& v, uint64_t cap, uint32_t slot_bytes
   }
   if (q.n) {
     if (v.preagg)
-      hipLaunchKernelGGL((k_probe<K, true, 4, kLayoutHash, false>), dim3(grid_cu(cu, q.n, 1024, 8)), dim3(256), 0, s, v, q, out);
+      hipLaunchKernelGGL((k_probe<K, true, 4, kLayoutHash, false>), dim3(grid_cu(cu, q.n, 1024, 8)), dim3(256), 0, s, v, q, out, ProbeFinish{});
     else
-      hipLaunchKernelGGL((k_probe<K, false, 4, kLayoutHash, false>), dim3(grid_cu(cu, q.n, 1024, 8)), dim3(256), 0, s, v, q, out);
+      hipLaunchKernelGGL((k_probe<K, false, 4, kLayoutHash, false>), dim3(grid_cu(cu, q.n, 1024, 8)), dim3(256), 0, s, v, q, out, ProbeFinish{});
   }
 }
 
@@ -1441,11 +1541,15 @@ extern "C" vx_status vx_join_plain_noalloc(const vx_build_desc* b, const vx_prob
   v.side = (unsigned long long*)nd->ptr;
   v.slots = nd->ptr + kNaSlotsOff;
   const hipStream_t s = (hipStream_t)stream;
-  // the aggregate row, the error word and the side record start at zero (fill kernels, no memset)
+  // the aggregate row, the error word and the side record start at zero (fill kernels, no memset),
+  // and the slots empty.  The caller's row is 8-byte aligned at least, so it has a fill of its own.
   fill_zero(out, 10, s);
-  fill_zero((uint64_t*)nd->ptr, kNaSlotsOff / 8, s);
-  if (ks == 8) noalloc_launch<int64_t>(v, cap, slot_bytes, bc, b->n, q, nd->cu_count, (unsigned long long*)out, s);
-  else noalloc_launch<int32_t>(v, cap, slot_bytes, bc, b->n, q, nd->cu_count, (unsigned long long*)out, s);
+  FillList fills;
+  fills.zero(nd->ptr, kNaSlotsOff);
+  fills.pattern(v.slots, cap * slot_bytes, slot_bytes / 4, ks == 4 ? 0x80000000u : 0u, ks == 4 ? 0u : 0x80000000u);
+  VX_TRY(fills.launch(s));
+  if (ks == 8) noalloc_launch<int64_t>(v, bc, b->n, q, nd->cu_count, (unsigned long long*)out, s);
+  else noalloc_launch<int32_t>(v, bc, b->n, q, nd->cu_count, (unsigned long long*)out, s);
   VX_HIP(hipGetLastError());
   return VX_OK;
 }

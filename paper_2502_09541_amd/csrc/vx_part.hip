@@ -483,7 +483,7 @@ static vx_status partition_impl(vx_ctx* ctx, const vx_partition_desc* d, vx_part
 
   // the counts land in host_acc (mapped), where the host reads them after the stream is drained
   const unsigned long long* h = (const unsigned long long*)ctx->host_acc;
-  unsigned long long* h_dev = (unsigned long long*)(ctx->host_small_dev - ctx->dev_acc_words);
+  unsigned long long* h_dev = (unsigned long long*)ctx->host_acc_dev;
   for (uint32_t p = 0; p < P; ++p) ctx->host_acc[p] = 0;
   // Pass A counts every chunk; pass B scatters it from the running position of each partition.  A
   // single chunk needs no second look at its rows: its counts give the positions at once.

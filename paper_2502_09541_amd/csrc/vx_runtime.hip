@@ -191,6 +191,36 @@ void fill_zero(uint64_t* p, uint64_t words, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)blocks), dim3(256), 0, s, p, words);
 }
 
+__global__ void __launch_bounds__(256) k_fill(FillList l) {
+  const uint64_t first = blockIdx.x * 256ull + threadIdx.x, step = gridDim.x * 256ull;
+  for (uint32_t j = 0; j < l.n; ++j) {
+    const FillList::Job b = l.job[j];
+    for (uint64_t q = first; q < b.quads; q += step) {
+      uint32_t v[4];
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i) {
+        const uint32_t at = (uint32_t)(4 * q + i) & (b.period - 1);
+        v[i] = at == 0 ? b.v0 : at == 1 ? b.v1 : 0u;
+      }
+      ((uint4*)b.p)[q] = make_uint4(v[0], v[1], v[2], v[3]);
+    }
+  }
+}
+
+void FillList::pattern(void* p, uint64_t bytes, uint32_t period, uint32_t v0, uint32_t v1) {
+  job[n++] = Job{p, bytes / 16, period, v0, v1, 0};   // callers stay below kMax
+}
+
+vx_status FillList::launch(hipStream_t s) {
+  uint64_t most = 0;
+  for (uint32_t j = 0; j < n; ++j) most = std::max(most, job[j].quads);
+  if (most)
+    hipLaunchKernelGGL(k_fill, dim3((unsigned)std::min<uint64_t>((most + 255) / 256, 8192)), dim3(256), 0, s, *this);
+  n = 0;
+  VX_HIP(hipGetLastError());
+  return VX_OK;
+}
+
 vx_status check_stall(vx_ctx* ctx, const char* what) {
   volatile uint32_t* w = (volatile uint32_t*)(ctx->host_small + kHostSmallWords - 1);
   const bool stalled = *w != 0;
@@ -243,7 +273,7 @@ vx_status vx_ctx_create(int device, void* arena, uint64_t arena_bytes, void* str
     c->l2_bytes = (uint64_t)pr.l2CacheSize;
   }
   c->dev_acc_words = kAccRows * kAccWords;
-  const uint64_t scratch_bytes = c->dev_acc_words * 8 + 256;
+  const uint64_t scratch_bytes = c->dev_acc_words * 8 + kFlagBytes;
   uint8_t* scratch = c->arena.alloc(scratch_bytes);
   if (!scratch) {
     delete c;
@@ -284,7 +314,8 @@ vx_status vx_ctx_create(int device, void* arena, uint64_t arena_bytes, void* str
     set_error("vx_ctx_create: pinned scratch has no device mapping");
     return VX_EHIP;
   }
-  c->host_small_dev = (uint64_t*)mapped + c->dev_acc_words;
+  c->host_acc_dev = (uint64_t*)mapped;
+  c->host_small_dev = c->host_acc_dev + c->dev_acc_words;
   *out = c;
   return VX_OK;
 }

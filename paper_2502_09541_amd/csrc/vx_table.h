@@ -87,12 +87,16 @@ struct KeyRange {
 // Launch helpers implemented in vx_join.hip and used by the other executors.
 // make_table lays the table out directly (slot = key - min) when `kr` holds a measured range no
 // wider than the hash table's capacity, so the direct table is never the larger of the two.
+// With `fills` the table's initial contents are added to the list, for the caller to launch.
 vx_status make_table(vx_ctx* ctx, int32_t key_type, uint32_t flags, const int32_t* pay_types,
                      uint32_t n_pay, uint64_t expected_rows, float load_factor, vx_table** out,
-                     const KeyRange* kr = nullptr);
-// Measure the range of n device-resident keys (one pass over them, then a 16-byte read back).
+                     const KeyRange* kr = nullptr, FillList* fills = nullptr);
+// Measure the range of n device-resident keys: one pass over them, whose workgroups store their
+// results to host_acc.
 vx_status key_range(vx_ctx* ctx, int32_t key_type, const void* dev_keys, uint64_t n, KeyRange* out);
+// cleared: the duplicate check's counters (kFlagCount) are zero already.  count: false leaves out the
+// duplicate check of a direct or dense table, which the caller makes itself.
 vx_status table_insert(vx_ctx* ctx, vx_table* t, const ColInfo& key, const ColInfo* pays,
-                       uint64_t n, hipStream_t s, int group_lanes);
+                       uint64_t n, hipStream_t s, int group_lanes, bool cleared = false, bool count = true);
 vx_status check_flags(vx_ctx* ctx, const char* what);
 }  // namespace vx
