@@ -879,6 +879,10 @@ vx_status check_flags(vx_ctx* ctx, const char* what) {
   VX_HIP(hipMemcpyAsync(ctx->host_small, ctx->dev_flags, sizeof f, hipMemcpyDeviceToHost, ctx->compute));
   VX_HIP(hipStreamSynchronize(ctx->compute));
   std::memcpy(&f, ctx->host_small, sizeof f);
+  return flags_status(f, what);
+}
+
+vx_status flags_status(unsigned int f, const char* what) {
   if (f & kFlagDup) {
     set_error("%s: duplicate key in a build declared unique", what);
     return VX_EDUPKEY;
@@ -902,21 +906,30 @@ static unsigned grid_for(vx_ctx* ctx, uint64_t work_items, uint64_t per_block, u
   return (unsigned)blocks;
 }
 
-vx_status key_range(vx_ctx* ctx, int32_t key_type, const void* dev_keys, uint64_t n, KeyRange* out) {
-  *out = KeyRange{};
+static unsigned key_range_groups(const vx_ctx* ctx, uint64_t n) {
+  return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>((n + 4095) / 4096, (uint64_t)ctx->cu_count * 2));
+}
+
+vx_status key_range_launch(vx_ctx* ctx, int32_t key_type, const void* dev_keys, uint64_t n, uint32_t slot) {
   if (n == 0) return VX_OK;
-  unsigned long long* mm = (unsigned long long*)ctx->host_acc_dev;   // free between executor steps
-  const unsigned g = grid_for(ctx, n, 256 * 16, 2);
-  VX_CHECK(3ull * g <= ctx->dev_acc_words, VX_EINVAL, "key range: %u workgroups exceed the scratch", g);
+  const unsigned g = key_range_groups(ctx, n);
+  const uint64_t per = ctx->dev_acc_words / 4;   // host_acc is free between executor steps
+  VX_CHECK(3ull * g <= per, VX_EINVAL, "key range: %u workgroups exceed the scratch", g);
+  unsigned long long* mm = (unsigned long long*)ctx->host_acc_dev + slot * per;
   if (key_type == VX_I64)
     hipLaunchKernelGGL(k_key_range<int64_t>, dim3(g), dim3(256), 0, ctx->compute, (const int64_t*)dev_keys, n, mm);
   else
     hipLaunchKernelGGL(k_key_range<int32_t>, dim3(g), dim3(256), 0, ctx->compute, (const int32_t*)dev_keys, n, mm);
   VX_HIP(hipGetLastError());
-  const unsigned long long* h = (const unsigned long long*)ctx->host_acc;
-  VX_HIP(hipStreamSynchronize(ctx->compute));
+  return VX_OK;
+}
+
+void key_range_collect(const vx_ctx* ctx, uint64_t n, uint32_t slot, KeyRange* out) {
+  *out = KeyRange{};
+  if (n == 0) return;
+  const unsigned long long* h = (const unsigned long long*)ctx->host_acc + slot * (ctx->dev_acc_words / 4);
   unsigned long long mn = ~0ull, mx = 0, empties = 0;
-  for (unsigned b = 0; b < g; ++b) {
+  for (unsigned b = 0; b < key_range_groups(ctx, n); ++b) {
     mn = std::min(mn, h[3 * b]);
     mx = std::max(mx, h[3 * b + 1]);
     empties += h[3 * b + 2];
@@ -927,6 +940,14 @@ vx_status key_range(vx_ctx* ctx, int32_t key_type, const void* dev_keys, uint64_
     out->min_ord = mn;
     out->max_ord = mx;
   }
+}
+
+vx_status key_range(vx_ctx* ctx, int32_t key_type, const void* dev_keys, uint64_t n, KeyRange* out) {
+  *out = KeyRange{};
+  if (n == 0) return VX_OK;
+  VX_TRY(key_range_launch(ctx, key_type, dev_keys, n, 0));
+  VX_HIP(hipStreamSynchronize(ctx->compute));
+  key_range_collect(ctx, n, 0, out);
   return VX_OK;
 }
 

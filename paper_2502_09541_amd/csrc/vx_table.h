@@ -94,9 +94,14 @@ vx_status make_table(vx_ctx* ctx, int32_t key_type, uint32_t flags, const int32_
 // Measure the range of n device-resident keys: one pass over them, whose workgroups store their
 // results to host_acc.
 vx_status key_range(vx_ctx* ctx, int32_t key_type, const void* dev_keys, uint64_t n, KeyRange* out);
+// The same in two steps, for several columns (slot 0 .. 3) before one wait: launch, drain the compute
+// stream, then collect.
+vx_status key_range_launch(vx_ctx* ctx, int32_t key_type, const void* dev_keys, uint64_t n, uint32_t slot);
+void key_range_collect(const vx_ctx* ctx, uint64_t n, uint32_t slot, KeyRange* out);
 // cleared: the duplicate check's counters (kFlagCount) are zero already.  count: false leaves out the
 // duplicate check of a direct or dense table, which the caller makes itself.
 vx_status table_insert(vx_ctx* ctx, vx_table* t, const ColInfo& key, const ColInfo* pays,
                        uint64_t n, hipStream_t s, int group_lanes, bool cleared = false, bool count = true);
 vx_status check_flags(vx_ctx* ctx, const char* what);
+vx_status flags_status(unsigned int flags, const char* what);   // the error that the kernels' flags stand for
 }  // namespace vx

@@ -152,6 +152,45 @@ def test_star_sentinel_keys_and_negative_groups(gpu, ctx):
     assert (-1, -1) in [tuple(r) for r in exp[0].tolist()]
 
 
+@pytest.mark.parametrize("key_dtype", [np.int32, np.int64])
+@pytest.mark.parametrize("tight", [False, True])
+@pytest.mark.parametrize("dup", [None, 0, 1, 2])
+def test_star_dimension_builds(gpu, tight, dup, key_dtype):
+    """Hashed (spread keys) and direct (narrow range, not a multiple of 4, one with the empty marker)
+    dimensions together, with room for all of their tables at once, and with room for the tables but not
+    for a check beside them; a repeated key is refused also where the filter drops its rows."""
+    rng = np.random.default_rng(17)
+    i32 = np.iinfo(np.int32)
+    # 2^18 slots each: 2 MiB + 2 MiB and 2 MiB for the check with 4-byte keys, 2 + 4 and 2 with 8-byte
+    # ones, beside 1.25 MiB that a context takes from its budget for scratch
+    budget = (6 << 20 if key_dtype == np.int32 else 8 << 20) if tight else 1 << 30
+    spread = [np.unique(rng.integers(i32.min + 1, i32.max, 100_100))[:100_000] for _ in range(2)]
+    keys = [spread[0], spread[1], np.append(np.arange(1000, 3503), np.iinfo(key_dtype).min)]
+    dims = []
+    for k, key in enumerate(keys):
+        key = rng.permutation(key).astype(key_dtype)
+        filt = rng.integers(0, 4, len(key)).astype(np.int32)
+        dims.append(dict(key=key, filt=filt, lo=0, hi=2, group=rng.integers(-2, 5, len(key)).astype(np.int32) if k else None))
+    fks = [rng.choice(np.append(d["key"], 5).astype(key_dtype), 5000) for d in dims]
+    meas = [rng.integers(-2**31, 2**31, 5000).astype(np.int32)]
+    exp = oracle.star_groupby(dims, fks, meas)
+    if dup is not None:
+        key, filt = dims[dup]["key"], dims[dup]["filt"]
+        key[7], filt[3], filt[7] = key[3], 3, 3
+    c = gpu.Context(budget)
+    try:
+        _say("star: dimension builds", budget, dup, key_dtype.__name__)
+        args = _dev_dims(dims), [dev(f) for f in fks], [dev(m) for m in meas]
+        if dup is None:
+            _check(c.join_star(*args), exp)
+        else:
+            with pytest.raises(gpu.VxError) as ei:
+                c.join_star(*args)
+            assert ei.value.status == gpu.VX_EDUPKEY
+    finally:
+        c.close()
+
+
 def test_star_full_size_dense_closed_form(gpu):
     """Full size: 600,000,000 fact rows (16.8 GB pinned), dimensions of 2,556 / 200,000 /
     3,000,000 / 2,000,000 rows.  Expected groups from direct-array lookups (dense dimension keys),
