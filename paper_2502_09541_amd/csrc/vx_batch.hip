@@ -14,12 +14,9 @@
 //
 // A job whose build keys fill their value range exactly (n unique keys from min to min + n - 1,
 // found by a min/max pass over every job before the graph runs) gets a direct table instead of
-// a hash table: the payload of key k sits at k - min, and a presence byte per key of the range
-// catches a duplicate (which would leave a key of the range missing).  The build sets the bytes
-// with plain stores (distinct keys never share a byte, so no atomic is needed); a small kernel
-// between the two phases counts each job's set bytes, and the host compares the count with the
-// job's rows.  A probe key outside the range then costs no memory access, and one inside reads
-// one payload.
+// a hash table: the payload of key k sits at k - min.  A probe key outside the range then costs no
+// memory access, and one inside reads one payload.  A duplicate leaves a key of the range missing: a
+// small kernel counts each job's distinct keys, and the host compares the count with the job's rows.
 //
 // Random table reads are what bounds the probe: served by the L2 they reach about half of its
 // request rate, and a table larger than one L2 is read from the MALL or HBM.  So the probe phase
@@ -30,9 +27,16 @@
 // region, a per-job scan turns the tallies into positions, and a scatter pass moves the keys.  A
 // probe work item (one 1024-thread workgroup per compute unit, its LDS) then stages its region
 // and streams its share of the region's keys, about a million.
-// Count, scan and scatter run on a second stream, the build phase beside the scatter.  Keys that
+// Count, scan and scatter run on a second stream, the build phase beside them.  Keys that
 // cannot match are dropped: outside the range of a direct table, or outside the smallest and
 // largest build key of a hash table (measured with the ranges, on every call).
+//
+// A direct table probed by staged regions is never written to memory: its build rows are clustered by
+// region (16-bit offset in the region, payload), or read where they are when there is one region, and a
+// probe work item fills its region in LDS from them; the probe keys are partitioned as 16-bit offsets.
+// Only jobs left to the tile map, or whose regions outgrow the stage, store payload and presence byte of
+// every key at random addresses.  64 jobs, 9,700,000 build and 378,000,000 probe keys: 1.38 -> 0.94 ms a
+// call; the random stores took 396 us, clustering takes 45, and the region probe 175 instead of 390.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -76,6 +80,11 @@ struct BatchJob {
   uint64_t cbase;           // the job's tallies: entry cbase + super-tile * n_parts + region
   uint8_t* pbuf;            // partitioned keys: the regions' arrays, in region order, then the sink slots
   unsigned long long* kept; // keys kept by the partitioning (written by the scan)
+  // build side by regions (direct tables with staged regions of at most kRowWindow keys): no table in
+  // memory; dpay holds the payloads region by region, region p's rows from p << part_shift on
+  uint32_t rows;            // 1: a probe work item builds its region in LDS from the region's build rows
+  uint16_t* boff;           // not in place: the clustered rows' keys, as offsets in their region
+  uint32_t* cursor;         // not in place: rows of region p that k_batch_build brought
 };
 
 constexpr uint32_t kMaxBatchJobs = 4096;
@@ -260,7 +269,8 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 constexpr uint32_t kPartThreads = 256, kPartItems = 16, kPartRows = kPartThreads * kPartItems;
-constexpr uint32_t kScatterItems = 16;               // keys per lane in a scatter round
+constexpr uint32_t kClusterThreads = 1024;
+constexpr uint32_t kRowWindow = 1 << 15;             // keys per region built in LDS (their offsets fit 16 bits)
 constexpr uint32_t kSuperTiles = 16;                 // partition tiles per super-tile (65536 rows)
 constexpr uint32_t kMaxTableParts = 1024;
 constexpr uint32_t kScanBlock = 1024;
@@ -288,6 +298,11 @@ struct RegionFn {
     }
     if (ko < kmin || ko > kmax) return parts;
     return (uint32_t)(slot_of(key_bits(k), log2cap) >> shift);
+  }
+  // of a direct table's key, within its region
+  template <typename K>
+  __device__ __forceinline__ uint16_t offset(K k) const {
+    return (uint16_t)((uint32_t)(key_ord(k) - kmin) & ((1u << shift) - 1u));
   }
 };
 
@@ -428,51 +443,59 @@ __global__ void __launch_bounds__(kScanBlock) k_batch_scan(const BatchJob* __res
   }
 }
 
-// Rows r0 .. r0 + T kScatterItems of a job's probe keys, kScatterItems per thread of T (rows past the
+// Rows r0 .. r0 + T ITEMS of a job's probe keys, ITEMS per thread of T (rows past the
 // end reread the last row), and their regions (`parts` for a key that cannot match or a row past
 // the end).
-template <typename K, uint32_t T>
-__device__ __forceinline__ void load_rows(const void* pkey, uint64_t np, uint64_t r0, K (&k)[kScatterItems]) {
-  const uint32_t last = (uint32_t)(np - r0 < T * kScatterItems ? np - r0 : T * kScatterItems) - 1;
+template <typename K, uint32_t T, uint32_t ITEMS>
+__device__ __forceinline__ void load_rows(const void* pkey, uint64_t np, uint64_t r0, K (&k)[ITEMS]) {
+  const uint32_t last = (uint32_t)(np - r0 < T * ITEMS ? np - r0 : T * ITEMS) - 1;
 #pragma unroll
-  for (uint32_t it = 0; it < kScatterItems; ++it) {
+  for (uint32_t it = 0; it < ITEMS; ++it) {
     const uint32_t row = it * T + threadIdx.x;
     k[it] = gload_nt<K>(pkey, r0 + (row < last ? row : last));
   }
 }
 
-template <typename K, uint32_t T>
-__device__ __forceinline__ void rows_regions(const RegionFn& region, uint64_t np, uint64_t r0, const K (&k)[kScatterItems],
-                                             uint32_t (&r)[kScatterItems]) {
-  const uint32_t n = (uint32_t)(np - r0 < T * kScatterItems ? np - r0 : T * kScatterItems);
+template <typename K, uint32_t T, uint32_t ITEMS>
+__device__ __forceinline__ void rows_regions(const RegionFn& region, uint64_t np, uint64_t r0, const K (&k)[ITEMS],
+                                             uint32_t (&r)[ITEMS]) {
+  const uint32_t n = (uint32_t)(np - r0 < T * ITEMS ? np - r0 : T * ITEMS);
 #pragma unroll
-  for (uint32_t it = 0; it < kScatterItems; ++it) {
+  for (uint32_t it = 0; it < ITEMS; ++it) {
     const uint32_t row = it * T + threadIdx.x;
     r[it] = row < n ? region(k[it]) : region.parts;
   }
 }
 
-// Workgroup size of the scatter: one round sorts T kScatterItems keys in LDS (16384 int32 or 8192
-// int64 keys), so that a region's run per round is a line or two on the bench's batch.
+// Workgroup size, keys per lane and workgroups per compute unit of the scatter: a round sorts 8192 keys
+// in LDS, so that a region's run per round is a line or two.  Two workgroups of 1024 fit a compute unit
+// for 4-byte keys (64 registers a lane, 48 KiB of LDS each): one then works while the other waits at a
+// barrier.  378,000,000 int32 keys of 64 jobs, half of them kept: 467 us, against 535 with two
+// workgroups of 512 and 614 with one of 1024 and rounds of 16384.
 template <typename K>
 constexpr uint32_t scatter_threads() { return sizeof(K) == 4 ? 1024 : 512; }
+template <typename K>
+constexpr uint32_t scatter_items() { return sizeof(K) == 4 ? 8 : 16; }
+template <typename K>
+constexpr uint32_t scatter_groups() { return sizeof(K) == 4 ? 2 : 1; }
 
 // Scatter pass: each kept key of super-tile st to its region's array, at the super-tile's
-// position for the region plus its rank.  The super-tile goes in rounds of T kScatterItems keys; each
+// position for the region plus its rank.  The super-tile goes in rounds of T ITEMS keys; each
 // round is first sorted by region in LDS (the rank of a key among the round's keys of its region
 // comes from an LDS counter), then written out in runs, so that neighbouring lanes store
 // neighbouring keys; the order within a region is arbitrary and the aggregates do not depend on
-// it.  Every thread issues kScatterItems stores per round (slots past the round's kept keys go to
+// it.  Every thread issues ITEMS stores per round (slots past the round's kept keys go to
 // sink slots past the partitioned keys), and the next round's loads are issued before them, so
 // that waiting for those loads never waits for the stores.  A round takes three barriers: after
 // the ranks, after the scan (which also advances the positions for the next round and clears
 // the counts), and after the sort; a sorted key's region is recomputed from the key when it is
-// stored.
-template <typename K, uint32_t T>
-__global__ void __launch_bounds__(T) k_batch_scatter(const BatchJob* __restrict__ jobs,
+// stored.  Of a job whose regions are built from rows only the key's offset in its region is kept, in
+// 16 bits: the scatter writes, and the probe reads, a half or a quarter of the bytes.
+template <typename K, uint32_t T, uint32_t ITEMS, uint32_t GROUPS>
+__global__ void __launch_bounds__(T, GROUPS * T / 256) k_batch_scatter(const BatchJob* __restrict__ jobs,
                                                      const unsigned long long* __restrict__ part_map,
                                                      uint64_t n_super, const uint32_t* __restrict__ pos) {
-  constexpr uint32_t R = T * kScatterItems;
+  constexpr uint32_t R = T * ITEMS;
   constexpr uint64_t kSuperRows = (uint64_t)kPartRows * kSuperTiles;
   // per region: next = where the region's next key goes, cnt = the round's keys, off = the
   // round's first sorted slot, delta = next - off (sorted key i of the region goes to delta + i,
@@ -489,6 +512,7 @@ __global__ void __launch_bounds__(T) k_batch_scatter(const BatchJob* __restrict_
     const uint32_t P = region.parts;
     const void* pkey = jb.pkey;
     void* const dst = jb.pbuf;
+    const bool narrow = jb.rows != 0;
     // slots past a round's kept keys store to this workgroup's own 64 sink slots, so that no
     // line is written by many workgroups at once
     const uint64_t np = jb.np, s0 = st * kSuperRows, s1 = s0 + kSuperRows < np ? s0 + kSuperRows : np;
@@ -499,19 +523,19 @@ __global__ void __launch_bounds__(T) k_batch_scatter(const BatchJob* __restrict_
       next[j] = j < P ? pos[jb.cbase + st * P + j] : 0u;
       cnt[j] = 0;
     }
-    K k[kScatterItems], kn[kScatterItems];
-    load_rows<K, T>(pkey, np, s0, kn);
+    K k[ITEMS], kn[ITEMS];
+    load_rows<K, T, ITEMS>(pkey, np, s0, kn);
     lds_barrier();
     for (uint64_t r0 = s0; r0 < s1; r0 += R) {
 #pragma unroll
-      for (uint32_t it = 0; it < kScatterItems; ++it) k[it] = kn[it];
+      for (uint32_t it = 0; it < ITEMS; ++it) k[it] = kn[it];
       // per key: region << 16 | rank among the round's keys of its region (no rank for a key that
       // cannot match: see the count).  cnt was cleared by the previous round's scan; the stores
       // of the previous round, which may still be going on in other waves, do not read it.
-      uint32_t rr[kScatterItems];
-      rows_regions<K, T>(region, np, r0, k, rr);
+      uint32_t rr[ITEMS];
+      rows_regions<K, T, ITEMS>(region, np, r0, k, rr);
 #pragma unroll
-      for (uint32_t it = 0; it < kScatterItems; ++it)
+      for (uint32_t it = 0; it < ITEMS; ++it)
         rr[it] = rr[it] < P ? rr[it] << 16 | atomicAdd(&cnt[rr[it]], 1u) : P << 16;
       lds_barrier();   // the ranks are taken, and every store of the previous round has read its LDS
       if (threadIdx.x < 64) {   // exclusive scan of cnt[0 .. P) into off; off[P] = the round's kept keys
@@ -539,20 +563,111 @@ __global__ void __launch_bounds__(T) k_batch_scatter(const BatchJob* __restrict_
       }
       lds_barrier();
 #pragma unroll
-      for (uint32_t it = 0; it < kScatterItems; ++it) {
+      for (uint32_t it = 0; it < ITEMS; ++it) {
         const uint32_t r = rr[it] >> 16;
         if (r < P) stage[off[r] + (rr[it] & 0xffffu)] = k[it];
       }
-      if (r0 + R < s1) load_rows<K, T>(pkey, np, r0 + R, kn);
+      if (r0 + R < s1) load_rows<K, T, ITEMS>(pkey, np, r0 + R, kn);
       lds_barrier();
       const uint32_t total = off[P];
 #pragma unroll
-      for (uint32_t it = 0; it < kScatterItems; ++it) {
+      for (uint32_t it = 0; it < ITEMS; ++it) {
         const uint32_t i = it * T + threadIdx.x;
         const K v = stage[i];
         const uint32_t at = i < total ? delta[region(v)] + i : sink;   // a kept key's region is below P
-        gstore_at<K>(dst, at * (uint32_t)sizeof(K), v);
+        if (narrow) gstore_at<uint16_t>(dst, at * 2u, region.offset(v));
+        else gstore_at<K>(dst, at * (uint32_t)sizeof(K), v);
       }
+    }
+  }
+}
+
+// Build side by regions: tile t of a job's build rows (cluster_map[g] = job << 32 | t), each row to the
+// next place of its region, whose rows number exactly its width when no key repeats: no count pass is
+// needed, a tile takes its places with one atomic per region.  The tile is sorted by region in LDS first,
+// so that neighbouring lanes store neighbouring rows: written unsorted, into a table or into regions, the
+// rows cost a memory request or two each (9,700,000 rows of 64 jobs took 396 us so).  Rows past a
+// region's width (a key repeats) are dropped; the probe finds the region's keys incomplete.
+template <typename P>
+constexpr uint32_t cluster_items() { return sizeof(P) == 4 ? 8 : 4; }   // 64 KiB or less: two workgroups per unit
+
+template <typename K, typename P>
+__device__ __forceinline__ void cluster_tiles(const BatchJob* __restrict__ jobs,
+                                              const unsigned long long* __restrict__ cluster_map, uint64_t n_tiles) {
+  constexpr uint32_t ITEMS = cluster_items<P>(), ROWS = kClusterThreads * ITEMS;
+  __shared__ uint32_t cnt[kMaxTableParts], off[kMaxTableParts], base[kMaxTableParts];
+  __shared__ uint32_t wtot[kClusterThreads / 64];
+  __shared__ uint32_t skey[ROWS];
+  __shared__ P spay[ROWS];
+  static_assert(kMaxTableParts <= kClusterThreads, "a thread per region");
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (uint64_t g = blockIdx.x; g < n_tiles; g += gridDim.x) {
+    const unsigned long long e = uniform_entry(cluster_map, g);
+    const BatchJob& jb = jobs[e >> 32];
+    const uint64_t r0 = (e & 0xffffffffull) * ROWS;
+    const uint32_t n = (uint32_t)(jb.nb - r0 < ROWS ? jb.nb - r0 : ROWS);
+    const uint32_t shift = jb.part_shift;
+    const uint64_t nb = jb.nb;
+    const void *bkey = jb.bkey, *bpay = jb.bpay;
+    const unsigned long long kmin = jb.kmin_ord;
+    cnt[threadIdx.x] = 0;
+    K k[ITEMS];
+    P v[ITEMS];
+#pragma unroll
+    for (uint32_t it = 0; it < ITEMS; ++it) {
+      const uint32_t row = it * kClusterThreads + threadIdx.x;
+      k[it] = gload_nt<K>(bkey, r0 + (row < n ? row : n - 1));
+      v[it] = gload_nt<P>(bpay, r0 + (row < n ? row : n - 1));
+    }
+    __syncthreads();   // the previous tile's stores have read their LDS too
+    uint32_t idx[ITEMS], rank[ITEMS];
+#pragma unroll
+    for (uint32_t it = 0; it < ITEMS; ++it) {
+      const uint32_t row = it * kClusterThreads + threadIdx.x;
+      const uint64_t i = key_ord(k[it]) - kmin;   // below nb: the range was measured over these keys
+      idx[it] = row < n && i < nb ? (uint32_t)i : ~0u;
+      rank[it] = 0;
+      if (idx[it] != ~0u) rank[it] = atomicAdd(&cnt[idx[it] >> shift], 1u);
+    }
+    __syncthreads();
+    const uint32_t c = cnt[threadIdx.x];
+    uint32_t incl = c;
+#pragma unroll
+    for (uint32_t o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += y;
+    }
+    if (lane == 63) wtot[wave] = incl;
+    uint32_t at = 0;
+    if (c) at = atomicAdd(jb.cursor + threadIdx.x, c);   // c is 0 past the last region
+    __syncthreads();
+    uint32_t first = 0, total = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kClusterThreads / 64; ++w) {
+      first += w < wave ? wtot[w] : 0u;
+      total += wtot[w];
+    }
+    off[threadIdx.x] = first + incl - c;
+    base[threadIdx.x] = at;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t it = 0; it < ITEMS; ++it)
+      if (idx[it] != ~0u) {
+        const uint32_t p = off[idx[it] >> shift] + rank[it];
+        skey[p] = idx[it];
+        spay[p] = v[it];
+      }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t it = 0; it < ITEMS; ++it) {
+      const uint32_t i = it * kClusterThreads + threadIdx.x;
+      if (i >= total) continue;
+      const uint32_t x = skey[i], p = x >> shift;
+      const uint64_t lo = (uint64_t)p << shift, width = nb - lo < (1ull << shift) ? nb - lo : 1ull << shift;
+      const uint32_t q = base[p] + i - off[p];
+      if (q >= width) continue;
+      gstore<uint16_t>(jb.boff, lo + q, (uint16_t)(x & ((1u << shift) - 1u)));
+      gstore<P>(jb.dpay, lo + q, spay[i]);
     }
   }
 }
@@ -610,9 +725,63 @@ __device__ __forceinline__ void probe_staged(const BatchJob& jb, K k, uint32_t p
   }
 }
 
+// The payloads of a region's build rows, at the offsets of their keys.
+template <typename K, typename P>
+__device__ __forceinline__ void stage_rows(const BatchJob& jb, uint64_t first, uint32_t width, uint32_t rows, uint8_t* stage) {
+  constexpr uint32_t U = 8;   // rows in flight per lane
+  for (uint32_t r = threadIdx.x; r < rows; r += kRegionThreads * U) {
+    uint32_t o[U];
+    P v[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint64_t i = r + u * kRegionThreads < rows ? r + u * kRegionThreads : r;
+      if (jb.in_place) {
+        const uint64_t x = key_ord(gload<K>(jb.bkey, i)) - jb.kmin_ord;
+        o[u] = x < width ? (uint32_t)x : ~0u;   // always: the range was measured over these keys
+        v[u] = gload<P>(jb.bpay, i);
+      } else {
+        o[u] = gload<uint16_t>(jb.boff, first + i);
+        v[u] = gload<P>(jb.dpay, first + i);
+      }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u)
+      if (r + u * kRegionThreads < rows && o[u] < width) ((P*)stage)[o[u]] = v[u];
+  }
+}
+
+// The sum of the payloads at the 16-bit offsets [q0, q1) of `keys` (256-byte aligned), eight to a load.
+template <typename P>
+__device__ __forceinline__ unsigned long long sum_offsets(const uint8_t* keys, uint64_t q0, uint64_t q1, const uint8_t* stage) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  constexpr uint32_t U = 4;   // loads in flight per lane
+  unsigned long long sum = 0;
+  auto add = [&](uint32_t o) { sum += (unsigned long long)(long long)((const P*)stage)[o]; };
+  const uint64_t a0 = (q0 + 7) / 8 * 8 < q1 ? (q0 + 7) / 8 * 8 : q1, a1 = q1 / 8 * 8 > a0 ? q1 / 8 * 8 : a0;
+  if (threadIdx.x < a0 - q0) add(gload<uint16_t>(keys, q0 + threadIdx.x));   // fewer than 8 each
+  if (threadIdx.x < q1 - a1) add(gload<uint16_t>(keys, a1 + threadIdx.x));
+  const uint64_t v1 = a1 / 8;
+  for (uint64_t v = a0 / 8 + threadIdx.x; v < v1; v += kRegionThreads * U) {
+    u32x4 x[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u)
+      x[u] = gload_nt<u32x4>(keys, v + u * kRegionThreads < v1 ? v + u * kRegionThreads : v);
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u)
+      if (v + u * kRegionThreads < v1) {
+#pragma unroll
+        for (uint32_t w = 0; w < 4; ++w) {
+          add(x[u][w] & 0xffffu);
+          add(x[u][w] >> 16);
+        }
+      }
+  }
+  return sum;
+}
+
 // Region probe (region_map[t] = job << 44 | region << 32 | item, ~0 for none): item `item` of
 // region p takes an even share of the region's keys; with its region staged in LDS when the job's
-// regions fit kStageBytes.
+// regions fit kStageBytes, from the table in memory or from the region's build rows.
 template <typename K>
 __global__ void __launch_bounds__(kRegionThreads) k_batch_region(const BatchJob* __restrict__ jobs,
                                                                  const unsigned long long* __restrict__ region_map,
@@ -642,10 +811,29 @@ __global__ void __launch_bounds__(kRegionThreads) k_batch_region(const BatchJob*
       const uint64_t entries = jb.direct ? jb.nb : jb.mask + 1;
       const uint64_t first = (uint64_t)p << jb.part_shift;
       const uint64_t count = (first + (1ull << jb.part_shift) < entries ? (1ull << jb.part_shift) : entries - first);
-      const uint8_t* src = (jb.direct ? jb.dpay : jb.slots) + first * entry;
-      const uint32_t words = (uint32_t)(count * entry / 4);
-      for (uint32_t w = threadIdx.x; w < words; w += blockDim.x) ((uint32_t*)stage)[w] = gload<uint32_t>(src, w);
-      __syncthreads();
+      if (jb.rows) {
+        const uint32_t width = (uint32_t)count;
+        uint32_t rows = width;
+        if (!jb.in_place) {
+          const uint32_t c = gload<uint32_t>(jb.cursor, p);
+          rows = c < width ? c : width;
+        }
+        if (jb.pay_size == 4) stage_rows<K, int>(jb, first, width, rows, stage);
+        else if (jb.pay_size == 8) stage_rows<K, long long>(jb, first, width, rows, stage);
+        __syncthreads();
+        if (!jb.in_place) {
+          if (threadIdx.x == 0) cnt = q1 - q0;   // every kept key lies in the region
+          sum = jb.pay_size == 4 ? sum_offsets<int>(jb.pbuf, q0, q1, stage)
+                                 : sum_offsets<long long>(jb.pbuf, q0, q1, stage);
+          block_add2(cnt, sum, acc + 2 * lo);
+          continue;
+        }
+      } else {
+        const uint8_t* src = (jb.direct ? jb.dpay : jb.slots) + first * entry;
+        const uint32_t words = (uint32_t)(count * entry / 4);
+        for (uint32_t w = threadIdx.x; w < words; w += blockDim.x) ((uint32_t*)stage)[w] = gload<uint32_t>(src, w);
+        __syncthreads();
+      }
       for (uint64_t q = q0 + threadIdx.x; q < q1; q += (uint64_t)blockDim.x * kRunUnroll) {
         K k[kRunUnroll];
 #pragma unroll
@@ -697,31 +885,72 @@ __global__ void __launch_bounds__(512) k_batch_phase(const BatchJob* jobs, uint3
   }
 }
 
-// Presence bytes set in the direct-table jobs' tables, per job, into cnt[j] (tile order).  Count
-// tile t belongs to the job whose first count tile is the largest one <= t; each covers
-// kCountWords 8-byte words.  A byte is 0 or 1, so a word's popcount is its set bytes.
+// The build phase where some jobs are built by regions: their rows' tiles, then the tiles of the tables
+// in memory as in k_batch_phase.
+template <typename K, typename P>
+__global__ void __launch_bounds__(kClusterThreads, 8) k_batch_build(const BatchJob* __restrict__ jobs,
+                                                                    const unsigned long long* __restrict__ cluster_map,
+                                                                    uint64_t n_cluster,
+                                                                    const unsigned long long* __restrict__ tile_map,
+                                                                    uint64_t n_tiles, uint32_t tile_rows,
+                                                                    uint32_t slot_shift, unsigned int* flags) {
+  cluster_tiles<K, P>(jobs, cluster_map, n_cluster);
+  for (uint64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+    const unsigned long long e = uniform_entry(tile_map, t);
+    if (e == ~0ull) continue;
+    const BatchJob& jb = jobs[e >> 32];
+    const uint64_t r0 = (e & 0xffffffffull) * tile_rows, r1 = r0 + tile_rows < jb.nb ? r0 + tile_rows : jb.nb;
+    batch_build_rows<K>(jb, r0, r1, slot_shift, flags);
+  }
+}
+
+// Distinct keys of the direct-table jobs, per job, into cnt[j] (tile order).  Count tile t belongs to
+// the job whose first count tile is the largest one <= t.  A table in memory: each tile covers
+// kCountWords 8-byte words of presence bytes, 0 or 1, so a word's popcount is its set bytes.  A job
+// built by regions: tile p sets the bits of region p's rows in LDS.  It runs beside the region probe, in
+// the threads and the LDS that the probe leaves: beside the scatter, whose workgroups fill the compute
+// units, those that it kept out started 120 us late.
 constexpr uint32_t kCountWords = 4096;
 
-__global__ void __launch_bounds__(256) k_batch_dupcount(const BatchJob* jobs, uint32_t n_jobs, uint64_t tiles,
+template <typename K>
+__global__ void __launch_bounds__(256) k_batch_dupcount(const BatchJob* __restrict__ jobs, uint32_t n_jobs, uint64_t tiles,
                                                         unsigned long long* cnt) {
-  __shared__ unsigned long long t0[kMaxBatchJobs];
   __shared__ unsigned long long part[4];
-  for (uint32_t j = threadIdx.x; j < n_jobs; j += blockDim.x) t0[j] = jobs[j].ctile0;
-  __syncthreads();
+  __shared__ uint32_t bits[kRowWindow / 32];
   for (uint64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
     uint32_t lo = 0, hi = n_jobs;
     while (hi - lo > 1) {
       const uint32_t mid = (lo + hi) >> 1;
-      if (t0[mid] <= t) lo = mid;
+      if (jobs[mid].ctile0 <= t) lo = mid;
       else hi = mid;
     }
     const BatchJob& jb = jobs[lo];
-    const uint64_t words = (jb.nb + 7) / 8;   // the bytes past nb up to the 256-byte alignment are 0
-    const uint64_t w0 = (t - jb.ctile0) * kCountWords;
-    const uint64_t w1 = w0 + kCountWords < words ? w0 + kCountWords : words;
     unsigned long long c = 0;
-    for (uint64_t w = w0 + threadIdx.x; w < w1; w += blockDim.x)
-      c += (unsigned long long)__popcll(((const unsigned long long*)jb.slots)[w]);
+    if (jb.rows) {   // uniform
+      const uint32_t p = (uint32_t)(t - jb.ctile0);
+      const uint64_t first = (uint64_t)p << jb.part_shift, left = jb.nb - first;
+      const uint32_t width = (uint32_t)(left < (1ull << jb.part_shift) ? left : 1ull << jb.part_shift);
+      uint32_t rows = width;
+      if (!jb.in_place) {
+        const uint32_t got = gload<uint32_t>(jb.cursor, p);
+        rows = got < width ? got : width;
+      }
+      for (uint32_t w = threadIdx.x; w < kRowWindow / 32; w += 256) bits[w] = 0;
+      __syncthreads();
+#pragma unroll 8
+      for (uint32_t i = threadIdx.x; i < rows; i += 256) {
+        const uint64_t x = jb.in_place ? key_ord(gload<K>(jb.bkey, i)) - jb.kmin_ord : gload<uint16_t>(jb.boff, first + i);
+        if (x < width) atomicOr(bits + (x >> 5), 1u << (x & 31));
+      }
+      __syncthreads();
+      for (uint32_t w = threadIdx.x; w < kRowWindow / 32; w += 256) c += (unsigned long long)__popc(bits[w]);
+    } else {
+      const uint64_t words = (jb.nb + 7) / 8;   // the bytes past nb up to the 256-byte alignment are 0
+      const uint64_t w0 = (t - jb.ctile0) * kCountWords;
+      const uint64_t w1 = w0 + kCountWords < words ? w0 + kCountWords : words;
+      for (uint64_t w = w0 + threadIdx.x; w < w1; w += blockDim.x)
+        c += (unsigned long long)__popcll(((const unsigned long long*)jb.slots)[w]);
+    }
     for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
@@ -729,7 +958,7 @@ __global__ void __launch_bounds__(256) k_batch_dupcount(const BatchJob* jobs, ui
       for (int w = 1; w < (int)(blockDim.x >> 6); ++w) c += part[w];
       if (c) atomicAdd(cnt + lo, c);
     }
-    __syncthreads();   // part is reused by the next tile
+    __syncthreads();   // part and bits are reused by the next tile
   }
 }
 
@@ -877,7 +1106,7 @@ struct BatchPlan {
   // runs on XCD x.  A job's build and probe tiles go to the same XCD.
   std::vector<unsigned long long> build_map, probe_map;
   uint64_t direct_bytes = 0;       // presence bytes and payloads of the direct-table jobs (after them)
-  uint32_t slot_shift = 3;
+  uint32_t slot_shift = 3, pay_size = 0;
   // probe by regions: the region kernel's work items (kXcds interleaved lists, like the tile
   // maps), the partitioning passes' super-tiles (job << 32 | super-tile), and the bytes of the
   // partitioned keys, tallies and kept totals (a block of their own)
@@ -885,6 +1114,11 @@ struct BatchPlan {
   uint64_t part_bytes = 0;
   uint64_t pkey_bytes = 0, tally_entries = 0;
   uint32_t part_jobs = 0, region_jobs = 0;
+  // build side by regions: the build's tiles of rows to cluster (job << 32 | tile), its cursors (in the partition
+  // block), and whether any direct job still has a table in memory
+  std::vector<unsigned long long> cluster_map;
+  uint64_t cursor_entries = 0;
+  bool tables = false;
 };
 
 // Which jobs get a direct table: per caller's job, direct[j] and the smallest key kmin[j]
@@ -973,7 +1207,7 @@ static void map_tiles(BatchPlan* pl, uint32_t slot_bytes, uint64_t l2_bytes) {
     const bool local = table_bytes_of(b, slot_bytes) <= l2_bytes / 4 * 3;
     if (b.n_parts) {
       for (uint32_t p = 0; p < b.n_parts; ++p) regions.push_back({i, p, b.items_per_region});
-      if (!local)
+      if (!local && !b.rows)
         for (uint32_t k = 0; k < b.build_tiles; ++k) bl[rb++ % kXcds].push_back(((unsigned long long)i << 32) | k);
       continue;
     }
@@ -1002,7 +1236,7 @@ static void map_tiles(BatchPlan* pl, uint32_t slot_bytes, uint64_t l2_bytes) {
   for (const Unit& u : regions) {
     const uint32_t x = least(rl);
     const BatchJob& b = pl->jobs[u.job];
-    if (u.region == 0 && table_bytes_of(b, slot_bytes) <= l2_bytes / 4 * 3)
+    if (u.region == 0 && !b.rows && table_bytes_of(b, slot_bytes) <= l2_bytes / 4 * 3)
       for (uint32_t k = 0; k < b.build_tiles; ++k) bl[x].push_back(((unsigned long long)u.job << 32) | k);
     for (uint64_t k = 0; k < u.entries; ++k)
       rl[x].push_back(((unsigned long long)u.job << 44) | ((unsigned long long)u.region << 32) | k);
@@ -1027,10 +1261,13 @@ static void map_tiles(BatchPlan* pl, uint32_t slot_bytes, uint64_t l2_bytes) {
 // relative to the partition block until setup_run relocates them.
 static void plan_regions(BatchPlan* pl, int ks, uint32_t slot_bytes, uint64_t part_budget, uint64_t stage) {
   pl->part_map.clear();
-  pl->part_bytes = pl->pkey_bytes = pl->tally_entries = 0;
+  pl->cluster_map.clear();
+  pl->part_bytes = pl->pkey_bytes = pl->tally_entries = pl->cursor_entries = 0;
   pl->part_jobs = pl->region_jobs = 0;
   const uint32_t J = (uint32_t)pl->jobs.size();
   const uint64_t item_keys = 1 << 20;   // probe keys per work item (its region is staged once per item)
+  const uint64_t row_item_keys = 1 << 18;
+  const uint64_t cluster_rows = kClusterThreads * (pl->pay_size == 8 ? cluster_items<long long>() : cluster_items<int>());
   for (uint32_t i = 0; i < J; ++i) {
     BatchJob& b = pl->jobs[i];
     const uint64_t table = table_bytes_of(b, slot_bytes);
@@ -1044,11 +1281,14 @@ static void plan_regions(BatchPlan* pl, int ks, uint32_t slot_bytes, uint64_t pa
       else
         sh = b.log2cap;
       b.part_shift = sh;
-      b.items_per_region = (uint32_t)std::max<uint64_t>(1, (b.np + item_keys - 1) / item_keys);
+      b.rows = b.direct && b.nb <= kRowWindow;
+      const uint64_t share = b.rows ? row_item_keys / 2 : item_keys;
+      b.items_per_region = (uint32_t)std::max<uint64_t>(1, (b.np + share - 1) / share);
       ++pl->region_jobs;
       continue;
     }
-    // the scatter addresses a job's partitioned keys (and sink slots) by 32-bit byte offsets
+    // the scatter addresses a job's partitioned keys (and sink slots) by 32-bit byte offsets, those of a
+    // job built by regions as 16-bit offsets in their region
     if (b.np == 0 || (b.np + 64ull * kSinkGroups) * (uint64_t)ks >= (1ull << 32)) continue;
     uint32_t parts, shift;
     bool staged;
@@ -1068,32 +1308,43 @@ static void plan_regions(BatchPlan* pl, int ks, uint32_t slot_bytes, uint64_t pa
     }
     const uint64_t ptiles = (b.np + kPartRows - 1) / kPartRows;
     const uint64_t stiles = (ptiles + kSuperTiles - 1) / kSuperTiles;
-    const uint64_t keys = align256((b.np + 64ull * kSinkGroups) * (uint64_t)ks), tallies = stiles * parts;   // + the sink slots
-    const uint64_t need = keys + tallies * 4 + 256 + 8;
+    const bool rows = b.direct && staged && (1ull << shift) <= kRowWindow;
+    const uint64_t es = rows ? 2 : (uint64_t)ks;
+    const uint64_t keys = align256((b.np + 64ull * kSinkGroups) * es), tallies = stiles * parts;   // + the sink slots
+    const uint64_t offs = rows ? align256(2 * b.nb) : 0, cursors = rows ? parts : 0;
+    const uint64_t need = keys + offs + (tallies + cursors) * 4 + 256 + 8;
     if (pl->part_bytes + need > part_budget) continue;
     b.n_parts = parts;
     b.part_shift = shift;
     b.staged = staged;
     b.ptiles = (uint32_t)ptiles;
     b.stiles = (uint32_t)stiles;
-    b.items_per_region = (uint32_t)std::max<uint64_t>(1, (b.np / parts + item_keys - 1) / item_keys);
+    const uint64_t share = rows ? row_item_keys : item_keys;
+    b.items_per_region = (uint32_t)std::max<uint64_t>(1, (b.np / parts + share - 1) / share);
+    b.rows = rows;
     b.pbuf = (uint8_t*)(uintptr_t)pl->pkey_bytes;
+    b.boff = (uint16_t*)(uintptr_t)(pl->pkey_bytes + keys);
+    b.cursor = (uint32_t*)(uintptr_t)(4 * pl->cursor_entries);
+    for (uint64_t t = 0; rows && t * cluster_rows < b.nb; ++t) pl->cluster_map.push_back(((unsigned long long)i << 32) | t);
     b.cbase = pl->tally_entries;
     b.kept = (unsigned long long*)(uintptr_t)(8ull * pl->part_jobs);   // index into the kept totals
-    pl->pkey_bytes += keys;
+    pl->pkey_bytes += keys + offs;
+    pl->cursor_entries += cursors;
     pl->tally_entries += tallies;
     pl->part_bytes += need;
     ++pl->part_jobs;
     ++pl->region_jobs;
     for (uint64_t t = 0; t < stiles; ++t) pl->part_map.push_back(((unsigned long long)i << 32) | t);
   }
-  pl->part_bytes = pl->pkey_bytes + align256(pl->tally_entries * 4) + align256(8ull * pl->part_jobs);
+  pl->part_bytes = pl->pkey_bytes + align256(pl->tally_entries * 4) + align256(8ull * pl->part_jobs) +
+                   align256(pl->cursor_entries * 4);
 }
 
 static vx_status plan_batch(const vx_batch_join* d, const BatchConfig& cfg, int ks, uint32_t ps,
                             const DirectInfo& di, uint64_t l2_bytes, bool regions, uint64_t part_budget,
                             uint64_t stage, BatchPlan* pl) {
   const uint32_t J = d->n_jobs;
+  pl->pay_size = ps;
   pl->jobs.resize(J);
   pl->job_of.resize(J);
   for (uint32_t j = 0; j < J; ++j) pl->job_of[j] = j;
@@ -1104,7 +1355,7 @@ static vx_status plan_batch(const vx_batch_join* d, const BatchConfig& cfg, int 
   if (ks == 8 && ps) slot_bytes = 16;
   pl->slot_shift = 0;
   while ((1u << pl->slot_shift) < slot_bytes) ++pl->slot_shift;
-  uint64_t bt = 0, pt = 0, ct = 0, slots = 0, dbytes = 0;
+  uint64_t bt = 0, pt = 0, slots = 0, dbytes = 0;
   for (uint32_t i = 0; i < J; ++i) {
     const uint32_t j = pl->job_of[i];
     BatchJob& b = pl->jobs[i];
@@ -1132,21 +1383,26 @@ static vx_status plan_batch(const vx_batch_join* d, const BatchConfig& cfg, int 
       b.slots = (uint8_t*)(uintptr_t)slots;
       slots += cap;
     }
-    b.ctile0 = ct;
     b.build_tiles = (uint32_t)((b.nb + cfg.tile_rows - 1) / cfg.tile_rows);
     b.probe_tiles = (uint32_t)((b.np + cfg.tile_rows - 1) / cfg.tile_rows);
-    b.count_tiles = b.direct ? (uint32_t)(((b.nb + 7) / 8 + kCountWords - 1) / kCountWords) : 0;
     bt += b.build_tiles;
     pt += b.probe_tiles;
-    ct += b.count_tiles;
   }
   pl->build_tiles = bt;
   pl->probe_tiles = pt;
-  pl->count_tiles = ct;
   pl->total_tiles = bt + pt;
   pl->slots = slots;
   pl->direct_bytes = dbytes;
   if (regions) plan_regions(pl, ks, slot_bytes, part_budget, stage);
+  pl->count_tiles = 0;
+  pl->tables = false;
+  for (BatchJob& b : pl->jobs) {
+    const bool table = b.direct && !b.rows;
+    b.ctile0 = pl->count_tiles;
+    b.count_tiles = table ? (uint32_t)(((b.nb + 7) / 8 + kCountWords - 1) / kCountWords) : b.rows ? b.n_parts : 0;
+    pl->count_tiles += b.count_tiles;
+    pl->tables |= table;
+  }
   map_tiles(pl, slot_bytes, l2_bytes);
   return VX_OK;
 }
@@ -1162,6 +1418,8 @@ struct BatchRun {
   unsigned long long* build_map = nullptr;
   unsigned long long* region_map = nullptr;  // the region probe's work items
   unsigned long long* part_map = nullptr;    // the partitioning passes' super-tiles
+  unsigned long long* cluster_map = nullptr; // the build rows' tiles
+  uint32_t* cursors = nullptr;
   uint32_t* tally = nullptr;                 // per partitioned job and super-tile: keys per region, then positions
   uint8_t* slots = nullptr;
   uint64_t counter_words = 0;
@@ -1185,7 +1443,8 @@ static uint64_t stage_bytes() {
 static uint64_t run_bytes(const BatchPlan& pl, uint32_t J, uint64_t counter_words) {
   return align256(pl.slots << pl.slot_shift) + align256(pl.direct_bytes) + align256((uint64_t)J * sizeof(BatchJob)) +
          align256(counter_words * 8) + align256(pl.probe_map.size() * 8) + align256(pl.build_map.size() * 8) +
-         align256(pl.region_map.size() * 8) + align256(pl.part_map.size() * 8) + pl.part_bytes;
+         align256(pl.region_map.size() * 8) + align256(pl.part_map.size() * 8) +
+         align256(pl.cluster_map.size() * 8) + pl.part_bytes;
 }
 
 static vx_status setup_run(vx_ctx* ctx, const vx_batch_join* d, const BatchConfig& cfg, int ks,
@@ -1210,6 +1469,7 @@ static vx_status setup_run(vx_ctx* ctx, const vx_batch_join* d, const BatchConfi
   const uint64_t desc_bytes = (uint64_t)J * sizeof(BatchJob);
   const uint64_t map_bytes = pl.probe_map.size() * 8, bmap_bytes = pl.build_map.size() * 8;
   const uint64_t rmap_bytes = pl.region_map.size() * 8, pmap_bytes = pl.part_map.size() * 8;
+  const uint64_t cmap_bytes = pl.cluster_map.size() * 8;
   const uint64_t bytes = run_bytes(pl, J, r->counter_words);
   r->mem.a = &ctx->arena;
   r->mem.p = ctx->arena.alloc(bytes);
@@ -1232,8 +1492,11 @@ static vx_status setup_run(vx_ctx* ctx, const vx_batch_join* d, const BatchConfi
   q += align256(rmap_bytes);
   r->part_map = (unsigned long long*)q;
   q += align256(pmap_bytes);
+  r->cluster_map = (unsigned long long*)q;
+  q += align256(cmap_bytes);
   uint8_t* part_block = q;
   r->tally = (uint32_t*)(part_block + pl.pkey_bytes);
+  r->cursors = (uint32_t*)(part_block + pl.part_bytes - align256(pl.cursor_entries * 4));
   for (uint32_t j = 0; j < J; ++j) {
     BatchJob& b = r->plan.jobs[j];
     if (b.direct) {
@@ -1245,6 +1508,8 @@ static vx_status setup_run(vx_ctx* ctx, const vx_batch_join* d, const BatchConfi
     b.side = sides + 2 * (uint64_t)j;
     if (b.n_parts && !b.in_place) {
       b.pbuf = part_block + (uint64_t)(uintptr_t)b.pbuf;
+      b.boff = (uint16_t*)(part_block + (uint64_t)(uintptr_t)b.boff);
+      b.cursor = (uint32_t*)((uint8_t*)r->cursors + (uint64_t)(uintptr_t)b.cursor);
       b.kept = (unsigned long long*)(part_block + pl.pkey_bytes + align256(pl.tally_entries * 4) +
                                      (uint64_t)(uintptr_t)b.kept);
     }
@@ -1258,16 +1523,19 @@ static vx_status setup_run(vx_ctx* ctx, const vx_batch_join* d, const BatchConfi
     VX_HIP(hipMemcpyAsync(r->region_map, pl.region_map.data(), rmap_bytes, hipMemcpyHostToDevice, ctx->compute));
   if (pmap_bytes)
     VX_HIP(hipMemcpyAsync(r->part_map, pl.part_map.data(), pmap_bytes, hipMemcpyHostToDevice, ctx->compute));
+  if (cmap_bytes)
+    VX_HIP(hipMemcpyAsync(r->cluster_map, pl.cluster_map.data(), cmap_bytes, hipMemcpyHostToDevice, ctx->compute));
   return VX_OK;
 }
 
-static void launch_dupcount(vx_ctx* ctx, const BatchRun& r, uint32_t J, hipStream_t s) {
+static void launch_dupcount(vx_ctx* ctx, const BatchRun& r, int ks, uint32_t J, hipStream_t s) {
   if (!r.plan.count_tiles) return;
   const unsigned g = (unsigned)std::min<uint64_t>(r.plan.count_tiles, (uint64_t)ctx->cu_count * 4);
-  hipLaunchKernelGGL(k_batch_dupcount, dim3(g), dim3(256), 0, s, r.jobs_dev, J, r.plan.count_tiles, r.bits);
+  if (ks == 8) hipLaunchKernelGGL(k_batch_dupcount<int64_t>, dim3(g), dim3(256), 0, s, r.jobs_dev, J, r.plan.count_tiles, r.bits);
+  else hipLaunchKernelGGL(k_batch_dupcount<int32_t>, dim3(g), dim3(256), 0, s, r.jobs_dev, J, r.plan.count_tiles, r.bits);
 }
 
-// A direct-table job with fewer than nb presence bytes set had a repeated build key.
+// A direct-table job with fewer than nb keys (presence bytes set, or bits of its regions) had one repeated.
 static bool direct_dups(const BatchPlan& pl, const unsigned long long* bits) {
   for (size_t i = 0; i < pl.jobs.size(); ++i)
     if (pl.jobs[i].direct && bits[i] != pl.jobs[i].nb) return true;
@@ -1283,10 +1551,12 @@ static vx_status enqueue_batch(vx_ctx* ctx, const BatchRun& r, const BatchConfig
   if (r.plan.slots)
     hipLaunchKernelGGL(k_batch_init, dim3(std::max(ig, 1u)), dim3(256), 0, s, (uint32_t*)r.slots, r.plan.slots,
                        sw, (uint32_t)ks);
-  if (r.plan.direct_bytes)
-    fill_zero((uint64_t*)(r.slots + align256(r.plan.slots << r.plan.slot_shift)), r.plan.direct_bytes / 8, s);
-  fill_zero((uint64_t*)r.counters, r.counter_words, s);
-  fill_zero((uint64_t*)ctx->dev_flags, 1, s);
+  FillList fills;   // 16-byte multiples: each range is the first of a 256-byte multiple
+  if (r.plan.tables) fills.zero(r.slots + align256(r.plan.slots << r.plan.slot_shift), r.plan.direct_bytes);
+  fills.zero(r.counters, (r.counter_words + 1) / 2 * 16);
+  fills.zero(ctx->dev_flags, kFlagBytes);
+  if (r.plan.cursor_entries) fills.zero(r.cursors, align256(r.plan.cursor_entries * 4));
+  VX_TRY(fills.launch(s));
   const uint64_t per_cu = cfg.block >= 512 ? 4 : 8;
   // the tile maps assume grids of a multiple of kXcds workgroups (see BatchPlan::probe_map)
   const uint64_t bmapped = r.plan.build_map.size(), mapped = r.plan.probe_map.size();
@@ -1299,7 +1569,7 @@ static vx_status enqueue_batch(vx_ctx* ctx, const BatchRun& r, const BatchConfig
   const char* fork_env = getenv("VX_BATCH_FORK");   // 0: everything on one stream, in order
   hipStream_t s2 = fork_env && fork_env[0] == '0' ? s : ctx->copy;
   const bool part = !r.plan.part_map.empty(), reg = !r.plan.region_map.empty();
-  hipEvent_t ev_built = nullptr, ev_done = nullptr;
+  hipEvent_t ev_built = nullptr, ev_done = nullptr, scattered = nullptr;
   if (reg) {
     hipEvent_t fork = get_event(ctx);
     ev_built = get_event(ctx);
@@ -1312,15 +1582,16 @@ static vx_status enqueue_batch(vx_ctx* ctx, const BatchRun& r, const BatchConfig
   if (part) {
     const uint64_t ns = r.plan.part_map.size();
     const unsigned g = (unsigned)std::min<uint64_t>(ns, (uint64_t)ctx->cu_count * 8);
-    const unsigned gs = (unsigned)std::min<uint64_t>(ns, (uint64_t)ctx->cu_count);   // one scatter workgroup per CU (its LDS)
+    const unsigned gs = (unsigned)std::min<uint64_t>(
+        ns, (uint64_t)ctx->cu_count * (ks == 8 ? scatter_groups<int64_t>() : scatter_groups<int32_t>()));
     if (ks == 8)
       hipLaunchKernelGGL(k_batch_count<int64_t>, dim3(g), dim3(kPartThreads), 0, s2, r.jobs_dev, r.part_map, ns, r.tally);
     else
       hipLaunchKernelGGL(k_batch_count<int32_t>, dim3(g), dim3(kPartThreads), 0, s2, r.jobs_dev, r.part_map, ns, r.tally);
     hipLaunchKernelGGL(k_batch_scan, dim3(J), dim3(kScanBlock), 0, s2, r.jobs_dev, r.tally);
-    // the build phase starts after the count, which reads at the memory's rate: beside the
+    // the tables in memory are built after the count, which reads at the memory's rate: beside the
     // scatter, which does not, the two slow each other less
-    if (s2 != s) {
+    if (s2 != s && bmapped) {
       hipEvent_t counted = get_event(ctx);
       VX_CHECK(counted, VX_EHIP, "batch: no events");
       VX_HIP(hipEventRecord(counted, s2));
@@ -1328,21 +1599,34 @@ static vx_status enqueue_batch(vx_ctx* ctx, const BatchRun& r, const BatchConfig
       put_event(ctx, counted);
     }
     if (ks == 8)
-      hipLaunchKernelGGL((k_batch_scatter<int64_t, scatter_threads<int64_t>()>), dim3(gs), dim3(scatter_threads<int64_t>()), 0, s2, r.jobs_dev, r.part_map, ns,
+      hipLaunchKernelGGL((k_batch_scatter<int64_t, scatter_threads<int64_t>(), scatter_items<int64_t>(), scatter_groups<int64_t>()>), dim3(gs), dim3(scatter_threads<int64_t>()), 0, s2, r.jobs_dev, r.part_map, ns,
                          (const uint32_t*)r.tally);
     else
-      hipLaunchKernelGGL((k_batch_scatter<int32_t, scatter_threads<int32_t>()>), dim3(gs), dim3(scatter_threads<int32_t>()), 0, s2, r.jobs_dev, r.part_map, ns,
+      hipLaunchKernelGGL((k_batch_scatter<int32_t, scatter_threads<int32_t>(), scatter_items<int32_t>(), scatter_groups<int32_t>()>), dim3(gs), dim3(scatter_threads<int32_t>()), 0, s2, r.jobs_dev, r.part_map, ns,
                          (const uint32_t*)r.tally);
     VX_HIP(hipGetLastError());
+    scattered = get_event(ctx);
+    VX_CHECK(scattered, VX_EHIP, "batch: no events");
+    VX_HIP(hipEventRecord(scattered, s2));
   }
   const unsigned long long* bmap = r.build_map;
-  if (ks == 8)
+  const uint64_t nc = r.plan.cluster_map.size();
+  if (nc) {
+    const unsigned g = (unsigned)ctx->cu_count * 2 / kXcds * kXcds;
+    auto launch = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(g), dim3(kClusterThreads), 0, s, r.jobs_dev, r.cluster_map, nc, bmap,
+                         (uint64_t)bmapped, cfg.tile_rows, r.plan.slot_shift, ctx->dev_flags);
+    };
+    const bool p8 = r.plan.pay_size == 8;
+    if (ks == 8) p8 ? launch(k_batch_build<int64_t, long long>) : launch(k_batch_build<int64_t, int>);
+    else p8 ? launch(k_batch_build<int32_t, long long>) : launch(k_batch_build<int32_t, int>);
+  } else if (bmapped && ks == 8) {
     hipLaunchKernelGGL((k_batch_phase<int64_t, true>), dim3(gb), dim3(cfg.block), 0, s, r.jobs_dev, J,
                        (uint64_t)bmapped, cfg.tile_rows, r.plan.slot_shift, r.acc, ctx->dev_flags, bmap);
-  else
+  } else if (bmapped) {
     hipLaunchKernelGGL((k_batch_phase<int32_t, true>), dim3(gb), dim3(cfg.block), 0, s, r.jobs_dev, J,
                        (uint64_t)bmapped, cfg.tile_rows, r.plan.slot_shift, r.acc, ctx->dev_flags, bmap);
-  launch_dupcount(ctx, r, J, s);
+  }
   if (reg) {
     VX_HIP(hipEventRecord(ev_built, s));
     VX_HIP(hipStreamWaitEvent(s2, ev_built, 0));
@@ -1368,6 +1652,11 @@ static vx_status enqueue_batch(vx_ctx* ctx, const BatchRun& r, const BatchConfig
       hipLaunchKernelGGL((k_batch_phase<int32_t, false>), dim3(gp), dim3(cfg.block), 0, s, r.jobs_dev, J,
                          (uint64_t)mapped, cfg.tile_rows, r.plan.slot_shift, r.acc, ctx->dev_flags, pmap);
   }
+  if (scattered) {
+    VX_HIP(hipStreamWaitEvent(s, scattered, 0));
+    put_event(ctx, scattered);
+  }
+  launch_dupcount(ctx, r, ks, J, s);
   if (reg) {
     VX_HIP(hipStreamWaitEvent(s, ev_done, 0));
     put_event(ctx, ev_done);
@@ -1617,9 +1906,9 @@ vx_status join_batch(vx_ctx* ctx, const vx_batch_join* d, vx_join_out* out) {
              VX_EDUPKEY, "batch: duplicate build key");
     VX_CHECK(!(f & kFlagFull), VX_ECAPACITY, "batch: table full (internal sizing error)");
     s.kernel_ms = ms;
-    // build phase, presence count, tile-map probe, count, scan, scatter, region probe
+    // build phase, key count, tile-map probe, count, scan, scatter, region probe
     const BatchPlan& gp = gc->run->plan;
-    s.kernel_launches = 1 + (gp.count_tiles ? 1 : 0) + (gp.probe_map.empty() ? 0 : 1) + (gp.part_jobs ? 3 : 0) +
+    s.kernel_launches = (gp.build_map.empty() && gp.cluster_map.empty() ? 0 : 1) + (gp.count_tiles ? 1 : 0) + (gp.probe_map.empty() ? 0 : 1) + (gp.part_jobs ? 3 : 0) +
                         (gp.region_map.empty() ? 0 : 1);
     s.n_parts = gp.part_jobs;
     s.survivors = gp.region_jobs;
@@ -1661,7 +1950,7 @@ vx_status join_batch(vx_ctx* ctx, const vx_batch_join* d, vx_join_out* out) {
                            r.acc + 2 * (uint64_t)j);
       }
     }
-    launch_dupcount(ctx, r, J, ctx->compute);
+    launch_dupcount(ctx, r, ks, J, ctx->compute);
     VX_HIP(hipGetLastError());
     VX_HIP(hipEventRecord(b, ctx->compute));
     std::vector<unsigned long long> bits(J);

@@ -387,3 +387,39 @@ def test_batch_direct_large_duplicate_detected(gpu, ctx):
             ctx.join_batch([dev(k)], [dev(rng.integers(0, 100, n).astype(np.int32))], [dev(k[:1000])], mode=mode,
                            tile_rows=8192, block=512, load_factor=0.5)
         assert ei.value.status == gpu.VX_EDUPKEY
+
+
+@pytest.mark.parametrize("kt,pt", [(np.int32, np.int32), (np.int32, np.int64), (np.int64, np.int32), (np.int64, np.int64),
+                                   (np.int32, None)])
+def test_batch_regions_built_from_rows(gpu, ctx, kt, pt):
+    """Direct tables at the edges of a region built in LDS (32,768 int32 or 16,384 int64 payloads) and of a
+    build tile (8,192 or 4,096 rows): one region, a last region of one row, many; probe sides of a few
+    rows and of several work items.  A repeated key is found within a region and across two, and the
+    graph still answers right once it is gone."""
+    import torch
+    rng = np.random.default_rng(37)
+    w = 16384 if pt == np.int64 else 32768
+    nbs = [1, 4096, 8191, w - 1, w, w + 1, 2 * w, 2 * w + 5, 300_001]
+    nps = [5, 0, 1000, 600_000, 70_001, 33, 65_536, 1_200_007, 2_000_003]
+    bk = [(rng.permutation(n) - 77).astype(kt) for n in nbs]
+    bp = [None if pt is None else rng.integers(-2**31, 2**31, n).astype(pt) for n in nbs]
+    pk = [rng.integers(-100, n + 50, m).astype(kt) for n, m in zip(nbs, nps)]
+    exp = [oracle.join_agg(b, [] if v is None else [v], p, []) for b, v, p in zip(bk, bp, pk)]
+    exp = [e if pt is not None else [e[0], 0] for e in exp]
+    args = [dev(x) for x in bk], [None if x is None else dev(x) for x in bp], [dev(x) for x in pk]
+    _say("batch regions from rows", kt.__name__, pt)
+    with gpu.Context(1 * GiB) as c:
+        for rep in range(3):
+            got, _ = c.join_batch(*args, tile_rows=4096, block=256, load_factor=0.5)
+            assert got == exp, rep
+            torch.cuda.synchronize()
+        for job, frm, to in ((3, 10, 11), (6, 10, 11), (8, 3, 299_923)):   # the smallest and largest key stay
+            at = {int(v): i for i, v in enumerate(bk[job])}
+            i, old = at[frm], bk[job][at[frm]].copy()
+            args[0][job][i] = to
+            with pytest.raises(gpu.VxError) as ei:
+                c.join_batch(*args, tile_rows=4096, block=256, load_factor=0.5)
+            assert ei.value.status == gpu.VX_EDUPKEY
+            args[0][job][i] = int(old)
+            got, _ = c.join_batch(*args, tile_rows=4096, block=256, load_factor=0.5)
+            assert got == exp
