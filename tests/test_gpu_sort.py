@@ -152,3 +152,21 @@ def test_sort_errors(gpu, ctx):
     with pytest.raises(gpu.VxError) as e:
         ctx.sort(np.arange(1000, dtype=np.int64))     # pageable memory
     assert e.value.status == gpu.VX_ENOTPINNED
+
+
+@pytest.mark.parametrize("dtype", [np.int32, np.int64])
+@pytest.mark.parametrize("n,chunk", [(4097, 1366), (70 * 64 + 1, 64), (131 * 1024, 1024), (3 * 40_000 - 1, 40_000),
+                                     (5, 1), (100_003, 50_001)])
+def test_sort_merge_rounds(gpu, ctx, dtype, n, chunk):
+    """Merge rounds of one pair, an odd segment, and more pairs than a launch takes (32); segments of one
+    key, and of several tiles; few distinct values (long ties across the pairs) and the type's extremes."""
+    rng = np.random.default_rng(n + chunk)
+    info = np.iinfo(dtype)
+    for name, keys in (("ties", rng.integers(0, 3, n)), ("wide", rng.integers(info.min, info.max, n, dtype=np.int64)),
+                       ("sorted", np.arange(n)), ("extremes", rng.choice([info.min, info.max, 0], n))):
+        print("sort merge rounds", dtype.__name__, n, chunk, name, flush=True)
+        hb = gpu.HostBuffer(n, np.dtype(dtype))
+        hb.array[:] = keys.astype(dtype)
+        ctx.sort(hb.array, chunk_rows=chunk)
+        assert np.array_equal(hb.array, np.sort(keys.astype(dtype)))
+        hb.free()
