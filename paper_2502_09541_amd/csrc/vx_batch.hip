@@ -467,17 +467,18 @@ __device__ __forceinline__ void rows_regions(const RegionFn& region, uint64_t np
   }
 }
 
-// Workgroup size, keys per lane and workgroups per compute unit of the scatter: a round sorts 8192 keys
-// in LDS, so that a region's run per round is a line or two.  Two workgroups of 1024 fit a compute unit
-// for 4-byte keys (64 registers a lane, 48 KiB of LDS each): one then works while the other waits at a
-// barrier.  378,000,000 int32 keys of 64 jobs, half of them kept: 467 us, against 535 with two
-// workgroups of 512 and 614 with one of 1024 and rounds of 16384.
-template <typename K>
-constexpr uint32_t scatter_threads() { return sizeof(K) == 4 ? 1024 : 512; }
-template <typename K>
-constexpr uint32_t scatter_items() { return sizeof(K) == 4 ? 8 : 16; }
-template <typename K>
-constexpr uint32_t scatter_groups() { return sizeof(K) == 4 ? 2 : 1; }
+// Forms of the scatter: lanes, keys per lane and round, workgroups per compute unit.  WIDE sorts rounds of
+// 16,384 int32 keys (8,192 int64 keys) and fills a unit's LDS; with two workgroups on rounds of 8,192
+// int32 keys, one works while the other waits at a barrier, but a region's run per round is half as long.
+template <typename K, bool WIDE>
+struct ScatterForm {
+  static constexpr uint32_t threads = sizeof(K) == 4 ? 1024 : 512, items = WIDE ? 16 : 8, groups = WIDE ? 1 : 2;
+};
+// The mean number of regions of a probe row's job above which rounds are wide.  Graph of 256 jobs, 4.4 G
+// probe rows: direct tables, mean 67: 11.6 ms short, 12.6 wide; hash tables, mean 281 or 345 by load
+// factor: 27.2 short, 24.3 wide.  The line lies between.  The scatter alone, 378 M rows of 64 jobs in up
+// to 32 regions: 467 us short, 614 wide.
+constexpr uint64_t kWideRegions = 128;
 
 // Scatter pass: each kept key of super-tile st to its region's array, at the super-tile's
 // position for the region plus its rank.  The super-tile goes in rounds of T ITEMS keys; each
@@ -1119,6 +1120,7 @@ struct BatchPlan {
   std::vector<unsigned long long> cluster_map;
   uint64_t cursor_entries = 0;
   bool tables = false;
+  bool wide_scatter = false;       // see kWideRegions
 };
 
 // Which jobs get a direct table: per caller's job, direct[j] and the smallest key kmin[j]
@@ -1396,13 +1398,19 @@ static vx_status plan_batch(const vx_batch_join* d, const BatchConfig& cfg, int 
   if (regions) plan_regions(pl, ks, slot_bytes, part_budget, stage);
   pl->count_tiles = 0;
   pl->tables = false;
+  uint64_t rows = 0, row_regions = 0;
   for (BatchJob& b : pl->jobs) {
+    if (b.n_parts && !b.in_place) {
+      rows += b.np;
+      row_regions += b.np * b.n_parts;
+    }
     const bool table = b.direct && !b.rows;
     b.ctile0 = pl->count_tiles;
     b.count_tiles = table ? (uint32_t)(((b.nb + 7) / 8 + kCountWords - 1) / kCountWords) : b.rows ? b.n_parts : 0;
     pl->count_tiles += b.count_tiles;
     pl->tables |= table;
   }
+  pl->wide_scatter = row_regions > kWideRegions * rows;
   map_tiles(pl, slot_bytes, l2_bytes);
   return VX_OK;
 }
@@ -1582,8 +1590,6 @@ static vx_status enqueue_batch(vx_ctx* ctx, const BatchRun& r, const BatchConfig
   if (part) {
     const uint64_t ns = r.plan.part_map.size();
     const unsigned g = (unsigned)std::min<uint64_t>(ns, (uint64_t)ctx->cu_count * 8);
-    const unsigned gs = (unsigned)std::min<uint64_t>(
-        ns, (uint64_t)ctx->cu_count * (ks == 8 ? scatter_groups<int64_t>() : scatter_groups<int32_t>()));
     if (ks == 8)
       hipLaunchKernelGGL(k_batch_count<int64_t>, dim3(g), dim3(kPartThreads), 0, s2, r.jobs_dev, r.part_map, ns, r.tally);
     else
@@ -1598,12 +1604,16 @@ static vx_status enqueue_batch(vx_ctx* ctx, const BatchRun& r, const BatchConfig
       VX_HIP(hipStreamWaitEvent(s, counted, 0));
       put_event(ctx, counted);
     }
-    if (ks == 8)
-      hipLaunchKernelGGL((k_batch_scatter<int64_t, scatter_threads<int64_t>(), scatter_items<int64_t>(), scatter_groups<int64_t>()>), dim3(gs), dim3(scatter_threads<int64_t>()), 0, s2, r.jobs_dev, r.part_map, ns,
-                         (const uint32_t*)r.tally);
-    else
-      hipLaunchKernelGGL((k_batch_scatter<int32_t, scatter_threads<int32_t>(), scatter_items<int32_t>(), scatter_groups<int32_t>()>), dim3(gs), dim3(scatter_threads<int32_t>()), 0, s2, r.jobs_dev, r.part_map, ns,
-                         (const uint32_t*)r.tally);
+    auto scatter = [&](auto form, auto kern) {
+      const unsigned gs = (unsigned)std::min<uint64_t>(ns, (uint64_t)ctx->cu_count * form.groups);
+      hipLaunchKernelGGL(kern, dim3(gs), dim3(form.threads), 0, s2, r.jobs_dev, r.part_map, ns, (const uint32_t*)r.tally);
+    };
+    using Long = ScatterForm<int64_t, true>;
+    using Wide = ScatterForm<int32_t, true>;
+    using Short = ScatterForm<int32_t, false>;
+    if (ks == 8) scatter(Long{}, k_batch_scatter<int64_t, Long::threads, Long::items, Long::groups>);
+    else if (r.plan.wide_scatter) scatter(Wide{}, k_batch_scatter<int32_t, Wide::threads, Wide::items, Wide::groups>);
+    else scatter(Short{}, k_batch_scatter<int32_t, Short::threads, Short::items, Short::groups>);
     VX_HIP(hipGetLastError());
     scattered = get_event(ctx);
     VX_CHECK(scattered, VX_EHIP, "batch: no events");

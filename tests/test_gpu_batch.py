@@ -423,3 +423,24 @@ def test_batch_regions_built_from_rows(gpu, ctx, kt, pt):
             args[0][job][i] = int(old)
             got, _ = c.join_batch(*args, tile_rows=4096, block=256, load_factor=0.5)
             assert got == exp
+
+
+def test_batch_wide_scatter_rounds(gpu, monkeypatch):
+    """int32 jobs whose probe rows meet more than 128 regions on average (the scatter's rounds of 16,384
+    keys), direct and hashed, with probe sides ragged against both round lengths."""
+    monkeypatch.setenv("VX_BATCH_STAGE_KB", "1")
+    rng = np.random.default_rng(41)
+    bk, bp, pk = [], [], []
+    for n, m in ((100_000, 300_001), (60_000, 16_383), (200_000, 131_073), (256, 5000)):
+        bk.append((rng.permutation(n) + 9).astype(np.int32))
+        bp.append(rng.integers(-2**31, 2**31, n).astype(np.int32))
+        pk.append(rng.integers(-50, 2 * n, m).astype(np.int32))
+    exp = [oracle.join_agg(a, [b], c, []) for a, b, c in zip(bk, bp, pk)]
+    args = [dev(x) for x in bk], [dev(x) for x in bp], [dev(x) for x in pk]
+    with gpu.Context(1 * GiB) as c:
+        for hashed in (False, True):
+            _say("batch wide scatter", hashed)
+            for rep in range(2):
+                got, st = c.join_batch(*args, hashed=hashed, tile_rows=4096, block=256, load_factor=0.5)
+                assert got == exp, rep
+            assert st["n_parts"] >= 3
