@@ -145,16 +145,16 @@ void put_event(vx_ctx* ctx, hipEvent_t e);
 void fill_zero(uint64_t* p, uint64_t words, hipStream_t s);
 
 // Several device ranges filled by one launch.  A range is 16-byte aligned and a multiple of 16 bytes;
-// every `period` 32-bit words (a power of two) start with v0, v1 and are zero else.
+// every `period` 32-bit words (a power of two) start with v0, v1, v2 and are zero else.
 struct FillList {
   static constexpr uint32_t kMax = 16;
   struct Job {
     void* p;
     uint64_t quads;
-    uint32_t period, v0, v1, reserved;
+    uint32_t period, v0, v1, v2;
   } job[kMax];
   uint32_t n = 0;
-  void pattern(void* p, uint64_t bytes, uint32_t period, uint32_t v0, uint32_t v1);
+  void pattern(void* p, uint64_t bytes, uint32_t period, uint32_t v0, uint32_t v1, uint32_t v2 = 0);
   void zero(void* p, uint64_t bytes) { pattern(p, bytes, 4, 0, 0); }
   vx_status launch(hipStream_t s);
 };

@@ -283,6 +283,7 @@ __global__ void __launch_bounds__(256) k_build_preagg(TableView t, BuildCols c, 
   __shared__ unsigned long long lkey[kPreaggLds];
   __shared__ unsigned long long lcnt[kPreaggLds];
   __shared__ unsigned long long lsum[kMaxPay][kPreaggLds];
+  __shared__ uint32_t spill;                  // a row of the tile found no place in LDS
   const unsigned long long kFree = ~0ull;     // LDS marker; real keys are stored as 64-bit
   const unsigned long long kFreeAlt = ~0ull - 1;
   for (uint64_t base = (uint64_t)blockIdx.x * kPreaggTile; base < n;
@@ -292,6 +293,7 @@ __global__ void __launch_bounds__(256) k_build_preagg(TableView t, BuildCols c, 
       lcnt[j] = 0;
       for (uint32_t p = 0; p < kMaxPay; ++p) lsum[p][j] = 0;
     }
+    if (threadIdx.x == 0) spill = 0;
     __syncthreads();
     uint64_t end = base + kPreaggTile < n ? base + kPreaggTile : n;
     for (uint64_t i = base + threadIdx.x; i < end; i += blockDim.x) {
@@ -314,14 +316,19 @@ __global__ void __launch_bounds__(256) k_build_preagg(TableView t, BuildCols c, 
           }
         }
       }
-      if (!placed) global_preagg_add<K>(t, k, 1ull, vals, flags);
+      if (!placed) {
+        spill = 1;
+        global_preagg_add<K>(t, k, 1ull, vals, flags, true);
+      }
     }
     __syncthreads();
+    // a tile of few keys: they are in many tiles, their lines are fought over, and a look waits too
+    const bool spilled = spill != 0;
     for (int j = threadIdx.x; j < kPreaggLds; j += blockDim.x) {
       if (lkey[j] != kFree) {
         unsigned long long sums[kMaxPay];
         for (uint32_t p = 0; p < kMaxPay; ++p) sums[p] = lsum[p][j];
-        global_preagg_add<K>(t, (K)(long long)lkey[j], lcnt[j], sums, flags);
+        global_preagg_add<K>(t, (K)(long long)lkey[j], lcnt[j], sums, flags, spilled);
       }
     }
     __syncthreads();
@@ -819,6 +826,10 @@ static vx_status plan_table(int32_t key_type, uint32_t flags, const int32_t* pay
   return VX_OK;
 }
 
+// The count that an empty slot starts with: a pre-aggregated one's first row need not add itself
+// (global_preagg_add).
+static uint32_t preagg_count0(const TableView& v) { return v.preagg ? 1u : 0u; }
+
 vx_status make_table(vx_ctx* ctx, int32_t key_type, uint32_t flags, const int32_t* pay_types,
                      uint32_t n_pay, uint64_t expected_rows, float load_factor, vx_table** out,
                      const KeyRange* kr, FillList* fills) {
@@ -859,7 +870,7 @@ vx_status make_table(vx_ctx* ctx, int32_t key_type, uint32_t flags, const int32_
     // every payload slot is written by the build; the presence bytes and the side record start at zero
     fl.zero(v.present, bits_bytes + 256);
   } else {   // the empty marker: word 0 of a 4-byte key, word 1 of an 8-byte one (little-endian)
-    fl.pattern(mem, slots_bytes, slot_bytes / 4, ks == 4 ? 0x80000000u : 0u, ks == 4 ? 0u : 0x80000000u);
+    fl.pattern(mem, slots_bytes, slot_bytes / 4, ks == 4 ? 0x80000000u : 0u, ks == 4 ? 0u : 0x80000000u, preagg_count0(v));
     fl.zero(v.side, 256);
   }
   if (!fills) (void)own.launch(ctx->compute);
@@ -1567,7 +1578,8 @@ extern "C" vx_status vx_join_plain_noalloc(const vx_build_desc* b, const vx_prob
   fill_zero(out, 10, s);
   FillList fills;
   fills.zero(nd->ptr, kNaSlotsOff);
-  fills.pattern(v.slots, cap * slot_bytes, slot_bytes / 4, ks == 4 ? 0x80000000u : 0u, ks == 4 ? 0u : 0x80000000u);
+  fills.pattern(v.slots, cap * slot_bytes, slot_bytes / 4, ks == 4 ? 0x80000000u : 0u, ks == 4 ? 0u : 0x80000000u,
+                preagg_count0(v));
   VX_TRY(fills.launch(s));
   if (ks == 8) noalloc_launch<int64_t>(v, bc, b->n, q, nd->cu_count, (unsigned long long*)out, s);
   else noalloc_launch<int32_t>(v, bc, b->n, q, nd->cu_count, (unsigned long long*)out, s);

@@ -200,15 +200,15 @@ __global__ void __launch_bounds__(256) k_fill(FillList l) {
 #pragma unroll
       for (uint32_t i = 0; i < 4; ++i) {
         const uint32_t at = (uint32_t)(4 * q + i) & (b.period - 1);
-        v[i] = at == 0 ? b.v0 : at == 1 ? b.v1 : 0u;
+        v[i] = at == 0 ? b.v0 : at == 1 ? b.v1 : at == 2 ? b.v2 : 0u;
       }
       ((uint4*)b.p)[q] = make_uint4(v[0], v[1], v[2], v[3]);
     }
   }
 }
 
-void FillList::pattern(void* p, uint64_t bytes, uint32_t period, uint32_t v0, uint32_t v1) {
-  job[n++] = Job{p, bytes / 16, period, v0, v1, 0};   // callers stay below kMax
+void FillList::pattern(void* p, uint64_t bytes, uint32_t period, uint32_t v0, uint32_t v1, uint32_t v2) {
+  job[n++] = Job{p, bytes / 16, period, v0, v1, v2};   // callers stay below kMax
 }
 
 vx_status FillList::launch(hipStream_t s) {

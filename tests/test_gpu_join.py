@@ -254,3 +254,22 @@ def test_zero_copy_granules_unaligned_column(gpu):
     finally:
         kh.free()
         ph.free()
+
+
+@pytest.mark.parametrize("kt", [np.int32, np.int64])
+@pytest.mark.parametrize("rows,keys", [(1, 1), (4096, 4096), (4097, 1023), (12_289, 1100), (50_000, 7), (60_001, 40_000)])
+def test_preaggregated_build_tiles(gpu, ctx, kt, rows, keys):
+    """Builds with repeated keys around a tile of 4096 rows and its 1024 LDS entries: tiles that fit, that
+    overflow by a few keys and that hold mostly distinct ones; the keys -1 and -2, which bypass LDS, and
+    the empty marker; a table indexed by key and a hash table; one to three payloads."""
+    rng = np.random.default_rng(rows + keys)
+    for spread in (1, 7919):
+        pool = (np.arange(keys, dtype=np.int64) * spread - 3).astype(kt)
+        pool[:3] = np.array([np.iinfo(kt).min, -1, -2], np.int64)[:len(pool)].astype(kt)
+        bk = pool[rng.integers(0, keys, rows)]
+        bps = [rng.integers(-2**31, 2**31, rows).astype(t) for t in (np.int64, np.int32, np.int64)[:1 + rows % 3]]
+        pk = np.concatenate([pool[rng.integers(0, keys, 3000)], rng.integers(-10, 10, 100).astype(kt)])
+        print("preagg tiles", kt.__name__, rows, keys, spread, flush=True)
+        for hashed in (False, True):
+            got = ctx.join_plain(dev(bk), [dev(p) for p in bps], dev(pk), [], unique=False, hashed=hashed)[0]
+            assert got == oracle.join_agg(bk, bps, pk, [])
