@@ -69,13 +69,14 @@ __device__ __forceinline__ uint32_t seg_advance(const unsigned long long* pre, u
 constexpr uint32_t kSideWords = 8;   // per-partition side record: count, payload sum (padded)
 constexpr uint32_t kSlotShift = 5;   // 32-byte slots: key, count, payload sum, padding
 
-// Empty every slot of a pre-aggregating table; zero a side record if one is given.
+// Empty every slot of a pre-aggregating table, its count at 1 for the row that claims it; zero a side
+// record if one is given.
 __global__ void k_pj_init(uint32_t* slots, uint64_t capacity, uint32_t key_size, unsigned long long* side) {
   const uint32_t words = 1u << (kSlotShift - 2);
   for (uint64_t s = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; s < capacity;
        s += (uint64_t)gridDim.x * blockDim.x) {
     uint32_t* w = slots + s * words;
-    for (uint32_t i = 0; i < words; ++i) w[i] = 0;
+    for (uint32_t i = 0; i < words; ++i) w[i] = i == 2;
     if (key_size == 4) w[0] = 0x80000000u;
     else w[1] = 0x80000000u;
   }
@@ -83,11 +84,12 @@ __global__ void k_pj_init(uint32_t* slots, uint64_t capacity, uint32_t key_size,
 }
 
 // Add (cnt, sum) to key k's record; returns the slot index when this call claimed a new slot,
-// else ~0.  LOOK: read the slot first.  A slot goes from empty to its key once, so only one seen empty
-// needs the compare-and-swap; that saves an atomic for a key that is there, but costs a read of a
-// line under contention for keys that every workgroup adds (rows go with it, LDS entries without:
-// 8.0 M rows, four of each key: 1049 us without, 871 with; Zipf(1.5) keys with it on both: 390 us
-// against 273).
+// else ~0.  An empty slot's count is 1 already: a new key's row adds only its payload (a two-table join
+// of 16.8 M + 16.8 M rows, unique build keys: 13.77 ms with two additions, 13.22 with one).
+// LOOK: read the slot first.  A slot goes from empty to its key once, so only one seen empty needs the
+// compare-and-swap; that saves an atomic for a key that is there, but costs a read of a line under
+// contention for keys that every workgroup adds (rows go with it, LDS entries without: 8.0 M rows, four
+// of each key: 1049 us without, 871 with; Zipf(1.5) keys with it on both: 390 us against 273).
 template <bool LOOK, typename K>
 __device__ __forceinline__ uint64_t preagg_claim_add(const TableView& t, K k, unsigned long long cnt,
                                                      unsigned long long sum, unsigned int* flags) {
@@ -106,7 +108,7 @@ __device__ __forceinline__ uint64_t preagg_claim_add(const TableView& t, K k, un
     const bool claimed = prev == kEmpty && (prev = atomicCAS((U*)slot, kEmpty, kb)) == kEmpty;
     if (claimed || prev == kb) {
       unsigned long long* w = (unsigned long long*)(slot + 8);
-      atomicAdd(w, cnt);
+      if (cnt != claimed) atomicAdd(w, cnt - claimed);
       if (t.n_pay) atomicAdd(w + 1, sum);
       return claimed ? h : ~0ull;
     }
@@ -290,7 +292,7 @@ __global__ void k_pj_compact(uint8_t* tslots, const uint32_t* claims, uint64_t n
     unsigned long long* w = (unsigned long long*)(src + 8);
     unsigned long long cnt = w[0], sum = w[1];
     *(U*)src = kEmpty;
-    w[0] = 0;
+    w[0] = 1;   // as k_pj_init
     w[1] = 0;
     uint64_t h = slot_of(key_bits((K)k), c.log2cap);
     for (uint64_t step = 0; step <= c.mask; ++step) {
