@@ -794,7 +794,7 @@ vx_status sort_impl(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {
       // merge rounds: pairs of neighbouring segments, X and Y in turn
       std::vector<uint64_t> seg;
       for (uint64_t j = 0; j <= runs; ++j)
-        if (j == 0 || j == runs || off[j] != off[j - 1]) seg.push_back(off[j]);
+        if (seg.empty() || off[j] != seg.back()) seg.push_back(off[j]);   // no segment is empty: every pair has tiles
       uint8_t* src = X[b];
       uint8_t* dst = Y[b];
       hipEvent_t e0 = get_event(ctx), e1 = get_event(ctx);

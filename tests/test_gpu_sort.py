@@ -170,3 +170,28 @@ def test_sort_merge_rounds(gpu, ctx, dtype, n, chunk):
         ctx.sort(hb.array, chunk_rows=chunk)
         assert np.array_equal(hb.array, np.sort(keys.astype(dtype)))
         hb.free()
+
+
+@pytest.mark.parametrize("dtype", [np.int32, np.int64])
+@pytest.mark.parametrize("n,chunk", [(64 * 1024 + 1, 1024), (128 * 1024 + 1, 1024), (64 * 1024, 1024), (65, 1)])
+def test_sort_merge_rounds_full_launches(gpu, ctx, dtype, n, chunk):
+    """Ranges of exactly 64 or 128 non-empty segments, so that the pairs fill their launches (32 each), before
+    a last run that has no key in most ranges; and the same without that run."""
+    rng = np.random.default_rng(n)
+    info = np.iinfo(dtype)
+    for name, keys in (("wide", rng.integers(info.min, info.max, n, dtype=np.int64)), ("ties", rng.integers(0, 3, n)),
+                       ("equal", np.full(n, 7))):
+        print("sort full merge launches", dtype.__name__, n, chunk, name, flush=True)
+        for where in ("host", "device"):
+            k = keys.astype(dtype)
+            if where == "host":
+                h = pinned(gpu, k)
+                ctx.sort(h, chunk_rows=chunk)
+                got = h.array.copy()
+                h.free()
+            else:
+                import torch
+                d = torch.from_numpy(k.copy()).cuda()
+                ctx.sort(d, chunk_rows=chunk)
+                got = d.cpu().numpy()
+            assert np.array_equal(got, np.sort(k))
