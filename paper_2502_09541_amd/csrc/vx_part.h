@@ -95,18 +95,23 @@ __device__ __forceinline__ uint32_t part_of(const PartSpec& ps, long long k, con
 
 constexpr uint32_t kMaxSumSlots = 64;
 
-// Device scratch of part_count and part_sweep over at most `rows` rows per launch.
-uint64_t part_work_bytes(uint32_t n_parts, uint64_t rows);
+// Rows of one launch over device-resident columns: the look-back words (8 bytes per partition and tile)
+// take 32 MiB for 1024 partitions, whatever the column's length.
+constexpr uint64_t kPartLaunchRows = 1ull << 25;
+
+// Device scratch of part_count and part_sweep over at most `rows` rows per launch, and of part_count
+// alone (sweep == false: no look-back words).
+uint64_t part_work_bytes(uint32_t n_parts, uint64_t rows, bool sweep = true);
 
 // Count the rows of every partition.  totals (n_parts u64) receives the counts, or has them added
 // when `accumulate`; base (n_parts + 1) the exclusive prefix of totals and its sum; host_totals
 // (optional, host-mapped) a copy of totals.  sums (optional): for partitions with sum_slot[p] >= 0
 // (a device int array of n_parts entries, slots < kMaxSumSlots), the row count and the SUM of
-// payload 0 are added to sums[2*slot] and sums[2*slot+1].  Leaves `work` ready for one part_sweep
-// over the same rows.
+// payload 0 are added to sums[2*slot] and sums[2*slot+1].  With `sweep` it leaves `work` ready for one
+// part_sweep over the same rows.
 vx_status part_count(vx_ctx* ctx, const PartSpec& ps, const PartIO& io, uint8_t* work, unsigned long long* totals,
                      bool accumulate, unsigned long long* base, unsigned long long* host_totals, const int* sum_slot,
-                     unsigned long long* sums, hipStream_t s);
+                     unsigned long long* sums, hipStream_t s, bool sweep = true);
 // Write the rows of io to their places: partition p's from out_base + base[p] on, in input order.
 // next (optional, n_parts; may be base) receives the position after each partition's rows, the
 // base of the chunk that follows.  `work` comes from part_count over the same rows, or was made

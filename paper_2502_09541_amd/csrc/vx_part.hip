@@ -2,6 +2,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <type_traits>
 #include <vector>
 
@@ -295,8 +296,8 @@ static uint32_t count_groups(uint64_t rows) {
 
 // sizes grow with the rows except where the tile does, so a launch over fewer rows than planned for
 // is allowed the small tiles' words
-uint64_t part_work_bytes(uint32_t n_parts, uint64_t rows) {
-  const uint64_t words = std::max(sweep_words(n_parts, rows), sweep_words(n_parts, std::min<uint64_t>(rows, 1ull << 19)));
+uint64_t part_work_bytes(uint32_t n_parts, uint64_t rows, bool sweep) {
+  const uint64_t words = !sweep ? 0 : std::max(sweep_words(n_parts, rows), sweep_words(n_parts, std::min<uint64_t>(rows, 1ull << 19)));
   return 64 + words * 8 + (uint64_t)count_groups(rows) * n_parts * 4 + 8;
 }
 
@@ -308,10 +309,10 @@ vx_status part_ready(const PartSpec& ps, uint64_t rows, uint8_t* work, hipStream
 
 vx_status part_count(vx_ctx* ctx, const PartSpec& ps, const PartIO& io, uint8_t* work, unsigned long long* totals,
                      bool accumulate, unsigned long long* base, unsigned long long* host_totals, const int* sum_slot,
-                     unsigned long long* sums, hipStream_t s) {
+                     unsigned long long* sums, hipStream_t s, bool sweep) {
   (void)ctx;
   const uint32_t P = ps.n_parts, groups = count_groups(io.n);
-  const uint64_t words = sweep_words(P, io.n);
+  const uint64_t words = sweep ? sweep_words(P, io.n) : 0;
   uint32_t* ticket = (uint32_t*)work;
   unsigned long long* status = (unsigned long long*)(work + 64);
   uint32_t* part = (uint32_t*)(status + words);
@@ -487,9 +488,7 @@ static vx_status partition_impl(vx_ctx* ctx, const vx_partition_desc* d, vx_part
   for (uint32_t p = 0; p < P; ++p) ctx->host_acc[p] = 0;
   // Pass A counts every chunk; pass B scatters it from the running position of each partition.  A
   // single chunk needs no second look at its rows: its counts give the positions at once.
-  bool counted_all = false;   // work is ready for the only chunk's sweep
-  ArenaBlock wmem;
-  wmem.a = &ctx->arena;
+  bool counted_all = false;   // the first pass sweeps the only chunk too
   auto run_pass = [&](bool do_scatter) -> vx_status {
     std::vector<PipeCol> cols(1 + (scatter ? d->n_pay : 0));
     cols[0].info = kc;
@@ -498,11 +497,19 @@ static vx_status partition_impl(vx_ctx* ctx, const vx_partition_desc* d, vx_part
       cols[1 + c].info = pc[c];
       cols[1 + c].may_copy = cols[1 + c].copy = do_scatter;
     }
-    Pipeline pipe;
-    VX_TRY(pipe.plan(ctx, n, 0, 0, cols));
-    if (!wmem.p) {
-      wmem.p = ctx->arena.alloc(part_work_bytes(P, pipe.chunk_rows()));
-      VX_CHECK(wmem.p, VX_EBUDGET, "partition: no room for the partition scratch");
+    bool device = true;
+    for (uint32_t c = 0; c < d->n_pay; ++c) device &= pc[c].where == Where::Device;
+    const bool resident = kc.where == Where::Device && (device || !do_scatter);   // nothing to stream
+    ArenaBlock wmem;
+    wmem.a = &ctx->arena;
+    std::unique_ptr<Pipeline> pipe;   // gone before wmem: it drains the streams
+    for (uint64_t rows = resident ? std::min(n, kPartLaunchRows) : 0;; rows = pipe->chunk_rows() / 2) {
+      pipe.reset(new Pipeline);
+      VX_TRY(pipe->plan(ctx, n, rows, 0, cols));
+      if (!do_scatter) counted_all = scatter && device && pipe->n_chunks() == 1 && !pipe->streamed();
+      wmem.p = ctx->arena.alloc(part_work_bytes(P, pipe->chunk_rows(), do_scatter || counted_all));
+      if (wmem.p) break;
+      VX_CHECK(pipe->chunk_rows() > 1024, VX_EBUDGET, "partition: no room for the partition scratch");
     }
     auto kernel = [&](const ChunkView& v) -> vx_status {
       PartIO io{};
@@ -510,8 +517,9 @@ static vx_status partition_impl(vx_ctx* ctx, const vx_partition_desc* d, vx_part
       io.key_size = (uint32_t)kc.elsize;
       io.n = v.rows;
       if (!do_scatter)
-        VX_TRY(part_count(ctx, ps, io, wmem.p, totals, v.index > 0, bnd, h_dev, nullptr, nullptr, ctx->compute));
-      if (!do_scatter && !(scatter && counted_all)) return VX_OK;
+        VX_TRY(part_count(ctx, ps, io, wmem.p, totals, v.index > 0, bnd, h_dev, nullptr, nullptr, ctx->compute,
+                          counted_all));
+      if (!do_scatter && !counted_all) return VX_OK;
       io.n_pay = d->n_pay;
       for (uint32_t c = 0; c < d->n_pay; ++c) {
         io.pay[c] = ((v.global_mask >> (1 + c)) & 1u) ? (const uint8_t*)v.ptr[1 + c] + v.row0 * pc[c].elsize
@@ -524,11 +532,7 @@ static vx_status partition_impl(vx_ctx* ctx, const vx_partition_desc* d, vx_part
       if (do_scatter) VX_TRY(part_ready(ps, v.rows, wmem.p, ctx->compute));
       return part_sweep(ctx, ps, io, wmem.p, bnd, bnd, ctx->compute);
     };
-    if (!do_scatter) {
-      counted_all = pipe.n_chunks() == 1 && !pipe.streamed();
-      for (uint32_t c = 0; c < d->n_pay; ++c) counted_all &= pc[c].where == Where::Device;
-    }
-    VX_TRY(pipe.run(kernel));
+    VX_TRY(pipe->run(kernel));
     VX_HIP(hipStreamSynchronize(ctx->compute));
     return VX_OK;
   };

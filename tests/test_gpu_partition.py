@@ -557,3 +557,46 @@ def test_partitioned_join_auto_on_scrambled_keys(gpu, ctx, monkeypatch):
     assert used in (gpu.VX_PART_LEARNED, gpu.VX_PART_QUANTILE)
     # the heaviest key alone holds about 9.5% of the rows; radix-hash would isolate none
     assert st["singleton_rows"] > 0.05 * (len(bk) + len(pk))
+
+
+@pytest.mark.parametrize("n_pay", [0, 1])
+def test_long_device_column_in_a_small_arena(gpu, n_pay):
+    """60,000,001 device rows in 1024 partitions with 50 MiB of arena: the rows take two launches, whose
+    scratch does not grow with the column; boundaries, order and a payload across the launches, against a
+    stable sort of the ids."""
+    import torch
+    n, P = 60_000_001, 1024
+    g = torch.Generator(device="cuda").manual_seed(17)
+    key = torch.randint(-2**31, 2**31 - 1, (n,), generator=g, device="cuda", dtype=torch.int32)
+    row = torch.arange(n, device="cuda", dtype=torch.int32)
+    out, orow = torch.empty_like(key), torch.empty_like(row)
+    _say("long device column", n, P, n_pay)
+    with gpu.Context(50 << 20) as c:
+        kw = dict(out_pays=[orow]) if n_pay else {}
+        r = c.partition(key, [row] if n_pay else [], method="radix_bits", n_parts=P, shift=3, out_key=out, **kw)
+    ids = (key >> 3) & (P - 1)
+    hist = torch.bincount(ids.long(), minlength=P).cpu().numpy().astype(np.uint64)
+    assert np.array_equal(r["hist"], hist)
+    assert np.array_equal(r["boundary"], np.concatenate([[0], np.cumsum(hist)]).astype(np.uint64))
+    order = torch.sort(ids.to(torch.int16), stable=True).indices
+    assert torch.equal(out, key[order])
+    if n_pay:
+        assert torch.equal(orow, order.to(torch.int32))
+
+
+@pytest.mark.parametrize("P", [16, 1024])
+def test_partition_scratch_sets_the_chunk(gpu, P):
+    """Arenas in which the partition scratch does not fit beside the largest chunk buffers: the chunks shrink."""
+    n = 300_001
+    key, pay = _keys(n, 3), np.arange(n, dtype=np.int32)
+    want = _expect(oracle.part_ids_hash(key, P.bit_length() - 1), P, key, [pay])
+    for kb in (1400, 1700, 2500, 4000):
+        for hk, hp in ((True, True), (True, False), (False, True), (False, False)):
+            k = pinned(gpu, key) if hk else dev(key)
+            p = pinned(gpu, pay) if hp else dev(pay)
+            ok, op = _torch_empty_like(key), _torch_empty_like(pay)
+            _say("scratch sets the chunk", P, kb, hk, hp)
+            with gpu.Context(kb << 10) as c:
+                r = c.partition(k, [p], method="radix_hash", n_parts=P, out_key=ok, out_pays=[op])
+            assert np.array_equal(r["hist"], want[0]) and np.array_equal(r["boundary"], want[1])
+            assert np.array_equal(ok.cpu().numpy(), want[2]) and np.array_equal(op.cpu().numpy(), want[3][0])
