@@ -395,8 +395,8 @@ static unsigned grid1(const vx_ctx* ctx, uint64_t n) {
 }
 
 // LSD radix sort of m int64 keys (signed order) in 8-bit digits, up to the highest in which the keys
-// differ.  Returns the buffer holding the result.
-static vx_status sort_i64(vx_ctx* ctx, long long* a, long long* b, uint64_t m, long long** sorted) {
+// differ.  scratch holds sort_scratch_bytes(m).  Returns the buffer holding the result.
+static vx_status sort_i64(vx_ctx* ctx, long long* a, long long* b, uint64_t m, uint8_t* scratch, long long** sorted) {
   *sorted = a;
   if (m < 2) return VX_OK;
   hipStream_t s = ctx->compute;
@@ -409,11 +409,7 @@ static vx_status sort_i64(vx_ctx* ctx, long long* a, long long* b, uint64_t m, l
   unsigned long long diff = hm[0] ^ hm[1];
   if (diff == 0) return VX_OK;
   uint32_t top = 63 - (uint32_t)__builtin_clzll(diff);
-  ArenaBlock scratch;
-  scratch.a = &ctx->arena;
-  scratch.p = ctx->arena.alloc(sort_scratch_bytes(m));
-  VX_CHECK(scratch.p, VX_EBUDGET, "sort: no room for digit histograms");
-  return sort_keys_i64(ctx, a, b, m, top / 8 + 1, scratch.p, sorted, s);
+  return sort_keys_i64(ctx, a, b, m, top / 8 + 1, scratch, sorted, s);
 }
 
 struct Model {
@@ -541,7 +537,10 @@ vx_status cdf_splitters(vx_ctx* ctx, const ColInfo& key, uint64_t n, const vx_pa
   rep->sample_ms = t1 - t0;
   if (m == 0) return VX_OK;   // no splitters: a single partition
   long long* sorted = nullptr;
-  VX_TRY(sort_i64(ctx, sa, sbuf, m, &sorted));
+  // the features and targets come after the sort: until then their room (8 bytes a key) is its scratch,
+  // which takes at most a tile's 2048 bytes per 2048 keys beside its bases, and none up to 8192 keys
+  VX_CHECK(sort_scratch_bytes(m) <= 8 * cap, VX_EINVAL, "cdf: sort scratch of %llu keys", m);
+  VX_TRY(sort_i64(ctx, sa, sbuf, m, (uint8_t*)fx, &sorted));
   long long ends[2];
   VX_HIP(hipMemcpyAsync(&ends[0], sorted, 8, hipMemcpyDeviceToHost, s));
   VX_HIP(hipMemcpyAsync(&ends[1], sorted + m - 1, 8, hipMemcpyDeviceToHost, s));
@@ -656,7 +655,7 @@ vx_status cdf_splitters(vx_ctx* ctx, const ColInfo& key, uint64_t n, const vx_pa
     const uint32_t np = (uint32_t)sp.size() + 1;
     ArenaBlock b;
     b.a = &ctx->arena;
-    b.p = ctx->arena.alloc(part_work_bytes(np, m) + (2 * (uint64_t)np + 1) * 8 + sp.size() * 8 + 256);
+    b.p = ctx->arena.alloc(part_work_bytes(np, m, false) + (2 * (uint64_t)np + 1) * 8 + sp.size() * 8 + 256);
     VX_CHECK(b.p, VX_EBUDGET, "cdf: no room for sample histograms");
     unsigned long long* tot = (unsigned long long*)b.p;
     long long* spl = (long long*)(tot + 2 * (uint64_t)np + 1);
@@ -671,7 +670,7 @@ vx_status cdf_splitters(vx_ctx* ctx, const ColInfo& key, uint64_t n, const vx_pa
     ps.n_parts = np;
     ps.splitters = spl;
     if (ps.n_split) VX_HIP(hipMemcpyAsync(spl, sp.data(), ps.n_split * 8, hipMemcpyHostToDevice, s));
-    VX_TRY(part_count(ctx, ps, io, work, tot, false, tot + np, nullptr, nullptr, nullptr, s));
+    VX_TRY(part_count(ctx, ps, io, work, tot, false, tot + np, nullptr, nullptr, nullptr, s, false));
     std::vector<unsigned long long> h(np);
     VX_HIP(hipMemcpyAsync(h.data(), tot, np * 8, hipMemcpyDeviceToHost, s));
     VX_HIP(hipStreamSynchronize(s));
@@ -706,7 +705,7 @@ vx_status cdf_splitters(vx_ctx* ctx, const ColInfo& key, uint64_t n, const vx_pa
     uint32_t pr = std::max<uint32_t>(rep->radix_parts, (uint32_t)splitters->size() + 1);
     ArenaBlock hb;
     hb.a = &ctx->arena;
-    hb.p = ctx->arena.alloc(part_work_bytes(pr, m) + (2 * (uint64_t)pr + 1) * 8 + splitters->size() * 8 + 256);
+    hb.p = ctx->arena.alloc(part_work_bytes(pr, m, false) + (2 * (uint64_t)pr + 1) * 8 + splitters->size() * 8 + 256);
     VX_CHECK(hb.p, VX_EBUDGET, "cdf: no room for sample histograms");
     unsigned long long* tot = (unsigned long long*)hb.p;
     unsigned long long* base = tot + pr;
@@ -720,7 +719,7 @@ vx_status cdf_splitters(vx_ctx* ctx, const ColInfo& key, uint64_t n, const vx_pa
     ps.fn = kPartHash;
     ps.n_parts = rep->radix_parts;
     ps.log2p = l;
-    VX_TRY(part_count(ctx, ps, io, work, tot, false, base, nullptr, nullptr, nullptr, s));
+    VX_TRY(part_count(ctx, ps, io, work, tot, false, base, nullptr, nullptr, nullptr, s, false));
     std::vector<unsigned long long> h(ps.n_parts);
     VX_HIP(hipMemcpyAsync(h.data(), tot, h.size() * 8, hipMemcpyDeviceToHost, s));
     VX_HIP(hipStreamSynchronize(s));
@@ -732,7 +731,7 @@ vx_status cdf_splitters(vx_ctx* ctx, const ColInfo& key, uint64_t n, const vx_pa
     pr2.splitters = spl;
     if (pr2.n_split)
       VX_HIP(hipMemcpyAsync(spl, splitters->data(), pr2.n_split * 8, hipMemcpyHostToDevice, s));
-    VX_TRY(part_count(ctx, pr2, io, work, tot, false, base, nullptr, nullptr, nullptr, s));
+    VX_TRY(part_count(ctx, pr2, io, work, tot, false, base, nullptr, nullptr, nullptr, s, false));
     h.assign(pr2.n_parts, 0);
     VX_HIP(hipMemcpyAsync(h.data(), tot, h.size() * 8, hipMemcpyDeviceToHost, s));
     fill_zero((uint64_t*)tot, 1, s);

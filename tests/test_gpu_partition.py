@@ -600,3 +600,20 @@ def test_partition_scratch_sets_the_chunk(gpu, P):
                 r = c.partition(k, [p], method="radix_hash", n_parts=P, out_key=ok, out_pays=[op])
             assert np.array_equal(r["hist"], want[0]) and np.array_equal(r["boundary"], want[1])
             assert np.array_equal(ok.cpu().numpy(), want[2]) and np.array_equal(op.cpu().numpy(), want[3][0])
+
+
+def test_whole_column_sample_needs_only_its_keys(gpu):
+    """Splitters from every key of a 20,000,003-row column: beside the sample (24 bytes a key), the model and
+    the training points, 16 MiB are enough for the sample's sort and histograms."""
+    import torch
+    n, P = 20_000_003, 1024
+    g = torch.Generator(device="cuda").manual_seed(23)
+    key = torch.randint(-2**62, 2**62, (n,), generator=g, device="cuda")
+    budget = 24 * n + (16 << 20) + (8 << 20)   # the context's scratch and the model's: under 8 MiB
+    _say("whole-column sample", n, P)
+    with gpu.Context(budget) as c:
+        r = c.partition(key, method="quantile", n_parts=P, sample_frac=1.0)
+    spl = torch.from_numpy(r["splitters"]).cuda()
+    ids = torch.searchsorted(spl, key, right=True)
+    assert np.array_equal(r["hist"], torch.bincount(ids, minlength=len(spl) + 1).cpu().numpy().astype(np.uint64))
+    assert r["hist"].max() <= 1.001 * n / P + 2      # the quantiles of the column itself
