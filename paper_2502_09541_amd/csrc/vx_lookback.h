@@ -3,6 +3,8 @@
 // before it while they run.
 #pragma once
 
+#include <cstdlib>
+
 #include "vx_internal.h"
 
 namespace vx {
@@ -14,7 +16,17 @@ namespace vx {
 constexpr uint32_t kTagShift = 56;
 constexpr unsigned long long kTagValue = (1ull << kTagShift) - 1;
 constexpr uint32_t kLookWindow = 8;        // tiles read ahead in one look-back step
-constexpr uint32_t kLookSpins = 1u << 22;  // polls before a workgroup gives up (seconds; never in a sound run)
+
+// Where a workgroup whose wait does not end says so (a host-mapped word), and after how many polls: seconds,
+// never in a sound run.  VX_LOOK_POLLS lowers the limit, so that tests reach it (0: no tile waits at all).
+struct LookLimit {
+  uint32_t* stall;
+  uint32_t polls;
+};
+inline LookLimit look_limit(const vx_ctx* ctx) {
+  const char* e = getenv("VX_LOOK_POLLS");
+  return LookLimit{stall_word(ctx), e ? (uint32_t)strtoul(e, nullptr, 10) : 1u << 22};
+}
 
 __device__ __forceinline__ unsigned long long look_load(const unsigned long long* w) {
   return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -26,15 +38,21 @@ __device__ __forceinline__ void look_store(unsigned long long* w, uint32_t tag, 
 // Position of tile t's first element of a group: the counts of the tiles before t, back to the nearest
 // one whose running position is known (tile 0 starts from the group's base).  The group's words are
 // words[t * stride].  Tiles are taken in ticket order, so every tile waited for is running or done
-// and publishes its count before it waits itself: the wait ends.  It is bounded all the same
-// (`stall` is set, and the call fails).
+// and publishes its count before it waits itself: the wait ends.  It is bounded all the same: a
+// workgroup that gives up sets the stall word, by which the call fails, and returns the part it has
+// added up, at most the true position.
 __device__ __forceinline__ unsigned long long look_back(const unsigned long long* words, uint32_t stride, uint64_t t,
-                                                        uint32_t pass, uint32_t* stall) {
+                                                        uint32_t pass, LookLimit limit) {
   const uint32_t own = 2 * pass + 1, known = 2 * pass + 2;
   unsigned long long sum = 0;
   int64_t look = (int64_t)t - 1;
-  uint32_t spins = 0;
-  for (;;) {
+  for (uint32_t polls = 0;; ++polls) {
+    if (polls >= limit.polls) {
+      __hip_atomic_store(limit.stall, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      return sum;
+    }
+    if ((polls & 4095u) == 4095u && __hip_atomic_load(limit.stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0)
+      return sum;   // another gave up
     unsigned long long w[kLookWindow];
 #pragma unroll
     for (uint32_t i = 0; i < kLookWindow; ++i) {
@@ -54,13 +72,6 @@ __device__ __forceinline__ unsigned long long look_back(const unsigned long long
     }
     if (done) return sum;
     look -= (int64_t)took;
-    if (took == 0 && ++spins >= kLookSpins) {
-      __hip_atomic_store(stall, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      return sum;
-    }
-    if (took == 0 && (spins & 4095u) == 4095u &&
-        __hip_atomic_load(stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0)
-      return sum;
   }
 }
 

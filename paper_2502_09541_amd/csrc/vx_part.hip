@@ -144,7 +144,7 @@ constexpr uint32_t kSweepThreads = 1024;
 template <typename K, uint32_t E, uint32_t ITEMS, uint32_t BITS>
 __global__ void __launch_bounds__(kSweepThreads, 4) k_part_sweep(PartSpec ps, PartIO io, const unsigned long long* base,
                                                                  unsigned long long* next, unsigned long long* status,
-                                                                 uint32_t* ticket, uint32_t* stall) {
+                                                                 uint32_t* ticket, LookLimit limit) {
   constexpr uint32_t THREADS = kSweepThreads, MAXP = 1u << BITS, WAVES = THREADS / 64, TILE = THREADS * ITEMS,
                      WROWS = 64 * ITEMS;
   static_assert(THREADS >= MAXP && E >= sizeof(K) && TILE * E >= 8 * (MAXP - 1) && TILE <= (1u << 15), "tile shape");
@@ -233,7 +233,7 @@ __global__ void __launch_bounds__(kSweepThreads, 4) k_part_sweep(PartSpec ps, Pa
       }
     if (threadIdx.x < P) {
       if (t != 0) {
-        pos = look_back(status + threadIdx.x, P, t, 0, stall);
+        pos = look_back(status + threadIdx.x, P, t, 0, limit);
         look_store(status + t * P + threadIdx.x, 2, pos + tot);
       }
       gbase[threadIdx.x] = io.out_base + pos - e;
@@ -334,21 +334,21 @@ vx_status part_count(vx_ctx* ctx, const PartSpec& ps, const PartIO& io, uint8_t*
 
 template <typename K, uint32_t E>
 static void launch_sweep(const PartSpec& ps, const PartIO& io, const unsigned long long* base, unsigned long long* next,
-                         unsigned long long* status, uint32_t* ticket, uint32_t* stall, hipStream_t s) {
+                         unsigned long long* status, uint32_t* ticket, LookLimit limit, hipStream_t s) {
   const uint32_t tile = sweep_tile(io.n);
   const dim3 grid((unsigned)((io.n + tile - 1) / tile));
   const dim3 block(kSweepThreads);
   // more than 256 partitions take wider ids, counters and ballots
   if (ps.n_parts <= 256) {
     if (tile == 2048)
-      hipLaunchKernelGGL((k_part_sweep<K, E, 2, 8>), grid, block, 0, s, ps, io, base, next, status, ticket, stall);
+      hipLaunchKernelGGL((k_part_sweep<K, E, 2, 8>), grid, block, 0, s, ps, io, base, next, status, ticket, limit);
     else
-      hipLaunchKernelGGL((k_part_sweep<K, E, 8, 8>), grid, block, 0, s, ps, io, base, next, status, ticket, stall);
+      hipLaunchKernelGGL((k_part_sweep<K, E, 8, 8>), grid, block, 0, s, ps, io, base, next, status, ticket, limit);
   } else {
     if (tile == 2048)
-      hipLaunchKernelGGL((k_part_sweep<K, E, 2, 10>), grid, block, 0, s, ps, io, base, next, status, ticket, stall);
+      hipLaunchKernelGGL((k_part_sweep<K, E, 2, 10>), grid, block, 0, s, ps, io, base, next, status, ticket, limit);
     else
-      hipLaunchKernelGGL((k_part_sweep<K, E, 8, 10>), grid, block, 0, s, ps, io, base, next, status, ticket, stall);
+      hipLaunchKernelGGL((k_part_sweep<K, E, 8, 10>), grid, block, 0, s, ps, io, base, next, status, ticket, limit);
   }
 }
 
@@ -361,12 +361,12 @@ vx_status part_sweep(vx_ctx* ctx, const PartSpec& ps, const PartIO& io, uint8_t*
   VX_CHECK((io.n + 2047) / 2048 < (1ull << 31), VX_EINVAL, "partition: %llu rows in one launch", (unsigned long long)io.n);
   uint32_t* ticket = (uint32_t*)work;
   unsigned long long* status = (unsigned long long*)(work + 64);
-  uint32_t* stall = stall_word(ctx);
+  const LookLimit limit = look_limit(ctx);
   bool wide = io.key_size == 8;
   for (uint32_t c = 0; c < io.n_pay; ++c) wide |= io.out_pay[c] && io.pay_size[c] == 8;
-  if (io.key_size == 8) launch_sweep<int64_t, 8>(ps, io, base, next, status, ticket, stall, s);
-  else if (wide) launch_sweep<int32_t, 8>(ps, io, base, next, status, ticket, stall, s);
-  else launch_sweep<int32_t, 4>(ps, io, base, next, status, ticket, stall, s);
+  if (io.key_size == 8) launch_sweep<int64_t, 8>(ps, io, base, next, status, ticket, limit, s);
+  else if (wide) launch_sweep<int32_t, 8>(ps, io, base, next, status, ticket, limit, s);
+  else launch_sweep<int32_t, 4>(ps, io, base, next, status, ticket, limit, s);
   VX_HIP(hipGetLastError());
   return VX_OK;
 }

@@ -345,15 +345,18 @@ template <typename K, uint32_t ITEMS>
 __global__ void __launch_bounds__(kDigitThreads) k_digit_sweep(const K* in, K* out, uint64_t n, uint32_t pass,
                                                               const unsigned long long* base,
                                                               unsigned long long* status, uint32_t* tickets,
-                                                              uint32_t* stall) {
+                                                              LookLimit limit) {
   constexpr uint32_t TILE = kDigitThreads * ITEMS;
   __shared__ K stage[TILE];
   __shared__ uint32_t cnt[kDigitWaves][256];
   __shared__ uint32_t wsum[4];
   __shared__ unsigned long long gbase[256];
-  __shared__ uint32_t ticket;
+  __shared__ uint32_t ticket, lost;
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (threadIdx.x == 0) ticket = atomicAdd(tickets + pass, 1u);
+  if (threadIdx.x == 0) {
+    ticket = atomicAdd(tickets + pass, 1u);
+    lost = 0;
+  }
   for (uint32_t i = threadIdx.x; i < kDigitWaves * 256; i += kDigitThreads) (&cnt[0][0])[i] = 0;
   __syncthreads();
   const uint64_t t = ticket;
@@ -386,12 +389,15 @@ __global__ void __launch_bounds__(kDigitThreads) k_digit_sweep(const K* in, K* o
       if (FULL || first + j * 64 < n) stage[cnt[wave][digit_of(k[j], pass)] + rank[j]] = k[j];
     if (threadIdx.x < 256) {
       if (t != 0) {
-        pos = look_back(status + threadIdx.x, 256, t, pass, stall);
+        pos = look_back(status + threadIdx.x, 256, t, pass, limit);
         look_store(status + t * 256 + threadIdx.x, 2 * pass + 2, pos + tot);
       }
       gbase[threadIdx.x] = pos - e;
+      // only where an earlier pass gave up a wait: the keys are then not those that the bases count
+      if (pos + tot > n) lost = 1;
     }
     __syncthreads();
+    if (lost) return;
     const uint32_t m = FULL ? TILE : (uint32_t)(n - t * TILE);
 #pragma unroll
     for (uint32_t j = 0; j < ITEMS; ++j) {
@@ -525,11 +531,11 @@ struct SweepScratch {
 // alternate between dst and alt so that the last one writes dst.  With an even number the first
 // writes alt, so src may be dst; with an odd number src may be alt.  The digit counts of
 // k_sweep_count sit in the buffer that the first pass writes.  scratch holds sweep_bytes(rows);
-// *stall is the context's stall word.
+// limit is the context's.
 // *launches grows by the launches made.
 template <typename K>
 vx_status radix_sort_keys(const K* src, K* alt, K* dst, uint64_t rows, uint32_t passes, uint8_t* scratch,
-                          uint32_t* stall, uint64_t* launches, hipStream_t s) {
+                          LookLimit limit, uint64_t* launches, hipStream_t s) {
   VX_CHECK(rows < (1ull << 44), VX_EINVAL, "sort: run of %llu keys is too long", (unsigned long long)rows);
   if (rows <= kLocalSortMax) {
     hipLaunchKernelGGL(k_local_sort<K>, dim3(1), dim3(1024), 0, s, src, dst, (uint32_t)rows);
@@ -552,16 +558,16 @@ vx_status radix_sort_keys(const K* src, K* alt, K* dst, uint64_t rows, uint32_t 
     const dim3 grid((unsigned)tiles), block(kDigitThreads);
     switch (tile) {
       case 2048:
-        hipLaunchKernelGGL((k_digit_sweep<K, 2>), grid, block, 0, s, in, out, rows, p, w.base, w.status, w.tickets, stall);
+        hipLaunchKernelGGL((k_digit_sweep<K, 2>), grid, block, 0, s, in, out, rows, p, w.base, w.status, w.tickets, limit);
         break;
       case 4096:
-        hipLaunchKernelGGL((k_digit_sweep<K, 4>), grid, block, 0, s, in, out, rows, p, w.base, w.status, w.tickets, stall);
+        hipLaunchKernelGGL((k_digit_sweep<K, 4>), grid, block, 0, s, in, out, rows, p, w.base, w.status, w.tickets, limit);
         break;
       case 8192:
-        hipLaunchKernelGGL((k_digit_sweep<K, 8>), grid, block, 0, s, in, out, rows, p, w.base, w.status, w.tickets, stall);
+        hipLaunchKernelGGL((k_digit_sweep<K, 8>), grid, block, 0, s, in, out, rows, p, w.base, w.status, w.tickets, limit);
         break;
       default:
-        hipLaunchKernelGGL((k_digit_sweep<K, 16>), grid, block, 0, s, in, out, rows, p, w.base, w.status, w.tickets, stall);
+        hipLaunchKernelGGL((k_digit_sweep<K, 16>), grid, block, 0, s, in, out, rows, p, w.base, w.status, w.tickets, limit);
         break;
     }
     VX_HIP(hipGetLastError());
@@ -572,10 +578,10 @@ vx_status radix_sort_keys(const K* src, K* alt, K* dst, uint64_t rows, uint32_t 
 }
 
 vx_status radix_sort_run(const void* src, void* alt, void* dst, uint64_t rows, uint32_t ks, uint8_t* scratch,
-                         uint32_t* stall, uint64_t* launches, hipStream_t s) {
+                         LookLimit limit, uint64_t* launches, hipStream_t s) {
   if (ks == 8)
-    return radix_sort_keys((const int64_t*)src, (int64_t*)alt, (int64_t*)dst, rows, 8, scratch, stall, launches, s);
-  return radix_sort_keys((const int32_t*)src, (int32_t*)alt, (int32_t*)dst, rows, 4, scratch, stall, launches, s);
+    return radix_sort_keys((const int64_t*)src, (int64_t*)alt, (int64_t*)dst, rows, 8, scratch, limit, launches, s);
+  return radix_sort_keys((const int32_t*)src, (int32_t*)alt, (int32_t*)dst, rows, 4, scratch, limit, launches, s);
 }
 
 uint64_t align_to(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
@@ -614,7 +620,7 @@ vx_status sort_impl(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {
   auto pass1_bytes = [&](uint64_t rows) { return 5 * align_to(rows * ks, 256) + sweep_bytes(rows) + (1ull << 20); };
   // a device column that is one run is sorted where it lies and needs one buffer beside it
   const uint64_t direct_bytes = align_to(n * ks, 256) + sweep_bytes(n) + 256;
-  uint32_t* stall_dev = stall_word(ctx);
+  const LookLimit limit = look_limit(ctx);
   uint64_t C = d->chunk_rows;
   if (!C && kc.where == Where::Device && direct_bytes <= ctx->arena.largest_free()) C = n;
   if (!C) {
@@ -652,7 +658,7 @@ vx_status sort_impl(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {
     auto direct = [&]() -> vx_status {
       VX_CHECK(e0 && e1, VX_EHIP, "sort: no HIP event");
       VX_HIP(hipEventRecord(e0, ctx->compute));
-      VX_TRY(radix_sort_run(out_dev, blk.p, out_dev, n, ks, blk.p + align_to(n * ks, 256), stall_dev, &launches,
+      VX_TRY(radix_sort_run(out_dev, blk.p, out_dev, n, ks, blk.p + align_to(n * ks, 256), limit, &launches,
                             ctx->compute));
       VX_HIP(hipEventRecord(e1, ctx->compute));
       return VX_OK;
@@ -693,7 +699,7 @@ vx_status sort_impl(vx_ctx* ctx, const vx_sort_desc* d, vx_stats* stats) {
       kev.push_back(e0);
       kev.push_back(e1);
       VX_HIP(hipEventRecord(e0, ctx->compute));
-      VX_TRY(radix_sort_run(src, alt, stage[b], v.rows, ks, scratch, stall_dev, &launches, ctx->compute));
+      VX_TRY(radix_sort_run(src, alt, stage[b], v.rows, ks, scratch, limit, &launches, ctx->compute));
       VX_HIP(hipEventRecord(e1, ctx->compute));
       VX_HIP(hipEventRecord(sorted_ev[b], ctx->compute));
       // a single run is the result: store it in place; otherwise to its rows of the scratch
@@ -894,7 +900,7 @@ vx_status sort_keys_i64(vx_ctx* ctx, long long* a, long long* b, uint64_t rows, 
   int64_t *src = (int64_t*)a, *other = (int64_t*)b;
   int64_t* dst = passes % 2 ? other : src;
   *sorted = (long long*)dst;
-  return radix_sort_keys(src, passes % 2 ? src : other, dst, rows, passes, scratch, stall_word(ctx), &launches, s);
+  return radix_sort_keys(src, passes % 2 ? src : other, dst, rows, passes, scratch, look_limit(ctx), &launches, s);
 }
 
 }  // namespace vx

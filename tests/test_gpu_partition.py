@@ -617,3 +617,23 @@ def test_whole_column_sample_needs_only_its_keys(gpu):
     ids = torch.searchsorted(spl, key, right=True)
     assert np.array_equal(r["hist"], torch.bincount(ids, minlength=len(spl) + 1).cpu().numpy().astype(np.uint64))
     assert r["hist"].max() <= 1.001 * n / P + 2      # the quantiles of the column itself
+
+
+@pytest.mark.parametrize("host", [False, True])
+def test_partition_gives_up_a_wait(gpu, ctx, host, monkeypatch):
+    """A sweep whose tiles give up their wait at once: the call fails (its rows stay inside the outputs)
+    and the next one is right."""
+    n, P = 4_000_037, 256
+    key = _keys(n, 9)
+    k = pinned(gpu, key) if host else dev(key)
+    ok = _torch_empty_like(key)
+    want = _expect(oracle.part_ids_hash(key, 8), P, key, [])
+    run = lambda: ctx.partition(k, method="radix_hash", n_parts=P, out_key=ok)   # noqa: E731
+    monkeypatch.setenv("VX_LOOK_POLLS", "0")
+    _say("partition gives up", host)
+    with pytest.raises(gpu.VxError) as e:
+        run()
+    assert e.value.status == gpu.VX_EHIP and "partition: a tile waited too long" in str(e.value)
+    monkeypatch.delenv("VX_LOOK_POLLS")
+    run()
+    assert np.array_equal(ok.cpu().numpy(), want[2])

@@ -195,3 +195,32 @@ def test_sort_merge_rounds_full_launches(gpu, ctx, dtype, n, chunk):
                 ctx.sort(d, chunk_rows=chunk)
                 got = d.cpu().numpy()
             assert np.array_equal(got, np.sort(k))
+
+
+@pytest.mark.parametrize("dtype", [np.int32, np.int64])
+@pytest.mark.parametrize("where", ["device", "host"])
+def test_sort_gives_up_a_wait(gpu, ctx, dtype, where, monkeypatch):
+    """A digit pass whose tiles give up their wait at once: the call fails (no store leaves the run,
+    although the passes that follow read keys that the counts do not hold) and the next one is right."""
+    import torch
+    k = _keys(3_000_001, dtype, 5)
+
+    def run():
+        if where == "device":
+            t = torch.from_numpy(k.copy()).cuda()
+            ctx.sort(t)
+            return t.cpu().numpy()
+        h = pinned(gpu, k)
+        try:
+            ctx.sort(h, chunk_rows=700_001)
+            return h.array.copy()
+        finally:
+            h.free()
+
+    monkeypatch.setenv("VX_LOOK_POLLS", "0")
+    _say("sort gives up", dtype.__name__, where)
+    with pytest.raises(gpu.VxError) as e:
+        run()
+    assert e.value.status == gpu.VX_EHIP and "sort: a tile waited too long" in str(e.value)
+    monkeypatch.delenv("VX_LOOK_POLLS")
+    assert np.array_equal(run(), np.sort(k))
