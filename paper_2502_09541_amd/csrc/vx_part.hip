@@ -157,6 +157,7 @@ __global__ void __launch_bounds__(kSweepThreads, 4) k_part_sweep(PartSpec ps, Pa
   __shared__ uint32_t tile_no;
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, P = ps.n_parts;
   if (threadIdx.x == 0) tile_no = atomicAdd(ticket, 1u);
+  look_ready(limit);
   if (ps.fn == kPartRange)
     for (uint32_t j = threadIdx.x; j < ps.n_split; j += THREADS) ((long long*)stage)[j] = ps.splitters[j];
   for (uint32_t i = threadIdx.x; i < WAVES * MAXP / 2; i += THREADS) ((uint32_t*)&cnt[0][0])[i] = 0;

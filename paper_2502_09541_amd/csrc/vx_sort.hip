@@ -357,6 +357,7 @@ __global__ void __launch_bounds__(kDigitThreads) k_digit_sweep(const K* in, K* o
     ticket = atomicAdd(tickets + pass, 1u);
     lost = 0;
   }
+  look_ready(limit);
   for (uint32_t i = threadIdx.x; i < kDigitWaves * 256; i += kDigitThreads) (&cnt[0][0])[i] = 0;
   __syncthreads();
   const uint64_t t = ticket;
