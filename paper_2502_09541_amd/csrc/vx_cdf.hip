@@ -545,6 +545,7 @@ vx_status cdf_splitters(vx_ctx* ctx, const ColInfo& key, uint64_t n, const vx_pa
   VX_HIP(hipMemcpyAsync(&ends[0], sorted, 8, hipMemcpyDeviceToHost, s));
   VX_HIP(hipMemcpyAsync(&ends[1], sorted + m - 1, 8, hipMemcpyDeviceToHost, s));
   VX_HIP(hipStreamSynchronize(s));
+  VX_TRY(check_stall(ctx, "cdf sample sort"));
   double t2 = now_ms();
   rep->sort_ms = t2 - t1;
   // feature scale: 1 / (L * 2^23), L = floor(log2(range + 1)) + 1 over the sample's key range

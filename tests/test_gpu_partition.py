@@ -637,3 +637,23 @@ def test_partition_gives_up_a_wait(gpu, ctx, host, monkeypatch):
     monkeypatch.delenv("VX_LOOK_POLLS")
     run()
     assert np.array_equal(ok.cpu().numpy(), want[2])
+
+
+def test_sample_sort_gives_up_a_wait(gpu, ctx, monkeypatch):
+    """The sort of the splitters' sample gives up its waits: that is the call's error, before any splitter is taken
+    from the keys it left, and nothing is left over for the next call."""
+    key = _keys(300_007, 31)
+    k = dev(key)
+    spl = ctx.partition(k, method="quantile", n_parts=64, sample_frac=1.0)["splitters"]
+    monkeypatch.setenv("VX_LOOK_POLLS", "0")
+    for call in (lambda: ctx.partition(k, method="quantile", n_parts=64, sample_frac=1.0),
+                 lambda: ctx.join_partitioned(k, [], k, method="quantile", n_parts=64, sample_frac=1.0)):
+        _say("sample sort gives up")
+        with pytest.raises(gpu.VxError) as e:
+            call()
+        assert e.value.status == gpu.VX_EHIP and "cdf sample sort: a tile waited too long" in str(e.value)
+    monkeypatch.delenv("VX_LOOK_POLLS")
+    t = dev(key)
+    ctx.sort(t)
+    assert np.array_equal(t.cpu().numpy(), np.sort(key))
+    assert np.array_equal(ctx.partition(k, method="quantile", n_parts=64, sample_frac=1.0)["splitters"], spl)
