@@ -962,6 +962,20 @@ vx_status key_range(vx_ctx* ctx, int32_t key_type, const void* dev_keys, uint64_
   return VX_OK;
 }
 
+// The duplicate check of a direct or dense table of n rows: its filled slots (presence bytes) against them.
+// The counters (kFlagCount) start at zero.
+static void launch_count(vx_ctx* ctx, const vx_table* t, uint64_t n, hipStream_t s) {
+  unsigned long long* cnt = (unsigned long long*)((uint8_t*)ctx->dev_flags + kFlagCount);
+  const unsigned g = grid_for(ctx, t->view.direct_range, 256 * 16, 2);
+  if (t->view.direct == kLayoutDense)
+    hipLaunchKernelGGL(k_dense_count, dim3(g), dim3(256), 0, s, (const uint8_t*)t->view.present, t->view.direct_range, cnt,
+                       n, ctx->dev_flags);
+  else if (t->key_type == VX_I64)
+    hipLaunchKernelGGL(k_direct_count<int64_t>, dim3(g), dim3(256), 0, s, t->view, cnt, n, ctx->dev_flags);
+  else
+    hipLaunchKernelGGL(k_direct_count<int32_t>, dim3(g), dim3(256), 0, s, t->view, cnt, n, ctx->dev_flags);
+}
+
 vx_status table_insert(vx_ctx* ctx, vx_table* t, const ColInfo& key, const ColInfo* pays,
                        uint64_t n, hipStream_t s, int group_lanes, bool cleared, bool count) {
   if (n == 0) return VX_OK;
@@ -976,33 +990,19 @@ vx_status table_insert(vx_ctx* ctx, vx_table* t, const ColInfo& key, const ColIn
     unsigned g = grid_for(ctx, n, kPreaggTile, 3);
     if (k64) hipLaunchKernelGGL(k_build_preagg<int64_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
     else hipLaunchKernelGGL(k_build_preagg<int32_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
-  } else if (t->view.direct == kLayoutDense) {
-    VX_CHECK(t->n_rows == 0, VX_EINVAL, "build: a dense table takes its rows in one insert");
-    unsigned long long* cnt = (unsigned long long*)((uint8_t*)ctx->dev_flags + kFlagCount);
-    if (!cleared) fill_zero((uint64_t*)cnt, 2, s);
-    const unsigned g = grid_for(ctx, n, 256, 8);
-    const unsigned gc = grid_for(ctx, t->view.direct_range, 256 * 16, 2);
-    if (k64) hipLaunchKernelGGL(k_build_dense<int64_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
-    else hipLaunchKernelGGL(k_build_dense<int32_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
-    if (count)
-      hipLaunchKernelGGL(k_dense_count, dim3(gc), dim3(256), 0, s, (const uint8_t*)t->view.present, t->view.direct_range,
-                       cnt, n, ctx->dev_flags);
   } else if (t->view.direct) {
-    // one insert per direct table: the duplicate check counts every slot against every row
+    // one insert per direct or dense table: the duplicate check counts every slot against every row
     VX_CHECK(t->n_rows == 0, VX_EINVAL, "build: a direct table takes its rows in one insert");
-    unsigned long long* cnt = (unsigned long long*)((uint8_t*)ctx->dev_flags + kFlagCount);
-    if (!cleared) fill_zero((uint64_t*)cnt, 2, s);
+    if (!cleared) fill_zero((uint64_t*)((uint8_t*)ctx->dev_flags + kFlagCount), 2, s);
     const unsigned g = grid_for(ctx, n, 256, 8);
-    const unsigned gc = grid_for(ctx, t->view.direct_range, 256 * 16, 2);
-    if (k64) {
-      hipLaunchKernelGGL(k_build_direct<int64_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
-      if (count)
-        hipLaunchKernelGGL(k_direct_count<int64_t>, dim3(gc), dim3(256), 0, s, t->view, cnt, n, ctx->dev_flags);
+    if (t->view.direct == kLayoutDense) {
+      if (k64) hipLaunchKernelGGL(k_build_dense<int64_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
+      else hipLaunchKernelGGL(k_build_dense<int32_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
     } else {
-      hipLaunchKernelGGL(k_build_direct<int32_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
-      if (count)
-        hipLaunchKernelGGL(k_direct_count<int32_t>, dim3(gc), dim3(256), 0, s, t->view, cnt, n, ctx->dev_flags);
+      if (k64) hipLaunchKernelGGL(k_build_direct<int64_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
+      else hipLaunchKernelGGL(k_build_direct<int32_t>, dim3(g), dim3(256), 0, s, t->view, c, n, ctx->dev_flags);
     }
+    if (count) launch_count(ctx, t, n, s);
   } else {
     unsigned g = grid_for(ctx, n, 256, 8);
     switch (group_lanes) {
@@ -1069,10 +1069,22 @@ static void launch_probe_as(const vx_table* t, const ProbeCols& q, unsigned long
     launch_probe_count<K, LAYOUT, false>(t, q, acc, s, g, f);
 }
 
+static unsigned probe_groups(vx_ctx* ctx, uint64_t rows) { return grid_for(ctx, rows, 256 * 4, 8); }
+
+// Whether a probe launch over `rows` rows counts the build's slots as well.  Its workgroups share them, and
+// few read slowly (a table of 268 MB took 48 ms on one): a launch of its own then costs less, some 6 us.  The
+// line is where the two meet: 32 KiB for each workgroup at 5 GB/s, or two workgroups per compute unit, which
+// read at the memory's rate.
+static bool probe_counts(vx_ctx* ctx, const vx_table* t, uint64_t rows) {
+  const uint64_t bytes = t->view.direct == kLayoutDense ? t->view.direct_range : t->view.direct_range << t->view.slot_shift;
+  const uint64_t groups = probe_groups(ctx, rows);
+  return groups >= 2ull * ctx->cu_count || bytes <= groups << 15;
+}
+
 static vx_status launch_probe(vx_ctx* ctx, const vx_table* t, const ProbeCols& q,
                               unsigned long long* acc, hipStream_t s, const RowsOut* ro, const ProbeFinish& f) {
   if (q.n == 0) return VX_OK;
-  const unsigned g = grid_for(ctx, q.n, 256 * 4, 8);
+  const unsigned g = probe_groups(ctx, q.n);
   const bool k64 = t->key_type == VX_I64;
   switch (t->view.direct) {
     case kLayoutDense:
@@ -1114,7 +1126,8 @@ static bool choose_zero_copy(int32_t late_mat, double sel, uint64_t rows, uint64
 // What a one-shot join's build left to its probe.
 struct Deferred {
   bool flags = false;         // the build's error flags are unread: read with the results
-  bool count = false;         // the duplicate check of a direct or dense table is not made: the probe makes it
+  bool count = false;         // the duplicate check of a direct or dense table is not made: the first probe launch
+                              // makes it, or one of its own beside it (probe_counts)
   bool acc_cleared = false;   // the accumulators and tickets of a publishing launch are zero
 };
 
@@ -1188,6 +1201,7 @@ vx_status probe_impl(vx_ctx* ctx, const vx_table* t, const vx_probe_desc* d, vx_
     rows->n_out = 0;
   }
 
+  bool counted = false;   // the probe has counted the build's slots
   uint32_t zc_shift = 0;
   while ((2u << zc_shift) <= ctx->zc_line) ++zc_shift;   // log2 of the measured granule
   const bool count_zc = (d->flags & VX_PROBE_COUNT_ZC) != 0;
@@ -1218,7 +1232,11 @@ vx_status probe_impl(vx_ctx* ctx, const vx_table* t, const vx_probe_desc* d, vx_
     }
     q.zc_shift = zc_shift;
     ProbeFinish f{};
-    f.count = build.count && v.index == 0;
+    if (build.count && v.index == 0) {
+      counted = probe_counts(ctx, t, v.rows);
+      f.count = counted;
+      if (!counted) launch_count(ctx, t, t->n_rows, ctx->compute);
+    }
     if (publish) {
       f.publish = 1;
       f.host = (unsigned long long*)ctx->host_acc_dev;
@@ -1261,7 +1279,7 @@ vx_status probe_impl(vx_ctx* ctx, const vx_table* t, const vx_probe_desc* d, vx_
       std::memcpy(&build_flags, ctx->host_small, 4);
       side = ctx->host_small[1];
     }
-    if (build.count) {   // fewer filled slots than rows: two rows shared a key
+    if (counted) {   // fewer filled slots than rows: two rows shared a key
       uint64_t filled = t->view.direct == kLayoutDirect ? side : 0;
       for (uint64_t r = 0; r < acc_rows; ++r) filled += ctx->host_acc[r * kAccWords + kGranuleWord];
       if (filled != t->n_rows) build_flags |= kFlagDup;
@@ -1318,7 +1336,7 @@ vx_status probe_impl(vx_ctx* ctx, const vx_table* t, const vx_probe_desc* d, vx_
 
 // defer (one-shot joins): leave the build's error flags for the probe to read with its own results
 // (one host round trip less), and with `fold` the duplicate check of a direct or dense table for it
-// to make beside its own work; the table is returned even if they will show a repeated key.
+// to make; the table is returned even if they will show a repeated key.
 vx_status build_impl(vx_ctx* ctx, const vx_build_desc* d, vx_table** out, double* ms, Deferred* defer, bool fold) {
   double t0 = now_ms();
   VX_CHECK(d != nullptr && out != nullptr, VX_EINVAL, "vx_build: null argument");

@@ -273,3 +273,52 @@ def test_preaggregated_build_tiles(gpu, ctx, kt, rows, keys):
         for hashed in (False, True):
             got = ctx.join_plain(dev(bk), [dev(p) for p in bps], dev(pk), [], unique=False, hashed=hashed)[0]
             assert got == oracle.join_agg(bk, bps, pk, [])
+
+
+@pytest.mark.parametrize("kt", [np.int32, np.int64])
+@pytest.mark.parametrize("step", [1, 2])
+@pytest.mark.parametrize("probe,chunk", [(1, 0), (1000, 0), (40_000, 0), (300_000, 0), (5000, 7), (300_000, 2048)])
+def test_duplicate_check_beside_a_small_probe(gpu, ctx, kt, step, probe, chunk):
+    """Dense (step 1) and direct (step 2) one-shot builds under probes of a workgroup to hundreds, in one launch and
+    in chunks from host memory: results against the oracle, and a repeated key is found whoever counts the slots."""
+    rng = np.random.default_rng(probe + step)
+    n = 1_000_003
+    bk = (rng.permutation(n) * step).astype(kt)
+    bp = rng.integers(-1000, 1000, n).astype(np.int32)
+    pk = rng.integers(0, 2 * step * n, probe).astype(kt)
+    p = pinned(gpu, pk) if chunk else dev(pk)
+    _say("small probe", kt.__name__, step, probe, chunk)
+    got, st = ctx.join_plain(dev(bk), [dev(bp)], p, chunk_rows=chunk)
+    assert got == oracle.join_agg(bk, [bp], pk, [])
+    for i, j in ((0, n - 1), (n // 2, n // 2 + 1)):
+        bad = bk.copy()
+        bad[i] = bad[j]
+        with pytest.raises(gpu.VxError) as e:
+            ctx.join_plain(dev(bad), [dev(bp)], p, chunk_rows=chunk)
+        assert e.value.status == gpu.VX_EDUPKEY
+
+
+@pytest.mark.parametrize("step", [1, 2])
+def test_small_probe_of_a_large_build_costs_the_build(gpu, step):
+    """A one-shot join of 2^24 build rows and one probe row takes about the time of the build alone; four times it
+    is the limit (a duplicate check left to the probe's one workgroup took 7 and 50 times it)."""
+    import time
+
+    import torch
+    n = 1 << 24
+    bk = (torch.randperm(n, device="cuda") * step).to(torch.int32)
+    pk = bk[:1].clone()
+    _say("large build, one probe row", step)
+    with gpu.Context(1 << 30) as c:
+        def least(f):
+            ts = []
+            for _ in range(5):
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                f()
+                ts.append(time.perf_counter() - t)
+            return min(ts)
+        build = least(lambda: c.build(bk, [bk]).destroy())
+        join = least(lambda: c.join_plain(bk, [bk], pk))
+    print("build", build, "join", join, flush=True)
+    assert join < 4 * build
