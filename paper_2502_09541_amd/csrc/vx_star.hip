@@ -405,6 +405,11 @@ vx_status join_star(vx_ctx* ctx, const vx_star_join* d, vx_join_out* out) {
       VX_TRY(make_table(ctx, ktype, VX_UNIQUE, pt, sd.group.data ? 1 : 0, sd.n, 0.5f, &dims[k].t, &dims[k].range,
                         &fills));
       s.table_bytes += dims[k].t->bytes;
+    }
+    // the presence bytes after every table: they go again before the group table and the chunk buffers are
+    // made, which may need the room in one piece
+    for (uint32_t k = k0; k < k1; ++k) {
+      const vx_star_dim& sd = d->dims[k];
       const TableView& v = dims[k].t->view;
       if (v.direct && !tight) {
         const uint64_t bytes = (v.direct_range + 255) / 256 * 256;

@@ -191,6 +191,23 @@ def test_star_dimension_builds(gpu, tight, dup, key_dtype):
         c.close()
 
 
+@pytest.mark.parametrize("slack", [0, 1 << 19, 1 << 20])
+def test_star_presence_bytes_leave_the_arena_whole(gpu, slack):
+    """Direct dimensions in an arena that holds their tables (4 MiB each), the context's scratch and a group table
+    of 8 MiB in one piece: the presence bytes (512 KiB a dimension) that go before it must not lie between them."""
+    rng = np.random.default_rng(29)
+    n = 1 << 19
+    dims = [dict(key=rng.permutation(n).astype(np.int32), filt=rng.integers(0, 4, n).astype(np.int32), lo=0, hi=2,
+                 group=rng.integers(0, 300, n).astype(np.int32)) for _ in range(4)]
+    fks = [rng.integers(0, n + 9, 20_000).astype(np.int32) for _ in dims]
+    meas = [rng.integers(-1000, 1000, 20_000).astype(np.int32)]
+    scratch, table, group = (10 << 17) + 256, (8 * n) + 256, 64 * ((1 << 17) + 4)
+    _say("star: presence bytes", slack)
+    with gpu.Context(scratch + 4 * table + group + slack) as c:
+        got = c.join_star(_dev_dims(dims), [dev(f) for f in fks], [dev(m) for m in meas], groups_cap=1 << 16)
+    _check(got, oracle.star_groupby(dims, fks, meas))
+
+
 def test_star_full_size_dense_closed_form(gpu):
     """Full size: 600,000,000 fact rows (16.8 GB pinned), dimensions of 2,556 / 200,000 /
     3,000,000 / 2,000,000 rows.  Expected groups from direct-array lookups (dense dimension keys),
