@@ -609,7 +609,7 @@ def test_whole_column_sample_needs_only_its_keys(gpu):
     n, P = 20_000_003, 1024
     g = torch.Generator(device="cuda").manual_seed(23)
     key = torch.randint(-2**62, 2**62, (n,), generator=g, device="cuda")
-    budget = 24 * n + (16 << 20) + (8 << 20)   # the context's scratch and the model's: under 8 MiB
+    budget = 24 * n + (16 << 20) + (3 << 20)   # the context's scratch and the model's: under 3 MiB
     _say("whole-column sample", n, P)
     with gpu.Context(budget) as c:
         r = c.partition(key, method="quantile", n_parts=P, sample_frac=1.0)
