@@ -639,9 +639,17 @@ uint64_t segments(const Side& sd, uint32_t P, uint32_t p, std::vector<unsigned l
   return tot;
 }
 
+// Waits for everything the context has in flight, so that its arena memory can be given out again.
+void drain(vx_ctx* ctx) {
+  for (hipStream_t s : {ctx->compute, ctx->copy, ctx->d2h}) (void)hipStreamSynchronize(s);
+}
+
 }  // namespace
 
-vx_status join_partitioned(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_out* out) {
+// mode: where the clustered build side lives (0 host, 1 device, 2 planned); *planned_device: the plan chose
+// the device.
+static vx_status partitioned_placed(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_out* out, uint64_t mode,
+                                    bool* planned_device) {
   double t0 = now_ms();
   const vx_build_desc& B = d->build;
   const vx_probe_desc& Q = d->probe;
@@ -727,7 +735,6 @@ vx_status join_partitioned(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_ou
   for (uint32_t c = 0; c < B.n_pay; ++c) hbytes += align_up(B.n * bs.pay[c].elsize, 256);
   double plan_compact = 0;   // expected bytes of the compact tables (0: no prediction)
   {
-    const uint64_t mode = env_u64("VX_PJ_DEVICE", 2);   // 0 host, 1 device, 2 planned
     bool fits = false;
     if (ps.fn == kPartRange && rep.sample_rows > 0) {
       const double ns_rows = (double)B.n * (1.0 - rep.single_share);
@@ -752,6 +759,7 @@ vx_status join_partitioned(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_ou
                 ctx->arena.largest_free() / 1073741824.0, fits ? "fits" : "does not fit");
     }
     bs.on_device = mode == 1 || (mode == 2 && fits);
+    *planned_device = mode == 2 && fits;
   }
   ArenaBlock cl_mem;
   uint8_t* hs = nullptr;
@@ -1116,6 +1124,18 @@ vx_status join_partitioned(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_ou
   return VX_OK;
 }
 
+vx_status join_partitioned(vx_ctx* ctx, const vx_partitioned_join* d, vx_join_out* out) {
+  const uint64_t mode = env_u64("VX_PJ_DEVICE", 2);
+  bool planned_device = false;
+  vx_status st = partitioned_placed(ctx, d, out, mode, &planned_device);
+  // the plan rests on a sample: where the rows turn out not to fit beside their clustered copy, it goes to
+  // host memory after all
+  if (st == VX_EBUDGET && planned_device) {
+    drain(ctx);
+    st = partitioned_placed(ctx, d, out, 0, &planned_device);
+  }
+  return st;
+}
 
 // ---------------------------------------------------------------- two-table radix join
 

@@ -115,6 +115,28 @@ def test_skew_small_budget_table_groups(gpu, skew, monkeypatch):
     assert st["sdma_bytes"] >= 2 * NP * 8                   # at least two passes over the probe keys
 
 
+def test_sample_that_misses_the_keys(gpu):
+    """A sample that shows one key where the other rows hold 500,000: the plan expects tiny tables and keeps the
+    clustered copy in the arena, where the largest partition's table does not fit beside it.  The join then takes
+    the host plan, which fits in every one of these arenas."""
+    na, seed, frac = 4_000_000, 3, float(np.float32(1e-4))
+    key = np.arange(na, dtype=np.int64) % 500_000 + 10
+    key[oracle.sample_bernoulli(np.arange(na, dtype=np.int64), seed, frac)] = 5
+    rng = np.random.default_rng(1)
+    pay, pk = rng.integers(0, 1 << 40, na), rng.integers(0, 600_000, 1_000_003)
+    exp = oracle.join_agg(key, [pay], pk, [])
+    H = [_pinned(gpu, a) for a in (key, pay, pk)]
+    for budget in (425 << 20, 440 << 20, 465 << 20):
+        _say("sample misses the keys", budget)
+        with gpu.Context(budget) as c:
+            got, st, used = c.join_partitioned(H[0], [H[1]], H[2], method="quantile", n_parts=4, seed=seed,
+                                               sample_frac=1e-4)
+        assert got == exp
+        assert st["zc_bytes"] > 0      # read back from host memory
+    for h in H:
+        h.free()
+
+
 # ----------------------------------------------------------------------------- full size
 
 def _chunked(n, step=1 << 27):
