@@ -820,8 +820,8 @@ static vx_status partitioned_placed(vx_ctx* ctx, const vx_partitioned_join* d, v
                              (uint64_t)P * sizeof(PjJob) / 8;
   const uint64_t chunk_bytes = env_u64("VX_CHUNK_BYTES", 64ull << 20) + 256;
   const uint64_t probe_buffers = Q.n_buffers ? Q.n_buffers : std::max<uint64_t>(2, env_u64("VX_BUFFERS", 2));
-  const uint64_t probe_bytes = qs.key.where != Where::Host ? 0
-                               : probe_buffers * (std::max<uint64_t>(chunk_bytes, std::min(Q.chunk_rows, Q.n) * ks) + 512);
+  const uint64_t buffer_bytes = std::max<uint64_t>(chunk_bytes, std::min(Q.chunk_rows, Q.n) * ks) + 512;
+  const uint64_t probe_bytes = qs.key.where != Where::Host ? 0 : probe_buffers * buffer_bytes;
   const bool build_all = ctx->arena.largest_free() >= all_bytes + aux_words * 8 + (1u << 20) + probe_bytes;
   uint32_t* claims = nullptr;   // slots claimed by a build in the transient table
   if (!build_all) {
@@ -880,10 +880,13 @@ static vx_status partitioned_placed(vx_ctx* ctx, const vx_partitioned_join* d, v
     const double spare = build_all ? (double)(ctx->arena.capacity() - ctx->arena.used()) - (double)(1u << 20)
                                    : (double)(ctx->arena.capacity() - ctx->arena.used()) - 1.05 * plan_compact -
                                          (double)(512u << 20);
-    qbuf = (uint32_t)std::max<double>(2.0, std::min<double>((double)kMaxBuffers, spare / (double)chunk_bytes));
+    qbuf = (uint32_t)std::max<double>(2.0, std::min<double>((double)kMaxBuffers, spare / (double)buffer_bytes));
   }
   Pipeline pipe;
-  VX_TRY(pipe.plan(ctx, Q.n, Q.chunk_rows, qbuf, qcols));
+  vx_status planned = pipe.plan(ctx, Q.n, Q.chunk_rows, qbuf, qcols);
+  // chunks of a given size do not shrink to the arena's holes: as many buffers as fit
+  while (planned == VX_EBUDGET && Q.n_buffers == 0 && qbuf > 2) planned = pipe.plan(ctx, Q.n, Q.chunk_rows, --qbuf, qcols);
+  VX_TRY(planned);
   if (!build_all) {   // compact tables: most of what is left
     cbytes = ctx->arena.largest_free() / 256 * 256;
     cbytes = cbytes > (1u << 20) ? cbytes - (1u << 20) : 0;

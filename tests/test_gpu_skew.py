@@ -137,6 +137,31 @@ def test_sample_that_misses_the_keys(gpu):
         h.free()
 
 
+def test_device_plan_with_given_chunk_rows(gpu, monkeypatch):
+    """Probe chunks larger than the automatic ones: the chunk buffers taken beside the device plan's tables are
+    counted at their own size, so the plan stays on the device."""
+    monkeypatch.setenv("VX_CHUNK_BYTES", str(2 * MiB))
+    rng = np.random.default_rng(8)
+    bk, bp = rng.integers(0, 1 << 40, 1_000_003), rng.integers(0, 1 << 40, 1_000_003)
+    pk = rng.choice(bk, 3_000_001)
+    H = [_pinned(gpu, a) for a in (bk, bp, pk)]
+    d = gpu.JoinDesc()
+    d.kind = gpu.VX_JOIN_PARTITIONED
+    pays, n_pay = gpu._cols([H[1]])
+    d.u.part.build = gpu.BuildDesc(gpu.col(H[0]), pays, n_pay, gpu.VX_PREAGG, len(bk), 0.0, 0)
+    d.u.part.probe = gpu.ProbeDesc(gpu.col(H[2]), None, 0, gpu.VX_LATE_AUTO, len(pk), 1_000_000, 0, 0, None, 0)
+    d.u.part.part.method = gpu.PART_METHODS["quantile"]
+    d.u.part.part.n_parts = 16
+    out = gpu.JoinOut()
+    _say("device plan, given chunk rows")
+    with gpu.Context(512 * MiB) as c:
+        gpu._check(gpu.lib().vx_join_agg(c.h, d, out))
+    assert out.agg.to_list(1) == oracle.join_agg(bk, [bp], pk, [])
+    assert out.stats.chunks == 4 and out.stats.zc_bytes == 0
+    for h in H:
+        h.free()
+
+
 # ----------------------------------------------------------------------------- full size
 
 def _chunked(n, step=1 << 27):
