@@ -1184,7 +1184,9 @@ void whole_side(Side& sd) {
 
 }  // namespace
 
-vx_status join_radix(vx_ctx* ctx, const vx_radix_join* d, vx_join_out* out) {
+// placement: where the clustered tables live (0 chosen, 1 host, 2 device); *chose_device: 0 took the device.
+static vx_status radix_placed(vx_ctx* ctx, const vx_radix_join* d, vx_join_out* out, int32_t placement,
+                              bool* chose_device) {
   const double t0 = now_ms();
   const vx_build_desc& A = d->a;
   const vx_probe_desc& Bd = d->b;
@@ -1253,8 +1255,9 @@ vx_status join_radix(vx_ctx* ctx, const vx_radix_join* d, vx_join_out* out) {
     // (2^24 + 2^24 rows in a 1 GiB arena, two slices a partition: 26.7 -> 13.7 ms).
     const uint64_t pass1_need = 2 * (chunk * rb + 1024) + part_work_bytes(P, chunk) + (32ull << 20);
     const uint64_t pass2_need = table_bytes(exp_rows) / 4 + 2ull * P * 2 * (kMaxSegs + 1) * 8 + (32ull << 20);
-    const bool dev = d->placement == 2 ||
-                     (d->placement == 0 && hA + hB + 512 + std::max(pass1_need, pass2_need) <= free0);
+    const bool dev = placement == 2 ||
+                     (placement == 0 && hA + hB + 512 + std::max(pass1_need, pass2_need) <= free0);
+    *chose_device = placement == 0 && dev;
     as.on_device = bs.on_device = dev;
     uint8_t* base = nullptr;
     if (dev) {
@@ -1477,6 +1480,18 @@ vx_status join_radix(vx_ctx* ctx, const vx_radix_join* d, vx_join_out* out) {
   s.kernel_ms = probe_k_ms;
   s.total_ms = now_ms() - t0;
   return VX_OK;
+}
+
+vx_status join_radix(vx_ctx* ctx, const vx_radix_join* d, vx_join_out* out) {
+  bool chose_device = false;
+  vx_status st = radix_placed(ctx, d, out, d->placement, &chose_device);
+  // the choice counts free bytes, not blocks: in an arena cut up by live tables the clustered tables may need
+  // host memory after all
+  if (st == VX_EBUDGET && chose_device) {
+    drain(ctx);
+    st = radix_placed(ctx, d, out, 1, &chose_device);
+  }
+  return st;
 }
 
 }  // namespace vx

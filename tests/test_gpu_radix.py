@@ -197,3 +197,30 @@ def test_radix_join_errors(gpu, ctx):
     with pytest.raises(gpu.VxError) as e:
         ctx.join_radix(k, [k], k, [k], n_parts=4, placement=3)
     assert e.value.status == gpu.VX_EINVAL
+
+
+def test_radix_join_in_a_divided_arena(gpu, monkeypatch):
+    """Free blocks of 64 and 190 MiB around a live table: together they would hold the clustered tables (200 MiB)
+    and the passes' buffers, neither does alone, and the join takes its host plan."""
+    import torch
+    monkeypatch.setenv("VX_CHUNK_BYTES", str(2 << 20))
+    n = 6_550_000
+    rng = np.random.default_rng(4)
+    ak, bk = rng.permutation(n), rng.integers(0, 2 * n, n)
+    ap, bp = rng.integers(0, 1 << 40, n), rng.integers(0, 1 << 40, n)
+    A, AP, B, BP = (pinned(gpu, x) for x in (ak, ap, bk, bp))
+    _say("radix join, divided arena")
+    with gpu.Context(256 << 20) as c:
+        hole = c.build(torch.arange(1 << 22, device="cuda") * 7919, [], hashed=True)
+        live = c.build(torch.arange(16, device="cuda"), [], hashed=True)
+        hole.destroy()
+        got, st = c.join_radix(A, [AP], B, [BP], n_parts=8)
+        live.destroy()
+    hit = bk < n
+    inv = np.empty(n, np.int64)
+    inv[ak] = ap
+    want = [int(hit.sum()), int(inv[bk[hit]].astype(np.uint64).sum()), int(bp[hit].astype(np.uint64).sum())]
+    assert got == want
+    assert st["zc_bytes"] > 0      # the clustered tables lay in host memory
+    for h in (A, AP, B, BP):
+        h.free()
