@@ -873,13 +873,11 @@ vx_status make_table(vx_ctx* ctx, int32_t key_type, uint32_t flags, const int32_
     fl.pattern(mem, slots_bytes, slot_bytes / 4, ks == 4 ? 0x80000000u : 0u, ks == 4 ? 0u : 0x80000000u, preagg_count0(v));
     fl.zero(v.side, 256);
   }
-  if (!fills) (void)own.launch(ctx->compute);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) {
+  const vx_status st = fills ? VX_OK : own.launch(ctx->compute);
+  if (st != VX_OK) {
     ctx->arena.release(mem);
     delete t;
-    set_error("build: init kernel launch failed: %s", hipGetErrorString(e));
-    return VX_EHIP;
+    return st;
   }
   *out = t;
   return VX_OK;

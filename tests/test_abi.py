@@ -72,3 +72,43 @@ def test_struct_layouts_match_header(tmp_path):
     out = subprocess.run([str(tmp_path / "layout")], check=True, capture_output=True, text=True).stdout
     got = {k: int(v) for k, v in (line.split() for line in out.splitlines())}
     assert got == want
+
+
+def test_failed_fill_launch_fails_the_table(tmp_path):
+    """make_table reports a fill that could not be launched and gives its memory back.  A program links the library
+    and stands in for the runtime's launch, which fails, and for its error state, which a read clears."""
+    import subprocess
+    src = tmp_path / "t.cpp"
+    src.write_text(r"""
+#include <cstdio>
+#include "vx_table.h"
+static hipError_t last = hipSuccess;
+static int launches = 0;
+extern "C" hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+extern "C" hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
+extern "C" hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
+  ++launches;
+  return last = hipErrorOutOfMemory;
+}
+extern "C" hipError_t hipGetLastError() {
+  const hipError_t e = last;
+  last = hipSuccess;
+  return e;
+}
+int main() {
+  vx_ctx ctx;
+  alignas(256) static unsigned char memory[1 << 16];
+  ctx.arena.init(memory, sizeof memory);
+  vx_table* t = nullptr;
+  const vx_status st = vx::make_table(&ctx, VX_I64, VX_UNIQUE, nullptr, 0, 100, 0.5f, &t);
+  std::printf("%d %d %d %llu\n", (int)st, launches, t != nullptr, (unsigned long long)ctx.arena.used());
+}
+""")
+    exe, lib = tmp_path / "t", os.path.dirname(vx.LIB_PATH)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", f"-I{rocm}/include", f"-I{ROOT}/include", f"-I{lib}/csrc",
+                    str(src), "-o", str(exe), vx.LIB_PATH, f"-L{rocm}/lib", "-lamdhip64", f"-Wl,-rpath,{lib}",
+                    f"-Wl,-rpath,{rocm}/lib", "-rdynamic"], check=True)
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1")
+    got = subprocess.run([str(exe)], check=True, capture_output=True, text=True, env=env).stdout.split()
+    assert got == [str(vx.VX_EHIP), "1", "0", "0"]
