@@ -474,11 +474,12 @@ template <typename K, bool WIDE>
 struct ScatterForm {
   static constexpr uint32_t threads = sizeof(K) == 4 ? 1024 : 512, items = WIDE ? 16 : 8, groups = WIDE ? 1 : 2;
 };
-// The mean number of regions of a probe row's job above which rounds are wide.  Graph of 256 jobs, 4.4 G
-// probe rows: direct tables, mean 67: 11.6 ms short, 12.6 wide; hash tables, mean 281 or 345 by load
-// factor: 27.2 short, 24.3 wide.  The line lies between.  The scatter alone, 378 M rows of 64 jobs in up
-// to 32 regions: 467 us short, 614 wide.
-constexpr uint64_t kWideRegions = 128;
+// The number of regions of a probe row's job above which rounds are wide, for 16-bit offsets (jobs built by
+// regions) and for whole keys; a batch goes by the mean over its probe rows of regions / this.  8 jobs, 160 M
+// int32 probe rows, graph in us, short / wide: offsets, 32 regions 526 / 593, 64: 632 / 633, 128: 844 / 783
+// (256 jobs, 4.4 G rows, mean 67: 11.6 ms / 12.6); whole keys, 16 regions 844 / 880, 32: 972 / 961, 64:
+// 906 / 872, 128: 1286 / 1139.
+constexpr double kWideOffsets = 128, kWideKeys = 24;
 
 // Scatter pass: each kept key of super-tile st to its region's array, at the super-tile's
 // position for the region plus its rank.  The super-tile goes in rounds of T ITEMS keys; each
@@ -1120,7 +1121,7 @@ struct BatchPlan {
   std::vector<unsigned long long> cluster_map;
   uint64_t cursor_entries = 0;
   bool tables = false;
-  bool wide_scatter = false;       // see kWideRegions
+  bool wide_scatter = false;       // see kWideOffsets
 };
 
 // Which jobs get a direct table: per caller's job, direct[j] and the smallest key kmin[j]
@@ -1398,11 +1399,11 @@ static vx_status plan_batch(const vx_batch_join* d, const BatchConfig& cfg, int 
   if (regions) plan_regions(pl, ks, slot_bytes, part_budget, stage);
   pl->count_tiles = 0;
   pl->tables = false;
-  uint64_t rows = 0, row_regions = 0;
+  double rows = 0, wide = 0;
   for (BatchJob& b : pl->jobs) {
     if (b.n_parts && !b.in_place) {
-      rows += b.np;
-      row_regions += b.np * b.n_parts;
+      rows += (double)b.np;
+      wide += (double)b.np * b.n_parts / (b.rows ? kWideOffsets : kWideKeys);
     }
     const bool table = b.direct && !b.rows;
     b.ctile0 = pl->count_tiles;
@@ -1410,7 +1411,7 @@ static vx_status plan_batch(const vx_batch_join* d, const BatchConfig& cfg, int 
     pl->count_tiles += b.count_tiles;
     pl->tables |= table;
   }
-  pl->wide_scatter = row_regions > kWideRegions * rows;
+  pl->wide_scatter = wide > rows;
   map_tiles(pl, slot_bytes, l2_bytes);
   return VX_OK;
 }

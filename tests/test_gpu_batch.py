@@ -444,3 +444,27 @@ def test_batch_wide_scatter_rounds(gpu, monkeypatch):
                 got, st = c.join_batch(*args, hashed=hashed, tile_rows=4096, block=256, load_factor=0.5)
                 assert got == exp, rep
             assert st["n_parts"] >= 3
+
+
+@pytest.mark.parametrize("slots_log2", [13, 14, 15])
+@pytest.mark.parametrize("offsets", [False, True])
+def test_batch_scatter_rounds_by_key_width(gpu, monkeypatch, slots_log2, offsets):
+    """Hash jobs of 16, 32 and 64 regions (4 KiB of 8-byte slots each): whole keys go from short rounds to wide ones
+    between the first two; alone, and beside a direct job whose 16-bit offsets keep the batch on short rounds."""
+    monkeypatch.setenv("VX_BATCH_STAGE_KB", "4")
+    rng = np.random.default_rng(slots_log2)
+    n = 1 << (slots_log2 - 1)
+    bk = [(rng.permutation(3 * n)[:n] - 5).astype(np.int32) for _ in range(3)]
+    pk = [rng.integers(-50, 3 * n, m).astype(np.int32) for m in (200_001, 16_385, 8_191)]
+    if offsets:
+        bk.append(rng.permutation(20_000).astype(np.int32))
+        pk.append(rng.integers(-50, 25_000, 3_000_001).astype(np.int32))
+    bp = [rng.integers(-2**31, 2**31, len(x)).astype(np.int32) for x in bk]
+    exp = [oracle.join_agg(a, [b], c, []) for a, b, c in zip(bk, bp, pk)]
+    args = [dev(x) for x in bk], [dev(x) for x in bp], [dev(x) for x in pk]
+    _say("batch scatter rounds", slots_log2, offsets)
+    with gpu.Context(1 * GiB) as c:
+        for rep in range(2):
+            got, st = c.join_batch(*args, tile_rows=4096, block=256, load_factor=0.5)
+            assert got == exp, rep
+        assert st["n_parts"] == len(bk)
