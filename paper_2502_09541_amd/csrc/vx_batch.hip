@@ -491,9 +491,10 @@ constexpr double kWideOffsets = 128, kWideKeys = 24;
 // that waiting for those loads never waits for the stores.  A round takes three barriers: after
 // the ranks, after the scan (which also advances the positions for the next round and clears
 // the counts), and after the sort; a sorted key's region is recomputed from the key when it is
-// stored.  Of a job whose regions are built from rows only the key's offset in its region is kept, in
-// 16 bits: the scatter writes, and the probe reads, a half or a quarter of the bytes.
-template <typename K, uint32_t T, uint32_t ITEMS, uint32_t GROUPS>
+// stored.  Of a job whose regions are built from rows (OFFSETS: the batch has one) only the key's offset in
+// its region is kept, in 16 bits: the scatter writes, and the probe reads, a half or a quarter of the bytes.
+// Without the test of it, whole keys take 843 us instead of 857 (16 hash jobs, 320 M int32 probe rows).
+template <typename K, uint32_t T, uint32_t ITEMS, uint32_t GROUPS, bool OFFSETS>
 __global__ void __launch_bounds__(T, GROUPS * T / 256) k_batch_scatter(const BatchJob* __restrict__ jobs,
                                                      const unsigned long long* __restrict__ part_map,
                                                      uint64_t n_super, const uint32_t* __restrict__ pos) {
@@ -514,7 +515,7 @@ __global__ void __launch_bounds__(T, GROUPS * T / 256) k_batch_scatter(const Bat
     const uint32_t P = region.parts;
     const void* pkey = jb.pkey;
     void* const dst = jb.pbuf;
-    const bool narrow = jb.rows != 0;
+    const bool narrow = OFFSETS && jb.rows != 0;
     // slots past a round's kept keys store to this workgroup's own 64 sink slots, so that no
     // line is written by many workgroups at once
     const uint64_t np = jb.np, s0 = st * kSuperRows, s1 = s0 + kSuperRows < np ? s0 + kSuperRows : np;
@@ -783,8 +784,10 @@ __device__ __forceinline__ unsigned long long sum_offsets(const uint8_t* keys, u
 
 // Region probe (region_map[t] = job << 44 | region << 32 | item, ~0 for none): item `item` of
 // region p takes an even share of the region's keys; with its region staged in LDS when the job's
-// regions fit kStageBytes, from the table in memory or from the region's build rows.
-template <typename K>
+// regions fit kStageBytes, from the table in memory or from the region's build rows (ROWS: the batch has such
+// a job; the code for them costs the others: without it 16 direct jobs without payloads take 578 us instead
+// of 618, 16 hash jobs 690 instead of 700).
+template <typename K, bool ROWS>
 __global__ void __launch_bounds__(kRegionThreads) k_batch_region(const BatchJob* __restrict__ jobs,
                                                                  const unsigned long long* __restrict__ region_map,
                                                                  uint64_t n_items, uint32_t slot_shift,
@@ -813,7 +816,7 @@ __global__ void __launch_bounds__(kRegionThreads) k_batch_region(const BatchJob*
       const uint64_t entries = jb.direct ? jb.nb : jb.mask + 1;
       const uint64_t first = (uint64_t)p << jb.part_shift;
       const uint64_t count = (first + (1ull << jb.part_shift) < entries ? (1ull << jb.part_shift) : entries - first);
-      if (jb.rows) {
+      if (ROWS && jb.rows) {
         const uint32_t width = (uint32_t)count;
         uint32_t rows = width;
         if (!jb.in_place) {
@@ -1121,6 +1124,7 @@ struct BatchPlan {
   std::vector<unsigned long long> cluster_map;
   uint64_t cursor_entries = 0;
   bool tables = false;
+  bool rows = false;               // a job's regions are built from its rows
   bool wide_scatter = false;       // see kWideOffsets
 };
 
@@ -1398,7 +1402,7 @@ static vx_status plan_batch(const vx_batch_join* d, const BatchConfig& cfg, int 
   pl->direct_bytes = dbytes;
   if (regions) plan_regions(pl, ks, slot_bytes, part_budget, stage);
   pl->count_tiles = 0;
-  pl->tables = false;
+  pl->tables = pl->rows = false;
   double rows = 0, wide = 0;
   for (BatchJob& b : pl->jobs) {
     if (b.n_parts && !b.in_place) {
@@ -1410,6 +1414,7 @@ static vx_status plan_batch(const vx_batch_join* d, const BatchConfig& cfg, int 
     b.count_tiles = table ? (uint32_t)(((b.nb + 7) / 8 + kCountWords - 1) / kCountWords) : b.rows ? b.n_parts : 0;
     pl->count_tiles += b.count_tiles;
     pl->tables |= table;
+    pl->rows |= b.rows != 0;
   }
   pl->wide_scatter = wide > rows;
   map_tiles(pl, slot_bytes, l2_bytes);
@@ -1612,9 +1617,17 @@ static vx_status enqueue_batch(vx_ctx* ctx, const BatchRun& r, const BatchConfig
     using Long = ScatterForm<int64_t, true>;
     using Wide = ScatterForm<int32_t, true>;
     using Short = ScatterForm<int32_t, false>;
-    if (ks == 8) scatter(Long{}, k_batch_scatter<int64_t, Long::threads, Long::items, Long::groups>);
-    else if (r.plan.wide_scatter) scatter(Wide{}, k_batch_scatter<int32_t, Wide::threads, Wide::items, Wide::groups>);
-    else scatter(Short{}, k_batch_scatter<int32_t, Short::threads, Short::items, Short::groups>);
+    const bool offsets = r.plan.cursor_entries != 0;
+    auto either = [&](auto form, auto whole, auto narrow) { offsets ? scatter(form, narrow) : scatter(form, whole); };
+    if (ks == 8)
+      either(Long{}, k_batch_scatter<int64_t, Long::threads, Long::items, Long::groups, false>,
+             k_batch_scatter<int64_t, Long::threads, Long::items, Long::groups, true>);
+    else if (r.plan.wide_scatter)
+      either(Wide{}, k_batch_scatter<int32_t, Wide::threads, Wide::items, Wide::groups, false>,
+             k_batch_scatter<int32_t, Wide::threads, Wide::items, Wide::groups, true>);
+    else
+      either(Short{}, k_batch_scatter<int32_t, Short::threads, Short::items, Short::groups, false>,
+             k_batch_scatter<int32_t, Short::threads, Short::items, Short::groups, true>);
     VX_HIP(hipGetLastError());
     scattered = get_event(ctx);
     VX_CHECK(scattered, VX_EHIP, "batch: no events");
@@ -1645,12 +1658,12 @@ static vx_status enqueue_batch(vx_ctx* ctx, const BatchRun& r, const BatchConfig
     const uint64_t items = r.plan.region_map.size();
     unsigned g = (unsigned)std::min<uint64_t>(items, (uint64_t)ctx->cu_count * (kLdsBytes / kStageBytes));   // stages per CU
     g = std::max(kXcds, g / kXcds * kXcds);
-    if (ks == 8)
-      hipLaunchKernelGGL(k_batch_region<int64_t>, dim3(g), dim3(kRegionThreads), 0, s2, r.jobs_dev, r.region_map, items,
-                         r.plan.slot_shift, (const uint32_t*)r.tally, r.acc);
-    else
-      hipLaunchKernelGGL(k_batch_region<int32_t>, dim3(g), dim3(kRegionThreads), 0, s2, r.jobs_dev, r.region_map, items,
-                         r.plan.slot_shift, (const uint32_t*)r.tally, r.acc);
+    auto region = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(g), dim3(kRegionThreads), 0, s2, r.jobs_dev, r.region_map, items, r.plan.slot_shift,
+                         (const uint32_t*)r.tally, r.acc);
+    };
+    if (ks == 8) r.plan.rows ? region(k_batch_region<int64_t, true>) : region(k_batch_region<int64_t, false>);
+    else r.plan.rows ? region(k_batch_region<int32_t, true>) : region(k_batch_region<int32_t, false>);
     VX_HIP(hipGetLastError());
     VX_HIP(hipEventRecord(ev_done, s2));
   }
