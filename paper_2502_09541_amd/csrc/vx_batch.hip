@@ -278,7 +278,7 @@ constexpr uint32_t kLdsBytes = 160 << 10;            // LDS per compute unit
 constexpr uint32_t kRegionThreads = 1024;
 constexpr uint32_t kStageBytes = 128 << 10;          // LDS for one table region
 constexpr uint32_t kRunUnroll = 16;                  // keys in flight per lane in the region probe
-constexpr uint32_t kSinkGroups = 256;                // scatter sink slots: 64 per group of workgroups
+constexpr uint32_t kSinkGroups = 512;                // scatter sink slots: 64 for each workgroup of its largest grid
 
 // How a job maps probe keys to table regions, read from its descriptor once (scalar registers).
 struct RegionFn {
@@ -519,7 +519,7 @@ __global__ void __launch_bounds__(T, GROUPS * T / 256) k_batch_scatter(const Bat
     // slots past a round's kept keys store to this workgroup's own 64 sink slots, so that no
     // line is written by many workgroups at once
     const uint64_t np = jb.np, s0 = st * kSuperRows, s1 = s0 + kSuperRows < np ? s0 + kSuperRows : np;
-    const uint32_t sink = (uint32_t)np + 64u * (blockIdx.x % kSinkGroups) + lane;   // the planner keeps it below 2^32 / key size
+    const uint32_t sink = (uint32_t)np + 64u * blockIdx.x + lane;   // the planner keeps it below 2^32 / key size
     // the previous super-tile's last stores, which may still be going on, read only stage, delta
     // and off[P]
     for (uint32_t j = threadIdx.x; j <= P; j += T) {
@@ -1611,7 +1611,7 @@ static vx_status enqueue_batch(vx_ctx* ctx, const BatchRun& r, const BatchConfig
       put_event(ctx, counted);
     }
     auto scatter = [&](auto form, auto kern) {
-      const unsigned gs = (unsigned)std::min<uint64_t>(ns, (uint64_t)ctx->cu_count * form.groups);
+      const unsigned gs = (unsigned)std::min<uint64_t>({ns, (uint64_t)ctx->cu_count * form.groups, kSinkGroups});
       hipLaunchKernelGGL(kern, dim3(gs), dim3(form.threads), 0, s2, r.jobs_dev, r.part_map, ns, (const uint32_t*)r.tally);
     };
     using Long = ScatterForm<int64_t, true>;
