@@ -1787,8 +1787,10 @@ static vx_status autotune(vx_ctx* ctx, const vx_batch_join* d, int ks, uint32_t 
 struct JobKey {
   const void *bkey, *bpay, *pkey;
   uint64_t nb, np;
+  int32_t key_type, pay_type;   // the columns' widths are in the graph's plan and kernels
   bool operator==(const JobKey& o) const {
-    return bkey == o.bkey && bpay == o.bpay && pkey == o.pkey && nb == o.nb && np == o.np;
+    return bkey == o.bkey && bpay == o.bpay && pkey == o.pkey && nb == o.nb && np == o.np && key_type == o.key_type &&
+           pay_type == o.pay_type;
   }
 };
 
@@ -1796,7 +1798,8 @@ static std::vector<JobKey> job_keys(const vx_batch_join* d) {
   std::vector<JobKey> k(d->n_jobs);
   for (uint32_t j = 0; j < d->n_jobs; ++j)
     k[j] = {d->build_key[j].data, d->build_pay ? d->build_pay[j].data : nullptr, d->probe_key[j].data,
-            d->n_build[j], d->n_probe[j]};
+            d->n_build[j], d->n_probe[j], d->build_key[j].type,
+            d->build_pay && d->build_pay[j].data ? d->build_pay[j].type : 0};
   return k;
 }
 

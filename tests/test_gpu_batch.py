@@ -468,3 +468,20 @@ def test_batch_scatter_rounds_by_key_width(gpu, monkeypatch, slots_log2, offsets
             got, st = c.join_batch(*args, tile_rows=4096, block=256, load_factor=0.5)
             assert got == exp, rep
         assert st["n_parts"] == len(bk)
+
+
+def test_batch_same_buffers_other_widths(gpu, ctx):
+    """The same build and probe buffers, first with an int64 payload column and then with an int32 one that starts at
+    the same address: the kept graph of the first call is not taken for the second."""
+    import torch
+    rng = np.random.default_rng(53)
+    n = 40_000
+    bk, pk = rng.permutation(n).astype(np.int32), rng.integers(0, 2 * n, 300_001).astype(np.int32)
+    wide = rng.integers(-2**40, 2**40, n)
+    k, p, w = dev(bk), dev(pk), dev(wide)
+    half = w.view(torch.int32)[:n]
+    assert half.data_ptr() == w.data_ptr()
+    for pay, host in ((w, wide), (half, wide.view(np.int32)[:n]), (w, wide)):
+        _say("batch same buffers", pay.dtype)
+        got, _ = ctx.join_batch([k], [pay], [p], tile_rows=4096, block=256, load_factor=0.5)
+        assert got == [oracle.join_agg(bk, [np.ascontiguousarray(host)], pk, [])]
