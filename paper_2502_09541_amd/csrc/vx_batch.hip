@@ -891,7 +891,8 @@ __global__ void __launch_bounds__(512) k_batch_phase(const BatchJob* jobs, uint3
 }
 
 // The build phase where some jobs are built by regions: their rows' tiles, then the tiles of the tables
-// in memory as in k_batch_phase.
+// in memory as in k_batch_phase.  The bound of two workgroups per compute unit leaves a lane 64 registers, and
+// 5 to 26 spill (40 bytes of scratch for int32 keys and payloads); its 45 us run beside a longer count.
 template <typename K, typename P>
 __global__ void __launch_bounds__(kClusterThreads, 8) k_batch_build(const BatchJob* __restrict__ jobs,
                                                                     const unsigned long long* __restrict__ cluster_map,
@@ -1439,7 +1440,7 @@ struct BatchRun {
   uint64_t counter_words = 0;
 };
 
-// Probe by regions unless VX_BATCH_REGIONS=0; VX_BATCH_STAGE_KB (at most 64) lowers the size of a
+// Probe by regions unless VX_BATCH_REGIONS=0; VX_BATCH_STAGE_KB (at most 128) lowers the size of a
 // region staged in LDS, so that small inputs exercise every path.
 static bool regions_enabled() {
   const char* e = getenv("VX_BATCH_REGIONS");

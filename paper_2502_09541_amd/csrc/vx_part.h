@@ -36,7 +36,7 @@ struct PartIO {
   const void* pay[4];
   uint32_t pay_size[4];
   uint64_t n;
-  void* out_key;                 // clustered outputs (device or host-mapped), may be null
+  void* out_key;                 // clustered outputs (device or host-mapped); null for a count
   void* out_pay[4];
   uint64_t out_base;             // row offset added to every output position
 };

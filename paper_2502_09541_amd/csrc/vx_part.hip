@@ -1,4 +1,4 @@
-// Partitioning: ids, per-wave histograms, scan, stable scatter, and vx_partition.
+// Partitioning: ids, counts, the stable scatter in one launch, and vx_partition.
 #include <algorithm>
 #include <cmath>
 #include <cstring>

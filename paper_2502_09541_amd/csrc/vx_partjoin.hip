@@ -214,7 +214,7 @@ __device__ __forceinline__ void pj_build_tile(PjBuildLds& l, const TableView& t,
   __syncthreads();
 }
 
-// One partition's table: its tiles grid-stride.
+// One partition's table: its tiles grid-stride.  (Two workgroups fit a compute unit, by LDS; three are launched.)
 template <typename K>
 __global__ void __launch_bounds__(256) k_pj_build(TableView t, const void* key, const void* pay0,
                                                   uint32_t pay_size, SegList sl, unsigned int* flags,
@@ -1252,7 +1252,11 @@ static vx_status radix_placed(vx_ctx* ctx, const vx_radix_join* d, vx_join_out* 
     // them beside pass 1's two chunk buffers, and then beside a table of at least a quarter of the
     // expected size: building a partition in up to four slices reads its B rows again from device
     // memory, at some 40 G rows/s, where the host copy costs 2 x 16 bytes a row of a 57 GB/s link
-    // (2^24 + 2^24 rows in a 1 GiB arena, two slices a partition: 26.7 -> 13.7 ms).
+    // (2^24 + 2^24 rows in a 1 GiB arena, two slices a partition: 26.7 -> 13.7 ms).  2^23 + 2^23 rows in two
+    // partitions, ms with room for a whole table / half / a quarter / an eighth: 6.35 / 7.02 / 9.25 / 9.26
+    // (Zipf(1.1) build rows 6.3 / 6.5 / 6.7 / 6.7, half of the rows in one key range 6.7 / 7.6 / 10.3 / 10.4),
+    // against 12.6 to 13.1 from host memory in all of them: a quarter is on the safe side, for partitions
+    // far over the expected size.
     const uint64_t pass1_need = 2 * (chunk * rb + 1024) + part_work_bytes(P, chunk) + (32ull << 20);
     const uint64_t pass2_need = table_bytes(exp_rows) / 4 + 2ull * P * 2 * (kMaxSegs + 1) * 8 + (32ull << 20);
     const bool dev = placement == 2 ||

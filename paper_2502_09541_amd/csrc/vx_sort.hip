@@ -2,7 +2,7 @@
 //
 // Pass 1 (the paper's SortExKernel): the column streams through the chunk pipeline in runs of
 // chunk_rows keys.  Each run is sorted on the GPU by an LSD radix sort of 8-bit digits (the sign
-// bit flipped so that signed order comes out) whose stable passes sort tiles of 8192 keys in LDS
+// bit flipped so that signed order comes out) whose stable passes sort tiles of 2048 to 16384 keys in LDS
 // and write each digit's keys of a tile as one run, and is stored to pinned host scratch by a
 // kernel on a second stream: kernel stores to mapped host memory run beside the host-to-device
 // copies.
@@ -167,12 +167,12 @@ __global__ void __launch_bounds__(256) k_store4(const uint32_t* src, uint32_t* d
 // (k_sweep_count, k_sweep_base).  A tile is sorted by digit in LDS and written in LDS order, so
 // each digit's keys of a tile are one run of consecutive addresses (64 keys on average at 16384).
 //
-// 16.0 M int64 keys in one run: 567 us of kernels (k_sweep_count 42 us, 3.0 TB/s; a sweep about
-// 65 us, 3.9 TB/s read and written, against 4.8 TB/s of a large copy), where a histogram launch per
+// 16.0 M int64 keys in one run: 576 us of kernels (k_sweep_count 40 us, 3.2 TB/s; a sweep 66.4 us,
+// 3.9 TB/s read and written, against 4.8 TB/s of a large copy), where a histogram launch per
 // pass, a three-launch column scan and a scatter took 1185 us (44 + 36 + 68 us a pass).  What bounds
 // a sweep is the ranking: with 11 vector instructions per digit bit instead of 4 (same_id) it took
-// 94 us.  The look-back is hidden behind other tiles' work: windows of 4, 8, 16 and 32 tiles gave
-// 752, 751, 779 and 846 us.
+// 94 us.  The look-back is hidden behind other tiles' work: with windows of 4, 8, 16 and 32 tiles a sweep
+// takes 66.8, 66.4, 67.6 and 74.0 us (tiles of 16384 keys).
 constexpr uint32_t kDigitThreads = 1024;
 constexpr uint32_t kDigitWaves = kDigitThreads / 64;
 constexpr uint32_t kLocalSortMax = 8192;                        // runs sorted by one workgroup in LDS
@@ -505,7 +505,7 @@ void merge_cuts_t(const K* const* runs, const uint64_t* len, uint32_t n_runs, ui
 }
 
 // Device scratch of one run's radix sort: look-back words, digit bases, tickets (digit_tile's rule
-// needs at most 2048 bytes of words per 4096 keys up to 2^18 keys, and per 8192 keys beyond).
+// needs 2048 bytes of words per 2048 keys up to 2^16 keys, per 4096 up to 2^18, and per 8192 at least beyond).
 uint64_t sweep_bytes(uint64_t rows) {
   return 3072 * std::max<uint64_t>(1, (rows + 8191) / 8192) + 262144;
 }
@@ -514,7 +514,9 @@ uint64_t sweep_bytes(uint64_t rows) {
 // small tiles writes shorter runs per digit and looks back over more tiles.  Sort kernels of one run,
 // int64 keys, us at tiles of 2048 / 4096 / 8192 / 16384: 20,000 keys 58 / 64 / 77 / 111; 262,144
 // keys - / 92 / 96 / 120; 1.0 M - / 141 / 130 / 148; 2.0 M - / 196 / 159 / 167; 4.0 M - / 299 / 249 /
-// 191; 16.0 M - / 844 / 714 / 566.
+// 191; 16.0 M - / 844 / 714 / 566.  A tile of 8192 int64 keys takes 83,992 bytes of LDS and 78 registers a
+// lane, just past what two workgroups per compute unit may have, and so is measured at one, like the tile of
+// 16384; the smaller ones run at two.
 uint32_t digit_tile(uint64_t rows) {
   return rows <= (1ull << 16) ? 2048 : rows <= (1ull << 18) ? 4096 : rows <= (1ull << 21) ? 8192 : 16384;
 }
