@@ -44,6 +44,7 @@
 #include <cstring>
 #include <fstream>
 #include <map>
+#include <mutex>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -1697,7 +1698,9 @@ static vx_status enqueue_batch(vx_ctx* ctx, const BatchRun& r, const BatchConfig
   return VX_OK;
 }
 
+// Shared by every context, whichever thread uses it.
 struct TuneCache {
+  std::mutex lock;
   std::map<std::string, BatchConfig> m;
 };
 
@@ -1718,6 +1721,7 @@ static std::string class_key(const vx_ctx* ctx, const vx_batch_join* d, int ks) 
 }
 
 static bool load_tuned(const std::string& key, BatchConfig* c) {
+  std::lock_guard<std::mutex> hold(g_tune.lock);
   auto it = g_tune.m.find(key);
   if (it != g_tune.m.end()) {
     *c = it->second;
@@ -1739,6 +1743,7 @@ static bool load_tuned(const std::string& key, BatchConfig* c) {
 }
 
 static void store_tuned(const std::string& key, const BatchConfig& c) {
+  std::lock_guard<std::mutex> hold(g_tune.lock);
   g_tune.m[key] = c;
   const char* path = getenv("VX_TUNE_CACHE");
   if (!path) return;
@@ -1813,8 +1818,6 @@ struct GraphCache {
   BatchRun* run = nullptr;
 };
 
-static std::map<const vx_ctx*, GraphCache*> g_graphs;
-
 static void drop_graph(GraphCache* g) {
   if (!g) return;
   if (g->exec) (void)hipGraphExecDestroy(g->exec);
@@ -1823,13 +1826,9 @@ static void drop_graph(GraphCache* g) {
   delete g;
 }
 
-
-void batch_release_ctx(const vx_ctx* ctx) {
-  auto it = g_graphs.find(ctx);
-  if (it != g_graphs.end()) {
-    drop_graph(it->second);
-    g_graphs.erase(it);
-  }
+void batch_release_ctx(vx_ctx* ctx) {
+  drop_graph(ctx->batch_graph);
+  ctx->batch_graph = nullptr;
 }
 
 vx_status join_batch(vx_ctx* ctx, const vx_batch_join* d, vx_join_out* out) {
@@ -1868,11 +1867,8 @@ vx_status join_batch(vx_ctx* ctx, const vx_batch_join* d, vx_join_out* out) {
   if (d->flags & VX_HASHED) di.direct.assign(J, 0);   // every job hashed; the ranges still filter probes
   const double t_checked = now_ms();
   if (d->mode == 0) {   // a graph kept for other jobs gives its arena memory back before tuning
-    auto it = g_graphs.find(ctx);
-    if (it != g_graphs.end() && it->second && !(it->second->key == job_keys(d) && it->second->di == di)) {
-      drop_graph(it->second);
-      it->second = nullptr;
-    }
+    const GraphCache* kept = ctx->batch_graph;
+    if (kept && !(kept->key == job_keys(d) && kept->di == di)) batch_release_ctx(ctx);
   }
   BatchConfig cfg;
   bool tuned = d->tile_rows == 0 || d->block == 0 || d->load_factor == 0.0f;
@@ -1890,7 +1886,7 @@ vx_status join_batch(vx_ctx* ctx, const vx_batch_join* d, vx_join_out* out) {
   vx_stats& s = out->stats;
   std::memset(&s, 0, sizeof s);
   if (d->mode == 0) {
-    GraphCache*& gc = g_graphs[ctx];
+    GraphCache*& gc = ctx->batch_graph;
     if (!gc || !(gc->key == job_keys(d)) || !(gc->di == di) || gc->cfg.tile_rows != cfg.tile_rows ||
         gc->cfg.block != cfg.block || gc->cfg.load_factor != cfg.load_factor) {
       drop_graph(gc);
@@ -2000,7 +1996,7 @@ vx_status join_batch(vx_ctx* ctx, const vx_batch_join* d, vx_join_out* out) {
     s.table_bytes = (r.plan.slots << r.plan.slot_shift) + r.plan.direct_bytes;
   }
   // accumulators are in tile order: entry i belongs to the caller's job job_of[i]
-  const std::vector<uint32_t>& job_of = d->mode == 0 ? g_graphs[ctx]->run->plan.job_of : order;
+  const std::vector<uint32_t>& job_of = d->mode == 0 ? ctx->batch_graph->run->plan.job_of : order;
   uint64_t rows = 0;
   for (uint32_t i = 0; i < J; ++i) {
     const uint32_t j = job_of[i];

@@ -81,6 +81,8 @@ struct ArenaBlock {
 
 // ---------------------------------------------------------------- columns
 
+struct GraphCache;   // the batch join's graph and tables kept for the next call (vx_batch.hip)
+
 enum class Where { Device, Host };
 
 struct ColInfo {
@@ -118,13 +120,14 @@ struct vx_ctx {
   uint8_t* host_scratch = nullptr;
   uint64_t host_scratch_bytes = 0;
   std::vector<hipEvent_t> ev_pool;
+  vx::GraphCache* batch_graph = nullptr;
   uint32_t zc_line = 128;   // zero-copy transfer granule (bytes), measured by vx_calibrate
 };
 
 namespace vx {
 
 // Drop the batch join's cached graph and tables held for this context.
-void batch_release_ctx(const vx_ctx* ctx);
+void batch_release_ctx(vx_ctx* ctx);
 // Give back arena memory that a call keeps for reuse by the next call of its kind (the batch
 // join's graph and tables): every entry point that does not reuse it calls this first, so its
 // working set sees the whole arena.

@@ -485,3 +485,40 @@ def test_batch_same_buffers_other_widths(gpu, ctx):
         _say("batch same buffers", pay.dtype)
         got, _ = ctx.join_batch([k], [pay], [p], tile_rows=4096, block=256, load_factor=0.5)
         assert got == [oracle.join_agg(bk, [np.ascontiguousarray(host)], pk, [])]
+
+
+def test_batch_contexts_on_their_own_threads(gpu):
+    """Four contexts, each on a thread and a stream of its own, alternate batches (whose graph and tuning are kept)
+    with a join that gives the kept graph's arena memory back."""
+    import threading
+
+    import torch
+    rng = np.random.default_rng(61)
+    work = []
+    for w in range(4):
+        bk = [rng.permutation(n).astype(np.int32) for n in (500 + w, 40_000 + w, 90_001)]
+        pk = [rng.integers(0, 2 * len(b), 5 * len(b)).astype(np.int32) for b in bk]
+        exp = [[int((p < len(b)).sum()), int(p[p < len(b)].sum())] for b, p in zip(bk, pk)]
+        work.append(([dev(b) for b in bk], [dev(p) for p in pk], exp))
+    torch.cuda.synchronize()
+    errors = []
+
+    def run(w):
+        try:
+            bk, pk, exp = work[w]
+            with gpu.Context(512 << 20, stream=torch.cuda.Stream()) as c:
+                for i in range(8):
+                    got, _ = c.join_batch(bk, bk, pk)
+                    assert got == exp, (w, i)
+                    if i % 3 == 2:
+                        assert c.join_plain(bk[1], [bk[1]], pk[1])[0] == exp[1]
+        except Exception as e:   # noqa: BLE001
+            errors.append(e)
+
+    _say("batch contexts on threads")
+    threads = [threading.Thread(target=run, args=(w,)) for w in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
