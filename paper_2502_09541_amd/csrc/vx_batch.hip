@@ -1818,8 +1818,14 @@ struct GraphCache {
   BatchRun* run = nullptr;
 };
 
+// Graphs are captured, instantiated, launched and destroyed by one thread at a time: four contexts on threads of
+// their own, each doing so, once ended the process with a segmentation fault inside these calls or the
+// library's beside them.  The cause is not known, and that case has not been run again.
+static std::mutex g_graph_calls;
+
 static void drop_graph(GraphCache* g) {
   if (!g) return;
+  std::lock_guard<std::mutex> hold(g_graph_calls);
   if (g->exec) (void)hipGraphExecDestroy(g->exec);
   if (g->graph) (void)hipGraphDestroy(g->graph);
   delete g->run;
@@ -1899,6 +1905,7 @@ vx_status join_batch(vx_ctx* ctx, const vx_batch_join* d, vx_join_out* out) {
       auto build = [&]() -> vx_status {
         VX_TRY(setup_run(ctx, d, cfg, ks, ps, di, ng->run));
         VX_HIP(hipStreamSynchronize(ctx->compute));
+        std::lock_guard<std::mutex> hold(g_graph_calls);
         VX_HIP(hipStreamBeginCapture(ctx->compute, hipStreamCaptureModeThreadLocal));
         vx_status cst = enqueue_batch(ctx, *ng->run, cfg, ks, J, ctx->compute, ctx->host_acc);
         hipError_t ce = hipStreamEndCapture(ctx->compute, &ng->graph);
@@ -1919,7 +1926,10 @@ vx_status join_batch(vx_ctx* ctx, const vx_batch_join* d, vx_join_out* out) {
     }
     hipEvent_t a = get_event(ctx), b = get_event(ctx);
     VX_HIP(hipEventRecord(a, ctx->compute));
-    VX_HIP(hipGraphLaunch(gc->exec, ctx->compute));
+    {
+      std::lock_guard<std::mutex> hold(g_graph_calls);
+      VX_HIP(hipGraphLaunch(gc->exec, ctx->compute));
+    }
     VX_HIP(hipEventRecord(b, ctx->compute));
     VX_HIP(hipStreamSynchronize(ctx->compute));
     float ms = 0;
